@@ -162,7 +162,10 @@ ampd_status ampd_kv_unpack(const ampd_kv_cache *cache, const ampd_batch *batch, 
  * bf16 cache: the page writes ride in the attention launch as work items of their own and the
  * attention items read the new tokens from k_new / v_new (which, like every DEVICE argument,
  * must stay valid until the call's stream work is done).  8-bit cache: a quantising append
- * launch runs first and attention reads the quantised pages.
+ * launch runs first and attention reads the quantised pages; in a batch of decode rows alone
+ * (every row has at most 32 query rows per KV head; up to 128 rows with new tokens) the items
+ * that read a row's last pages quantise its new tokens themselves, and the work list travels
+ * in the kernel's arguments.
  * q: DEVICE bf16 [sum L][Hq][d];  out: DEVICE bf16 [sum L][Hq][d].
  * workspace: DEVICE, 256-byte aligned, >= ampd_workspace_bytes(). */
 ampd_status ampd_incr_prefill_attn(const ampd_kv_cache *cache, const ampd_batch *batch,
@@ -229,9 +232,10 @@ typedef struct {
     int64_t num_wide_items;     /* prefill tiles: up to 256 query rows, 8 waves share K/V tiles */
     int64_t num_narrow_items;   /* decode-style items: <= 32 query rows, 8 waves split the keys */
     int64_t num_combine_items;  /* query tiles whose key range was split */
-    int64_t num_append_launches; /* append launches that precede the attention launch (8-bit cache; 0 for bf16) */
+    int64_t num_append_launches; /* append launches that precede the attention launch (8-bit cache; 0 for bf16, and for
+                                 * decode rows alone, whose items append) */
     int64_t partial_bytes;      /* split-KV partial results inside the workspace */
-    int64_t plan_bytes;         /* work list inside the workspace */
+    int64_t plan_bytes;         /* work list inside the workspace (0: it travels in the kernel's arguments) */
     int64_t num_append_items;   /* bf16 cache: page-write items (64 packed rows each) that close the attention launch */
     int64_t num_workgroups;     /* workgroups of the attention launch: num_items, or 256 persistent workgroups that work
                                  * through the items when the launch holds tiles and more items than that */

@@ -240,16 +240,17 @@ ampd_status stage_plan(DeviceState& d, const Plan& plan, void* workspace, bool m
 // device must have been set up by ampd_init) and records no timing events.
 ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& plan, const void* q, void* out,
                     void* workspace, hipStream_t st, const void* k_new = nullptr, const void* v_new = nullptr) {
-    if (plan.items.empty()) return k_new ? do_append(c, b, k_new, v_new, st) : AMPD_OK;
+    if (plan.num_items == 0) return k_new ? do_append(c, b, k_new, v_new, st) : AMPD_OK;
     const bool use_static = workspace == nullptr;
     const bool timing = t_timing && !use_static;
     // bf16 cache: the page writes are append items of the attention launch (the plan holds them), and the attention
     // items read the new tokens from k_new / v_new; 8-bit cache: a quantising append launch goes first
-    const bool fused_append = k_new && plan.num_append > 0;
+    // (decode rows alone: inside the items that read the pages)
+    const bool fused_append = k_new && (plan.num_append > 0 || plan.by_table);
     uint32_t* slot_flag = nullptr;     // the attention launch below releases the staging slot through these
     uint32_t slot_seq = 0;
 
-    {
+    if (use_static || !plan.by_table) {
         std::lock_guard<std::mutex> lk(g_mu);
         DeviceState* d = nullptr;
         if (use_static) {
@@ -261,19 +262,21 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
         } else {
             HIP_TRY(ensure_device(&d));
         }
-        Slot* s = nullptr;
-        PendingUpload up;
-        ampd_status vs = stage_plan(*d, plan, workspace, !use_static, &s, &up);
-        if (vs != AMPD_OK) return vs;
-        if (k_new && !fused_append) {
-            vs = do_append(c, b, k_new, v_new, st, 0, 0, -1, &up);     // the work list rides on the append launch
+        if (!plan.by_table) {                                          // (a table travels in the kernels' arguments)
+            Slot* s = nullptr;
+            PendingUpload up;
+            ampd_status vs = stage_plan(*d, plan, workspace, !use_static, &s, &up);
             if (vs != AMPD_OK) return vs;
+            if (k_new && !fused_append) {
+                vs = do_append(c, b, k_new, v_new, st, 0, 0, -1, &up);     // the work list rides on the append launch
+                if (vs != AMPD_OK) return vs;
+            }
+            if (up.bytes > 0) HIP_TRY(launch_upload(up.src, up.dst, up.bytes, st));
+            s->seq = ++d->seq;
+            s->pending = true;
+            slot_flag = s->flag;
+            slot_seq = s->seq;
         }
-        if (up.bytes > 0) HIP_TRY(launch_upload(up.src, up.dst, up.bytes, st));
-        s->seq = ++d->seq;
-        s->pending = true;
-        slot_flag = s->flag;
-        slot_seq = s->seq;
     }
 
     char* ws = static_cast<char*>(workspace);
@@ -293,7 +296,7 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
     p.combs = reinterpret_cast<const CombItem*>(ws + plan.off_combs);
     p.partial = reinterpret_cast<float*>(ws + plan.off_partial);
     p.queue_heads = reinterpret_cast<int32_t*>(ws + plan.off_queues);
-    p.nitems = (int32_t)plan.items.size();
+    p.nitems = (int32_t)plan.num_items;
     p.Hq = c->num_q_heads;
     p.Hkv = c->num_kv_heads;
     p.P = c->page_size;
@@ -305,14 +308,21 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
     const int kvt = c->kv_dtype == AMPD_KV_FP8_E4M3 ? KV_FP8 : KV_BF16;
 
     if (timing) HIP_TRY(hipEventRecord(t_ev[1], st));
-    HIP_TRY(launch_attn(p, c->head_dim, kvt, plan.grid, st));
+    HIP_TRY(plan.by_table ? launch_rows(p, plan.table, kvt, plan.grid, st) : launch_attn(p, c->head_dim, kvt, plan.grid, st));
     if (timing) HIP_TRY(hipEventRecord(t_ev[2], st));
     int comb_rows = 0, comb_splits = 0;
     for (const CombItem& ci : plan.combs) {
         comb_rows = std::max(comb_rows, ci.nq * ((ci.heads >> 16) & 0xff));
         comb_splits = std::max(comb_splits, (int)ci.nsplit);
     }
-    HIP_TRY(launch_combine(p, c->head_dim, (int)plan.combs.size(), comb_rows, comb_splits, st));
+    for (int i = 0; plan.by_table && i < plan.table.n; ++i) {
+        const RowTable& t = plan.table;
+        const int L = t.e[i].req_L >> 24;
+        if (t.e[i].part_off < 0) continue;
+        comb_rows = std::max(comb_rows, L * t.G);
+        comb_splits = std::max(comb_splits, (t.e[i].C + L + t.chunk - 1) / t.chunk);
+    }
+    HIP_TRY(launch_combine(p, plan.by_table ? &plan.table : nullptr, c->head_dim, (int)plan.num_combs, comb_rows, comb_splits, st));
     if (timing) {
         HIP_TRY(hipEventRecord(t_ev[3], st));
         t_valid = true;
@@ -442,7 +452,7 @@ ampd_status ampd_paged_attn(const ampd_kv_cache* cache, const ampd_batch* batch,
     vs = make_plan(cache, batch, opts, false, &planp);
     if (vs != AMPD_OK) return vs;
     const Plan& plan = *planp;
-    if (plan.items.empty()) return AMPD_OK;
+    if (plan.num_items == 0) return AMPD_OK;
     if (!q || !out) return AMPD_ERR_INVALID_ARG;
     vs = check_workspace(plan, workspace, workspace_bytes);
     if (vs != AMPD_OK) return vs;

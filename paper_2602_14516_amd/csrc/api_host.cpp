@@ -96,7 +96,7 @@ ampd_status make_plan(const ampd_kv_cache* c, const ampd_batch* b, const ampd_pl
         t_key = std::move(key);
         t_plan_valid = true;
     }
-    if (t_plan.partial_floats > 0x7fffffff || t_plan.items.size() > 0x7fffffffu) return AMPD_ERR_UNSUPPORTED;
+    if (t_plan.partial_floats > 0x7fffffff || t_plan.num_items > 0x7fffffff) return AMPD_ERR_UNSUPPORTED;
     *plan = &t_plan;
     return AMPD_OK;
 }
@@ -129,12 +129,12 @@ ampd_status ampd_plan_describe(const ampd_kv_cache* cache, const ampd_batch* bat
     vs = make_plan(cache, batch, opts, true, &planp);
     if (vs != AMPD_OK) return vs;
     const Plan& plan = *planp;
-    info->num_items = (int64_t)plan.items.size();
+    info->num_items = plan.num_items;
     info->num_wide_items = plan.num_wide;
     info->num_narrow_items = plan.num_narrow;
-    info->num_combine_items = (int64_t)plan.combs.size();
+    info->num_combine_items = plan.num_combs;
     info->num_append_items = plan.num_append;
-    info->num_append_launches = plan.num_append > 0 ? 0 : (batch->num_reqs + APPEND_MAX_REQS - 1) / APPEND_MAX_REQS;
+    info->num_append_launches = plan.num_append > 0 || plan.by_table ? 0 : (batch->num_reqs + APPEND_MAX_REQS - 1) / APPEND_MAX_REQS;
     info->partial_bytes = plan.partial_floats * 4;
     info->plan_bytes = plan.plan_bytes;
     info->num_workgroups = plan.grid;
@@ -149,9 +149,11 @@ int64_t ampd_plan_items(const ampd_kv_cache* cache, const ampd_batch* batch, con
     vs = make_plan(cache, batch, opts, true, &planp);
     if (vs != AMPD_OK) return vs;
     const Plan& plan = *planp;
-    const int64_t n = (int64_t)plan.items.size();
+    std::vector<Item> items;
+    if (h_items && max_items > 0) plan_items(plan, items);
+    const int64_t n = plan.num_items;
     for (int64_t i = 0; i < n && i < max_items && h_items; ++i) {
-        const Item& it = plan.items[i];
+        const Item& it = items[i];
         int32_t* o = h_items + i * 10;
         o[0] = it.req;
         o[1] = (it.heads >> 24) & 0xff;

@@ -13,7 +13,7 @@ struct AttnParams {
     const void* q;             // bf16 [sum L][Hq][D]
     void* out;                 // bf16 [sum L][Hq][D]
     const void* k_new;         // bf16 [sum L][Hkv][D]: the new tokens of this call when their page writes ride in the
-    const void* v_new;         //   attention launch (bf16 cache; keys >= C are then read from here), else null
+    const void* v_new;         //   attention launch (bf16 cache: keys >= C are then read from here), else null
     const void* k_pool;        // [pages][Hkv][P][D]
     const void* v_pool;
     const float* k_scale;      // [pages][Hkv] (8-bit cache) or null
@@ -55,8 +55,10 @@ struct AppendParams {
 // h_src: pinned, device-visible host memory; bytes is rounded up to 16
 hipError_t launch_upload(const void* h_src, void* d_dst, size_t bytes, hipStream_t st);
 hipError_t launch_attn(const AttnParams& p, int D, int kvt, int grid, hipStream_t st);
+// a batch of decode rows alone, whose list travels in the arguments; p.k_new: the call appends (both kinds of cache)
+hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid, hipStream_t st);
 // max_rows: the largest nq * heads among the split tiles (sizes the second grid dimension)
-hipError_t launch_combine(const AttnParams& p, int D, int ncombs, int max_rows, int max_splits, hipStream_t st);
+hipError_t launch_combine(const AttnParams& p, const RowTable* t, int D, int ncombs, int max_rows, int max_splits, hipStream_t st);
 hipError_t launch_append(const AppendParams& p, int kvt, int max_pages_touched, int nreq, hipStream_t st);
 // bf16 only: pack = pages -> packed rows (k_new / v_new are written), otherwise packed rows -> pages
 hipError_t launch_kv_move(const AppendParams& p, bool pack, int max_pages_touched, int nreq, hipStream_t st);

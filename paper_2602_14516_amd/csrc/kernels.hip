@@ -139,8 +139,8 @@ struct ItemCtx {
 };
 constexpr int NEVER = 0x3fffffff;
 
-__device__ __forceinline__ ItemCtx load_item(const AttnParams& p, int idx) {
-    const Item it = p.items[idx];
+template <int KVT>
+__device__ __forceinline__ ItemCtx item_ctx(const AttnParams& p, const Item& it) {
     ItemCtx c;
     c.req = it.req;
     c.kvh = it.heads & 0xff;
@@ -153,7 +153,7 @@ __device__ __forceinline__ ItemCtx load_item(const AttnParams& p, int idx) {
     c.part_off = it.part_off;
     c.C = it.C;
     c.row_off = it.row_off;
-    c.c_rows = p.k_new ? it.C : NEVER;
+    c.c_rows = KVT == KV_BF16 && p.k_new ? it.C : NEVER;
     c.bt_row = p.block_table + (int64_t)it.req * p.max_pages;
     return c;
 }
@@ -370,9 +370,9 @@ __device__ __forceinline__ void pv16(uint32_t vl, const bf16x8& P, WaveAcc16<D>&
     }
 }
 
+// S^T and its softmax; P = the operand of the second product
 template <int D>
-__device__ __forceinline__ void block16(uint32_t kl, uint32_t vl, const bf16x8 (&Q)[D / 32], WaveAcc16<D>& st,
-                                        float c, int rel, bool masked, int lane) {
+__device__ __forceinline__ bf16x8 softmax16(uint32_t kl, const bf16x8 (&Q)[D / 32], WaveAcc16<D>& st, float c, int rel, bool masked, int lane) {
     f32x4 S[2];
     qk16<D>(kl, Q, S, lane);
     if (masked) mask16(S, rel);                          // wave-uniform
@@ -389,7 +389,7 @@ __device__ __forceinline__ void block16(uint32_t kl, uint32_t vl, const bf16x8 (
         P[i] = (__bf16)pv;
     }
     st.l += psum;
-    pv16<D>(vl, P, st, lane);
+    return P;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -573,7 +573,7 @@ __device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" :
 //                 registers; the data is in LDS once the vector-memory counter has drained,
 //                 which the barrier that ends a pipeline step waits for.
 //   DMA = false: global -> registers (fetch_kv) -> LDS (commit), widening 8-bit codes.
-template <int D, int KVT, int NTHR, int NKEYS>
+template <int D, int KVT, int NTHR, int NKEYS, bool FRESH_SCALES = false>
 struct Loader {
     using G_ = Geo<D>;
     static constexpr int KPW = G_::KPW;
@@ -671,9 +671,15 @@ struct Loader {
         return (uint32_t)(((l >> 2) % KPW) * p.Hkv * D * 2 + ((l / (4 * KPW)) * 4 + (l & 3)) * 16);
     }
 
+    // FRESH_SCALES: this workgroup may have written the scale itself (see append_item_pages), so it is read through the
+    // vector memory path; the scalar cache would not see the store.
+    __device__ __forceinline__ static float scale_at(const float* s) {
+        if constexpr (FRESH_SCALES) return __hip_atomic_load(s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else return *s;
+    }
     // ---- register-staged path
     // FULL: the whole tile lies inside the key range and in the pages
-    template <bool FULL>
+    template <bool FULL, bool DO_K, bool DO_V>
     __device__ __forceinline__ void fetch_kv_impl(const AttnParams& p, const ItemCtx& ic, int kbase, int t) {
         const uint32_t lo = lane_off(t);
 #pragma unroll
@@ -683,48 +689,60 @@ struct Loader {
             // of key 16, the first of the second page when pages hold 16 keys (with larger pages slot 1 is never read)
             const int sl = !TWO_SCALES ? ps : ps == 0 ? 0 : ps == 16 / KPP ? 1 : -1;
             if (sl >= 0) {
-                ks[sl] = 1.0f;
-                vs[sl] = 1.0f;
+                if (DO_K) ks[sl] = 1.0f;
+                if (DO_V) vs[sl] = 1.0f;
                 if (KVT == KV_FP8 && (FULL || r.key0 < ic.kv_end)) {   // (a group past the key range has no page)
-                    ks[sl] = p.k_scale[(int64_t)r.page * p.Hkv + ic.kvh];
-                    vs[sl] = p.v_scale[(int64_t)r.page * p.Hkv + ic.kvh];
+                    if (DO_K) ks[sl] = scale_at(p.k_scale + (int64_t)r.page * p.Hkv + ic.kvh);
+                    if (DO_V) vs[sl] = scale_at(p.v_scale + (int64_t)r.page * p.Hkv + ic.kvh);
                 }
             }
             const int key = r.key0 + lane_key(t);
             if (FULL || (key < ic.kv_end && key < ic.c_rows)) {
-                k[ps].load(r.kb, lo);
-                v[ps].load(r.vb, lo);
+                if (DO_K) k[ps].load(r.kb, lo);
+                if (DO_V) v[ps].load(r.vb, lo);
             } else if (KVT == KV_BF16 && key < ic.kv_end) {      // a new token of this call: read its packed row
                 const Row n = new_row_of(p, ic, r);
                 const uint32_t nlo = new_lane_off(p, t);
-                k[ps].load(n.kb, nlo);
-                v[ps].load(n.vb, nlo);
+                if (DO_K) k[ps].load(n.kb, nlo);
+                if (DO_V) v[ps].load(n.vb, nlo);
             } else {
-                k[ps].zero();                                    // keys past the item's end: zeros, so
-                v[ps].zero();                                    // that 0-weights never meet NaN garbage
+                if (DO_K) k[ps].zero();                          // keys past the item's end: zeros, so
+                if (DO_V) v[ps].zero();                          // that 0-weights never meet NaN garbage
             }
         }
     }
+    template <bool DO_K = true, bool DO_V = true>
     __device__ __forceinline__ void fetch_kv(const AttnParams& p, const ItemCtx& ic, int kbase, int t) {
         if (kbase + NKEYS <= min(ic.kv_end, ic.c_rows))          // uniform: whole tile inside the key range, in pages
-            fetch_kv_impl<true>(p, ic, kbase, t);
+            fetch_kv_impl<true, DO_K, DO_V>(p, ic, kbase, t);
         else
-            fetch_kv_impl<false>(p, ic, kbase, t);
+            fetch_kv_impl<false, DO_K, DO_V>(p, ic, kbase, t);
     }
     // kl / vl: LDS byte addresses of this tile's K and V
+    __device__ __forceinline__ void commit_k(const AttnParams& p, uint32_t kl, int t) const {
+#pragma unroll
+        for (int ps = 0; ps < NPASS; ++ps) put(k[ps], k_scale_of(p, ps), kl + slot_of(ps, t));
+    }
+    __device__ __forceinline__ void commit_v(const AttnParams& p, uint32_t vl, int t) const {
+#pragma unroll
+        for (int ps = 0; ps < NPASS; ++ps) put(v[ps], v_scale_of(p, ps), vl + slot_of(ps, t));
+    }
     __device__ __forceinline__ void commit(const AttnParams& p, uint32_t kl, uint32_t vl, int t) const {
 #pragma unroll
         for (int ps = 0; ps < NPASS; ++ps) {
-            const uint32_t o = ((ps * NW + (t >> 6)) * GPP + lane_group(t)) * G_::GS + lane_slot(t) * 16;
-            if constexpr (KVT == KV_FP8) {
-                *LDS_PTR(u32x4, kl + o) = k[ps].widen_first(k_scale_of(p, ps));
-                *LDS_PTR(u32x4, kl + o + 16) = k[ps].widen_second(k_scale_of(p, ps));
-                *LDS_PTR(u32x4, vl + o) = v[ps].widen_first(v_scale_of(p, ps));
-                *LDS_PTR(u32x4, vl + o + 16) = v[ps].widen_second(v_scale_of(p, ps));
-            } else {
-                *LDS_PTR(u32x4, kl + o) = k[ps].widen(k_scale_of(p, ps));
-                *LDS_PTR(u32x4, vl + o) = v[ps].widen(v_scale_of(p, ps));
-            }
+            put(k[ps], k_scale_of(p, ps), kl + slot_of(ps, t));
+            put(v[ps], v_scale_of(p, ps), vl + slot_of(ps, t));
+        }
+    }
+    __device__ __forceinline__ static uint32_t slot_of(int ps, int t) {
+        return ((ps * NW + (t >> 6)) * GPP + lane_group(t)) * G_::GS + lane_slot(t) * 16;
+    }
+    __device__ __forceinline__ static void put(const RawChunk<KVT>& c, float scale, uint32_t at) {
+        if constexpr (KVT == KV_FP8) {
+            *LDS_PTR(u32x4, at) = c.widen_first(scale);
+            *LDS_PTR(u32x4, at + 16) = c.widen_second(scale);
+        } else {
+            *LDS_PTR(u32x4, at) = c.widen(scale);
         }
     }
 
@@ -913,14 +931,182 @@ __device__ __forceinline__ void wide_body(const AttnParams& p, const ItemCtx& ic
 }
 
 // ---------------------------------------------------------------------------------------------
-// narrow body: <= 32 query rows; the 8 waves take 32-key blocks round-robin, each through its
-// own LDS region, and merge their (m, l, O) through LDS at the end
+// narrow body: <= 32 query rows; the 32-key blocks of the key range belong round-robin to 8 softmax states, which are
+// merged through LDS at the end.  A workgroup of 8 waves keeps one state per wave, one of 4 waves two per wave (the same
+// blocks in the same order per state, so the result is the same bit for bit); a wave stages its blocks through an LDS
+// region of its own.
 
 // ROWS: query rows a wave carries (32, or 16 for items of at most 16 rows: half the matrix and softmax work per key)
-template <int D, int KVT, int ROWS>
+__device__ __forceinline__ int exponent_for(float amax) {
+    // smallest e with amax <= 448 * 2^e  (448 = 1.75 * 2^8), clamped to [-40, 119]
+    const uint32_t u = __float_as_uint(amax);
+    const int ex = (int)(u >> 23) - 127;
+    const uint32_t man = u & 0x7fffffu;
+    int e = (man <= 0x600000u) ? ex - 8 : ex - 7;
+    if ((u >> 23) == 0) e = -40;                              // zero / subnormal
+    return min(119, max(-40, e));
+}
+
+__device__ __forceinline__ uint32_t encode4(float a, float b, float c, float d) {
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
+    return (uint32_t)w;
+}
+
+// The three passes over one (page, KV head) of K or V that an append into an 8-bit cache takes, by nthr threads (this one: t).
+// src: packed row of the first new token of this page and head (consecutive tokens row_bytes apart); n: new tokens of the page.
+__device__ __forceinline__ u32x4 new_chunk(const char* src, int64_t row_bytes, int u, int cph) {
+    return *reinterpret_cast<const u32x4*>(src + (u / cph) * row_bytes + (u % cph) * 16);
+}
+// this thread's largest magnitude
+__device__ __forceinline__ float page_amax(const char* src, int64_t row_bytes, int n, int cph, int t, int nthr) {
+    float amax = 0.0f;
+    for (int u = t; u < n * cph; u += nthr) {
+        const u32x4 v = new_chunk(src, row_bytes, u, cph);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            amax = fmaxf(amax, fabsf(__uint_as_float(w[x] << 16)));
+            amax = fmaxf(amax, fabsf(__uint_as_float(w[x] & 0xffff0000u)));
+        }
+    }
+    return amax;
+}
+// the page's first n_old slots held codes of exponent e_old: re-encode them for e > e_old
+__device__ __forceinline__ void page_reencode(uint8_t* pg, int n_old, int D, int e_old, int e, int t, int nthr) {
+    const float f = __uint_as_float((uint32_t)(e_old - e + 127) << 23);     // 2^(e_old - e)
+    for (int u = t; u < n_old * (D / 4); u += nthr) {
+        uint32_t* q4 = reinterpret_cast<uint32_t*>(pg) + u;
+        const uint32_t w = *q4;
+        const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(w, false);
+        const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8(w, true);
+        *q4 = encode4(lo.x * f, lo.y * f, hi.x * f, hi.y * f);
+    }
+}
+// encode the new tokens into the slots from dst on: x * 2^-e, |.| <= 448 by construction
+__device__ __forceinline__ void page_encode(uint8_t* dst, const char* src, int64_t row_bytes, int n, int D, int e, int t, int nthr) {
+    const int cph = D / 8;
+    const float inv = __uint_as_float((uint32_t)(127 - e) << 23);
+    for (int u = t; u < n * cph; u += nthr) {
+        const u32x4 v = new_chunk(src, row_bytes, u, cph);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        float f[8];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            f[2 * x] = __uint_as_float(w[x] << 16) * inv;
+            f[2 * x + 1] = __uint_as_float(w[x] & 0xffff0000u) * inv;
+        }
+        u32x2 o;
+        o.x = encode4(f[0], f[1], f[2], f[3]);
+        o.y = encode4(f[4], f[5], f[6], f[7]);
+        *reinterpret_cast<u32x2*>(dst + (u / cph) * D + (u % cph) * 8) = o;
+    }
+}
+
+// The append of an item's own new tokens into an 8-bit cache (launches of decode rows alone: one item holds all pages of its
+// KV head that new tokens fall into, or shares them with a neighbour page by page, since pieces start at multiples of 64 keys).
+// A wave takes one (page, K or V) at a time.
+template <int D, int NW>
+__device__ __forceinline__ void append_item_pages(const AttnParams& p, const ItemCtx& ic, int tid) {
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int first = max(ic.C, ic.kv_begin);
+    const int lp0 = first >> p.logP, npages = ((ic.kv_end - 1) >> p.logP) - lp0 + 1;
+    const int64_t row_bytes = (int64_t)p.Hkv * D * 2;
+    for (int w = wave; w < 2 * npages; w += NW) {
+        const int lp = lp0 + (w >> 1), is_v = w & 1;
+        const int t0 = max(first, lp << p.logP), t1 = min(ic.kv_end, (lp + 1) << p.logP);
+        const int n_old = max(0, ic.C - (lp << p.logP));
+        const int page = ic.bt_row[lp];
+        const char* src = static_cast<const char*>(is_v ? p.v_new : p.k_new) +
+                          ((int64_t)(ic.row_off + t0 - ic.C) * p.Hkv + ic.kvh) * D * 2;
+        float* scl = const_cast<float*>(is_v ? p.v_scale : p.k_scale) + (int64_t)page * p.Hkv + ic.kvh;
+        uint8_t* pg = static_cast<uint8_t*>(const_cast<void*>(is_v ? p.v_pool : p.k_pool)) +
+                      (((int64_t)page * p.Hkv + ic.kvh) << p.logP) * D;
+        const float s_old = n_old > 0 ? *scl : 0.0f;
+        float amax = page_amax(src, row_bytes, t1 - t0, D / 8, lane, 64);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+        int e = exponent_for(amax);
+        if (n_old > 0) {
+            const int e_old = (int)(__float_as_uint(s_old) >> 23) - 127;
+            if (e > e_old)
+                page_reencode(pg, n_old, D, e_old, e, lane, 64);
+            else
+                e = e_old;
+        }
+        page_encode(pg + (int64_t)(t0 & (p.P - 1)) * D, src, row_bytes, t1 - t0, D, e, lane, 64);
+        if (lane == 0) *scl = __uint_as_float((uint32_t)(e + 127) << 23);
+    }
+}
+
+// The same for a row with one new token (a decode step), by the one wave that will read the token's page, without holding up
+// the others: start() issues the loads before the wave streams its first block, finish() encodes and stores when the wave is
+// about to fetch the row's last block, which is the only one that holds the token.  Lanes 0 .. D/8 - 1 carry K, as many
+// after them V.  (Done by the whole workgroup in front of its stream instead, the append cost a launch of 608 items 6 us.)
+template <int D>
+struct NewToken {
+    static constexpr int CPK = D / 8;
+    u32x4 row;
+    float s_old;
+    int page;
+    __device__ __forceinline__ static bool carries(int lane) { return lane < 2 * CPK; }
+    __device__ __forceinline__ static bool is_v(int lane) { return lane >= CPK; }
+    __device__ __forceinline__ static float* scale(const AttnParams& p, const ItemCtx& ic, int page, int lane) {
+        return const_cast<float*>(is_v(lane) ? p.v_scale : p.k_scale) + (int64_t)page * p.Hkv + ic.kvh;
+    }
+    __device__ __forceinline__ void start(const AttnParams& p, const ItemCtx& ic, int lane) {
+        page = ic.bt_row[ic.C >> p.logP];
+        if (carries(lane))
+            row = *reinterpret_cast<const u32x4*>(static_cast<const char*>(is_v(lane) ? p.v_new : p.k_new) +
+                                                  (((int64_t)ic.row_off * p.Hkv + ic.kvh) * D + (lane % CPK) * 8) * 2);
+    }
+    __device__ __forceinline__ void start_scale(const AttnParams& p, const ItemCtx& ic, int lane) {
+        if (carries(lane)) s_old = *scale(p, ic, page, lane);
+    }
+    __device__ __forceinline__ void finish(const AttnParams& p, const ItemCtx& ic, int lane) {
+        const uint32_t w[4] = {row.x, row.y, row.z, row.w};
+        float f[8], amax = 0.0f;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            f[2 * x] = __uint_as_float(w[x] << 16);
+            f[2 * x + 1] = __uint_as_float(w[x] & 0xffff0000u);
+            amax = fmaxf(amax, fmaxf(fabsf(f[2 * x]), fabsf(f[2 * x + 1])));
+        }
+#pragma unroll
+        for (int o = CPK / 2; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+        const int slot = ic.C & (p.P - 1);                    // = tokens the page already holds
+        int e = exponent_for(amax);
+        const int e_old = slot > 0 ? (int)(__float_as_uint(s_old) >> 23) - 127 : e;
+        const int64_t tile = (((int64_t)page * p.Hkv + ic.kvh) << p.logP) * D;
+        if (__any(carries(lane) && e > e_old)) {              // rare: the page's exponent rises
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const int ne = __builtin_amdgcn_readlane(e, v * CPK), oe = __builtin_amdgcn_readlane(e_old, v * CPK);
+                if (ne > oe)
+                    page_reencode(static_cast<uint8_t*>(const_cast<void*>(v ? p.v_pool : p.k_pool)) + tile, slot, D, oe, ne, lane, 64);
+            }
+        }
+        e = max(e, e_old);
+        if (carries(lane)) {
+            const float inv = __uint_as_float((uint32_t)(127 - e) << 23);
+            const u32x2 o = {encode4(f[0] * inv, f[1] * inv, f[2] * inv, f[3] * inv), encode4(f[4] * inv, f[5] * inv, f[6] * inv, f[7] * inv)};
+            uint8_t* pg = static_cast<uint8_t*>(const_cast<void*>(is_v(lane) ? p.v_pool : p.k_pool)) + tile;
+            *reinterpret_cast<u32x2*>(pg + slot * D + (lane % CPK) * 8) = o;
+            if (lane % CPK == 0) *scale(p, ic, page, lane) = __uint_as_float((uint32_t)(e + 127) << 23);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // a wave's own stores and loads stay in order
+    }
+};
+
+constexpr int LEAN_ROWS = 8;
+// NW: waves of the workgroup.  QUANT: the item appends its own new tokens (8-bit cache) before it reads its pages.
+// LEAN: K and V of a block take turns in one LDS region per wave, and the merge holds the item's rows only (at most 8).
+template <int D, int KVT, int ROWS, int NW, bool QUANT = false, bool LEAN = false>
 __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& ic, uint32_t smem, int tid) {
     using G_ = Geo<D>;
     constexpr bool R16 = ROWS == 16;
+    constexpr int NACC = ATTN_WAVES / NW;
+    constexpr bool ONE_TOKEN = QUANT && R16 && !LEAN;     // (the lean form has no registers left for it)
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & (ROWS - 1);
     const int tl = row / ic.gn, hg = row - tl * ic.gn;
@@ -930,50 +1116,107 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
     const int first_lim = ic.C + ic.q0;                  // smallest last-visible key among the rows
 
     bf16x8 Q[R16 ? D / 32 : G_::NKK];
-    std::conditional_t<R16, WaveAcc16<D>, WaveAcc<D>> st;
+    std::conditional_t<R16, WaveAcc16<D>, WaveAcc<D>> acc[NACC];
     if constexpr (R16) {
         load_q16<D>(p, ic, tok, hg, valid, lane, Q);
-#pragma unroll
-        for (int dt = 0; dt < D / 16; ++dt) st.O[dt] = f32x4{0, 0, 0, 0};
     } else {
         load_q<D>(p, ic, tok, hg, valid, lane, Q);
+    }
 #pragma unroll
-        for (int db = 0; db < G_::NDB; ++db) st.O[db] = f32x16{0};
-    }
-    st.m = NEG_INF;
-    st.l = 0.0f;
-
-    const uint32_t kl = smem + wave * (2 * G_::B32);
-    const uint32_t vl = kl + G_::B32;
-    const int nblocks = (ic.kv_end - ic.kv_begin + 31) >> 5;
-    Loader<D, KVT, 64, 32> ld;
-    if (wave < nblocks) {
-        ld.fetch_pages(p, ic, ic.kv_begin + wave * 32, lane);
-        ld.fetch_kv(p, ic, ic.kv_begin + wave * 32, lane);
-        if (wave + ATTN_WAVES < nblocks) ld.fetch_pages(p, ic, ic.kv_begin + (wave + ATTN_WAVES) * 32, lane);
-    }
-    for (int b = wave; b < nblocks; b += ATTN_WAVES) {
-        const int kbase = ic.kv_begin + b * 32;
-        ld.commit(p, kl, vl, lane);
-        if (b + ATTN_WAVES < nblocks) {
-            ld.fetch_kv(p, ic, kbase + 32 * ATTN_WAVES, lane);
-            if (b + 2 * ATTN_WAVES < nblocks) ld.fetch_pages(p, ic, kbase + 64 * ATTN_WAVES, lane);
+    for (auto& st : acc) {
+        if constexpr (R16) {
+#pragma unroll
+            for (int dt = 0; dt < D / 16; ++dt) st.O[dt] = f32x4{0, 0, 0, 0};
+        } else {
+#pragma unroll
+            for (int db = 0; db < G_::NDB; ++db) st.O[db] = f32x16{0};
         }
-        if constexpr (R16)
-            block16<D>(kl, vl, Q, st, p.c_log2, lim - kbase - 4 * key_group16(lane >> 4), kbase + 31 > first_lim, lane);
-        else
-            block32<D>(kl, vl, Q, st, p.c_log2, lim - kbase - 4 * (lane >> 5), kbase + 31 > first_lim, lane);
+        st.m = NEG_INF;
+        st.l = 0.0f;
     }
-    // merge the waves: LDS holds O as [wave][row 0..31][D + 4] fp32 and (m, l) as [wave][32][2]
-    const float ltot = R16 ? sum_xor32(sum_xor16(st.l)) : sum_xor32(st.l);
+
+    const uint32_t kl = smem + wave * ((LEAN ? 1 : 2) * G_::B32);
+    const uint32_t vl = LEAN ? kl : kl + G_::B32;
+    const int nblocks = (ic.kv_end - ic.kv_begin + 31) >> 5;
+    Loader<D, KVT, 64, 32, QUANT> ld;
+    auto first_block = [&]() {
+        ld.fetch_kv(p, ic, ic.kv_begin + wave * 32, lane);
+        if (wave + NW < nblocks) ld.fetch_pages(p, ic, ic.kv_begin + (wave + NW) * 32, lane);
+    };
+    NewToken<D> nt;
+    bool pending = false;                                 // this wave has a token to encode before it fetches the last block
+    auto encode_before = [&](int b) {
+        if constexpr (ONE_TOKEN) {
+            if (pending && b == nblocks - 1) nt.finish(p, ic, lane);
+        }
+    };
+    if (wave < nblocks) ld.fetch_pages(p, ic, ic.kv_begin + wave * 32, lane);
+    if (QUANT && p.k_new && ic.kv_end > ic.C) {           // uniform
+        if (ONE_TOKEN && ic.nq == 1) {
+            pending = wave == (nblocks - 1) % NW;
+            if (pending) nt.start(p, ic, lane);
+            if (pending && wave == nblocks - 1) nt.start_scale(p, ic, lane);
+            encode_before(wave);
+            if (wave < nblocks) first_block();
+            if (pending && wave != nblocks - 1) nt.start_scale(p, ic, lane);
+        } else {
+            // blocks from nold on hold pages that get new tokens; the first blocks before them travel while the append runs
+            const int nold = ((max(ic.C, ic.kv_begin) & ~(p.P - 1)) - ic.kv_begin) >> 5;
+            if (wave < nold) first_block();
+            append_item_pages<D, NW>(p, ic, tid);
+            __syncthreads();
+            if (wave >= nold && wave < nblocks) first_block();
+        }
+    } else if (wave < nblocks) {
+        first_block();
+    }
+    for (int b0 = wave; b0 < nblocks; b0 += ATTN_WAVES) {
+        static_for<0, NACC>([&](auto ac) {
+            auto& st = acc[decltype(ac)::value];
+            const int b = b0 + decltype(ac)::value * NW;
+            if (b >= nblocks) return;
+            const int kbase = ic.kv_begin + b * 32;
+            const bool more = b + NW < nblocks;
+            const int rel = lim - kbase - 4 * (R16 ? key_group16(lane >> 4) : lane >> 5);
+            const bool masked = kbase + 31 > first_lim;
+            if constexpr (LEAN) {
+                ld.commit_k(p, kl, lane);
+                encode_before(b + NW);
+                if (more) ld.template fetch_kv<true, false>(p, ic, kbase + 32 * NW, lane);
+                const bf16x8 P = softmax16<D>(kl, Q, st, p.c_log2, rel, masked, lane);
+                ld.commit_v(p, vl, lane);
+                if (more) ld.template fetch_kv<false, true>(p, ic, kbase + 32 * NW, lane);
+                if (b + 2 * NW < nblocks) ld.fetch_pages(p, ic, kbase + 64 * NW, lane);
+                pv16<D>(vl, P, st, lane);
+                return;
+            }
+            ld.commit(p, kl, vl, lane);
+            encode_before(b + NW);
+            if (more) {
+                ld.fetch_kv(p, ic, kbase + 32 * NW, lane);
+                if (b + 2 * NW < nblocks) ld.fetch_pages(p, ic, kbase + 64 * NW, lane);
+            }
+            if constexpr (R16) {
+                const bf16x8 P = softmax16<D>(kl, Q, st, p.c_log2, rel, masked, lane);
+                pv16<D>(vl, P, st, lane);
+            } else {
+                block32<D>(kl, vl, Q, st, p.c_log2, rel, masked, lane);
+            }
+        });
+    }
+    // merge the waves' states: LDS holds O as [state][row][D + 4] fp32 and (m, l) as [state][row][2]
     __syncthreads();                                      // every wave is done with its K/V region
-    constexpr int NW = ATTN_WAVES;
     constexpr int OSTR = D + 4;
     const uint32_t obase = smem;
-    const uint32_t mlbase = smem + NW * 32 * OSTR * 4;
-    {
+    const int mrows = LEAN ? LEAN_ROWS : ROWS;            // rows of a state in LDS
+    const uint32_t mlbase = smem + ATTN_WAVES * mrows * OSTR * 4;
+    static_for<0, NACC>([&](auto ac) {
+        const auto& st = acc[decltype(ac)::value];
         const int g = lane / ROWS;
-        const uint32_t orow = obase + ((wave * 32 + row) * OSTR) * 4;
+        const int slot = (wave + decltype(ac)::value * NW) * mrows + row;
+        const uint32_t orow = obase + slot * OSTR * 4;
+        const float ltot = R16 ? sum_xor32(sum_xor16(st.l)) : sum_xor32(st.l);
+        if (LEAN && row >= LEAN_ROWS) return;
         if constexpr (R16) {
 #pragma unroll
             for (int dt = 0; dt < D / 16; ++dt) *LDS_PTR(f32x4, orow + (dt * 16 + g * 4) * 4) = st.O[dt];
@@ -988,28 +1231,28 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
                 }
         }
         if (g == 0) {
-            *LDS_PTR(float, mlbase + ((wave * 32 + row) * 2) * 4) = st.m;
-            *LDS_PTR(float, mlbase + ((wave * 32 + row) * 2 + 1) * 4) = ltot;
+            *LDS_PTR(float, mlbase + slot * 8) = st.m;
+            *LDS_PTR(float, mlbase + slot * 8 + 4) = ltot;
         }
-    }
+    });
     __syncthreads();
     // thread -> (row r, DPT consecutive d): 16 threads per row
-    constexpr int DPT = D / 16;
-    const int r = tid >> 4, dc = (tid & 15) * DPT;
+    constexpr int DPT = D / 16, NS = ATTN_WAVES;
+    const int dc = (tid & 15) * DPT;
     const int rows = ic.nq * ic.gn;
-    if (r < rows) {
-        float mw[NW], lw[NW];
+    for (int r = tid >> 4; r < rows; r += 4 * NW) {
+        float mw[NS], lw[NS];
         float mall = NEG_INF;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            mw[w] = *LDS_PTR(float, mlbase + ((w * 32 + r) * 2) * 4);
-            lw[w] = *LDS_PTR(float, mlbase + ((w * 32 + r) * 2 + 1) * 4);
+        for (int w = 0; w < NS; ++w) {
+            mw[w] = *LDS_PTR(float, mlbase + ((w * mrows + r) * 2) * 4);
+            lw[w] = *LDS_PTR(float, mlbase + ((w * mrows + r) * 2 + 1) * 4);
             mall = fmaxf(mall, mw[w]);
         }
         const float muse = mall == NEG_INF ? 0.0f : mall;
-        float lsum = 0.0f, wgt[NW];
+        float lsum = 0.0f, wgt[NS];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
+        for (int w = 0; w < NS; ++w) {
             wgt[w] = fast_exp2(mw[w] - muse);
             lsum += lw[w] * wgt[w];
         }
@@ -1017,8 +1260,8 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
 #pragma unroll
         for (int x = 0; x < DPT; ++x) acc[x] = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const uint32_t src = obase + ((w * 32 + r) * OSTR + dc) * 4;
+        for (int w = 0; w < NS; ++w) {
+            const uint32_t src = obase + ((w * mrows + r) * OSTR + dc) * 4;
 #pragma unroll
             for (int x = 0; x < DPT; x += 4) {
                 const f32x4 o = *LDS_PTR(f32x4, src + x * 4);
@@ -1062,6 +1305,7 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
 // the same launch never read these page slots (they take new tokens from the packed rows), so the two kinds
 // need no order among themselves.
 
+template <int NTHR>
 __device__ __forceinline__ void append_body(const AttnParams& p, const ItemCtx& ic, int D, int tid) {
     const int cpt = p.Hkv * D / 8;                           // 16-byte chunks per packed row (one of K or V)
     const int cph = D / 8;
@@ -1069,7 +1313,7 @@ __device__ __forceinline__ void append_body(const AttnParams& p, const ItemCtx& 
     const int total = ic.nq * cpt;
     int r = ic.req;                                          // request of the row this thread is at: rows only move forward
     ReqInfo ri = p.reqs[r];
-    for (int u = tid; u < total; u += AWG) {
+    for (int u = tid; u < total; u += NTHR) {
         const int row = first_row + u / cpt, rem = u % cpt;
         while (row >= ri.row_off + ri.L) ri = p.reqs[++r];   // (requests with L = 0 are stepped over)
         const int h = rem / cph, ch = rem % cph;
@@ -1125,17 +1369,17 @@ template <int D, int KVT>
 __device__ __forceinline__ void run_item(const AttnParams& p, int idx, uint32_t smem, int tid) {
     const int kind = (p.items[idx].heads >> 24) & 0xff;
     if (kind == KIND_NULL) return;                         // a filler that keeps the following items on their XCD
-    const ItemCtx ic = load_item(p, idx);
+    const ItemCtx ic = item_ctx<KVT>(p, p.items[idx]);
     if (kind == KIND_WIDE)
         wide_body<D, KVT>(p, ic, smem, tid);
     else if (kind == KIND_NARROW) {
         if (ic.nq * ic.gn <= 16)
-            narrow_body<D, KVT, 16>(p, ic, smem, tid);
+            narrow_body<D, KVT, 16, ATTN_WAVES>(p, ic, smem, tid);
         else
-            narrow_body<D, KVT, 32>(p, ic, smem, tid);
+            narrow_body<D, KVT, 32, ATTN_WAVES>(p, ic, smem, tid);
     }
     else if (KVT == KV_BF16)
-        append_body(p, ic, D, tid);
+        append_body<AWG>(p, ic, D, tid);
 }
 
 // One workgroup per work item when the items fit one round on the CUs (gridDim.x = number of items).  Otherwise
@@ -1177,6 +1421,78 @@ __global__ __launch_bounds__(AWG, 1) void attn_kernel(const AttnParams p) {
         __syncthreads();                                   // (s_next is written again at the end of the next item)
         if (idx < 0) return;
     }
+}
+
+// The launch of a batch of decode rows alone whose work list travels in the arguments (see RowTable): one workgroup of NW
+// waves per item, then (bf16 cache) the append items.  Bound: HBM, and around an item's stream its latencies (item, page
+// ids, first block before the first key; merge behind the last), which only other items can hide.
+//   8 waves: one workgroup fills a CU (133 KB of LDS; 57 GB/s when it streams alone, over an 8-bit cache 41).  Few items,
+//     or whole rows that keep HBM busy by themselves.
+//   4 waves: two (bf16 cache: 223 -> 203 registers, 67 KB) or three workgroups per CU (8-bit cache: K and V of a block take
+//     turns in one LDS region and the merge holds 8 rows, 33 KB and 166 registers), so that an item's latencies pass under
+//     its neighbours' streams.
+// No list in memory means no upload launch in front; over an 8-bit cache the item that reads the pages of a row's new tokens
+// quantises them itself, so the append launch is gone too (25 rows of 0.7-7 k tokens over 8 KV heads: append 5.1 us + gap
+// 4 + attention 43.9 -> 40.5 us; four bf16 rows of 36-70 k tokens 30.3 -> 27.8 us per call, one row of 1.5 k 16.7 -> 13.5).
+
+// Page writes of packed rows [first_row, first_row + APPEND_ITEM_ROWS): which request and position a row belongs to is
+// written to LDS by the table's entries first.
+template <int D, int NTHR>
+__device__ __forceinline__ void append_table_rows(const AttnParams& p, const RowTable& t, int first_row, uint32_t smem, int tid) {
+    if (tid < t.n) {
+        const RowEntry e = t.e[tid];
+        const int L = e.req_L >> 24;
+        for (int i = 0; i < L; ++i) {
+            const int row = e.row_off + i - first_row;
+            if (row >= 0 && row < APPEND_ITEM_ROWS) *LDS_PTR(u32x2, smem + row * 8) = u32x2{(uint32_t)e.req_L & 0xffffff, (uint32_t)(e.C + i)};
+        }
+    }
+    __syncthreads();
+    const int nrows = min(APPEND_ITEM_ROWS, t.sum_L - first_row);
+    const int cpt = p.Hkv * (D / 8);                         // 16-byte chunks per packed row (one of K or V)
+    for (int u = tid; u < nrows * cpt; u += NTHR) {
+        const int row = u / cpt, rem = u % cpt, h = rem / (D / 8), ch = rem % (D / 8);
+        const u32x2 at = *LDS_PTR(const u32x2, smem + row * 8);
+        const int pos = (int)at.y;
+        const int page = p.block_table[(int64_t)at.x * p.max_pages + (pos >> p.logP)];
+        const int64_t src = (int64_t)(first_row + row) * p.Hkv * D + rem * 8;
+        const int64_t dst = ((((int64_t)page * p.Hkv + h) << p.logP) + (pos & (p.P - 1))) * D + ch * 8;
+        const u32x4 kx = *reinterpret_cast<const u32x4*>(static_cast<const char*>(p.k_new) + src * 2);
+        const u32x4 vx = *reinterpret_cast<const u32x4*>(static_cast<const char*>(p.v_new) + src * 2);
+        *reinterpret_cast<u32x4*>(static_cast<char*>(const_cast<void*>(p.k_pool)) + dst * 2) = kx;
+        *reinterpret_cast<u32x4*>(static_cast<char*>(const_cast<void*>(p.v_pool)) + dst * 2) = vx;
+    }
+}
+
+template <int D, int NW, bool LEAN>
+constexpr int rows_smem() {
+    constexpr int kv = NW * (LEAN ? 1 : 2) * Geo<D>::B32;
+    constexpr int merge = ATTN_WAVES * (LEAN ? LEAN_ROWS : NW == ATTN_WAVES ? 32 : 16) * ((D + 4) * 4 + 8);
+    return kv > merge ? kv : merge;
+}
+template <int D, int KVT, int NW>
+__global__ __launch_bounds__(64 * NW, D == 64 ? 4 : NW < ATTN_WAVES && KVT == KV_FP8 ? 3 : 2) void decode_rows_kernel(const AttnParams p, const RowTable t) {
+    constexpr bool LEAN = NW < ATTN_WAVES && KVT == KV_FP8;
+    __shared__ __attribute__((aligned(16))) char smem_raw[rows_smem<D, NW, LEAN>()];
+    const uint32_t smem = (uint32_t)(uintptr_t)LDS_PTR(char, smem_raw);
+    const int idx = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    if (idx >= t.n_items) {
+        if constexpr (KVT == KV_BF16) append_table_rows<D, 64 * NW>(p, t, (idx - t.n_items) * APPEND_ITEM_ROWS, smem, tid);
+        return;
+    }
+    int row;
+    if (idx < t.n_whole) {                                   // the last row whose whole pieces start at or before idx
+        const bool a = lane < t.n && t.e[min(lane, t.n - 1)].first <= idx;
+        const bool b = lane + 64 < t.n && t.e[min(lane + 64, t.n - 1)].first <= idx;
+        row = __popcll(__ballot(a)) + __popcll(__ballot(b)) - 1;
+    } else {
+        row = (idx - t.n_whole) / t.Hkv;
+    }
+    const ItemCtx ic = item_ctx<KVT>(p, table_item(t, t.e[__builtin_amdgcn_readfirstlane(row)], idx));
+    if (NW < ATTN_WAVES || ic.nq * ic.gn <= 16)
+        narrow_body<D, KVT, 16, NW, KVT == KV_FP8, LEAN>(p, ic, smem, tid);
+    else
+        narrow_body<D, KVT, 32, NW, KVT == KV_FP8>(p, ic, smem, tid);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1232,17 +1548,15 @@ __device__ __forceinline__ float combine_quad(const float* part0, int nsplit, in
 // hundred splits and few rows (a decode row over a long context) is then a chain of one or two memory latencies per
 // thread instead of eight, on NSL times as many workgroups.
 template <int D, int CR>
-__global__ __launch_bounds__(WG) void combine_kernel(const AttnParams p) {
+__device__ __forceinline__ void combine_tile(const AttnParams& p, const CombItem& ci, int row_off) {
     constexpr int QPR = D / 4;                         // float4 groups per row
     constexpr int NSL = CR * QPR >= WG ? 1 : WG / (CR * QPR);
     constexpr int PER = CR * QPR < WG ? CR * QPR : WG; // (row, quad) pairs in flight per pass
     __shared__ float red[NSL > 1 ? (NSL - 1) * PER * 6 : 1];
-    const CombItem ci = p.combs[blockIdx.x];
     const int kvh = ci.heads & 0xff, g0 = (ci.heads >> 8) & 0xff, gn = (ci.heads >> 16) & 0xff;
     const int rows = ci.nq * gn;
     const int r0 = blockIdx.y * CR;                    // grid.y covers the tallest tile
     if (r0 >= rows) return;
-    const ReqInfo ri = p.reqs[ci.req];
     const int nr = min(CR, rows - r0);
     const int slice = threadIdx.x / PER, u0 = threadIdx.x % PER;
     const float* part0 = p.partial + ci.part_off;
@@ -1250,7 +1564,7 @@ __global__ __launch_bounds__(WG) void combine_kernel(const AttnParams p) {
         const float inv = 1.0f / lsum;
         const int tl = r / gn, hg = r - tl * gn;
         const int hq = kvh * (p.Hq / p.Hkv) + g0 + hg;
-        char* dst = static_cast<char*>(p.out) + (((int64_t)(ri.row_off + ci.q0 + tl) * p.Hq + hq) * D + dq) * 2;
+        char* dst = static_cast<char*>(p.out) + (((int64_t)(row_off + ci.q0 + tl) * p.Hq + hq) * D + dq) * 2;
         bf16x4 o = {(__bf16)(acc[0] * inv), (__bf16)(acc[1] * inv), (__bf16)(acc[2] * inv), (__bf16)(acc[3] * inv)};
         *reinterpret_cast<u32x2*>(dst) = __builtin_bit_cast(u32x2, o);
     };
@@ -1296,6 +1610,18 @@ __global__ __launch_bounds__(WG) void combine_kernel(const AttnParams p) {
         }
         finish(r, dq, acc, lsum);
     }
+}
+
+template <int D, int CR>
+__global__ __launch_bounds__(WG) void combine_kernel(const AttnParams p) {
+    const CombItem ci = p.combs[blockIdx.x];
+    combine_tile<D, CR>(p, ci, p.reqs[ci.req].row_off);
+}
+// the same for a launch by table: one grid column per (row, KV head)
+template <int D, int CR>
+__global__ __launch_bounds__(WG) void combine_rows_kernel(const AttnParams p, const RowTable t) {
+    const RowEntry e = t.e[blockIdx.x / t.Hkv];
+    if (e.part_off >= 0) combine_tile<D, CR>(p, table_comb(t, e, blockIdx.x % t.Hkv), e.row_off);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1344,22 +1670,6 @@ __global__ __launch_bounds__(WG) void kv_move_bf16_kernel(const AppendParams p) 
 // KV append, 8-bit cache.  grid = (pages touched, requests, 2 {K,V} x KV heads): one block per
 // (page, head), so that the chain amax of the new tokens -> exponent -> (re-encode old slots) -> encode,
 // which is a few dependent memory round trips, runs for all heads at once.
-__device__ __forceinline__ int exponent_for(float amax) {
-    // smallest e with amax <= 448 * 2^e  (448 = 1.75 * 2^8), clamped to [-40, 119]
-    const uint32_t u = __float_as_uint(amax);
-    const int ex = (int)(u >> 23) - 127;
-    const uint32_t man = u & 0x7fffffu;
-    int e = (man <= 0x600000u) ? ex - 8 : ex - 7;
-    if ((u >> 23) == 0) e = -40;                              // zero / subnormal
-    return min(119, max(-40, e));
-}
-
-__device__ __forceinline__ uint32_t encode4(float a, float b, float c, float d) {
-    int w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
-    w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
-    return (uint32_t)w;
-}
-
 __global__ __launch_bounds__(WG) void append_fp8_kernel(const AppendParams p) {
     __shared__ float red[WG / 64];
     __shared__ int e_sh[2];
@@ -1378,73 +1688,33 @@ __global__ __launch_bounds__(WG) void append_fp8_kernel(const AppendParams p) {
     const char* src = static_cast<const char*>(is_v ? p.v_new : p.k_new);
     uint8_t* dst = static_cast<uint8_t*>(is_v ? p.v_pool : p.k_pool);
     float* scl = is_v ? p.v_scale : p.k_scale;
-    const int cph = p.D / 8;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    {
-        // 1. amax over the new tokens of this (page, head)
-        float amax = 0.0f;
-        const int total = (t1 - t0) * cph;
-        for (int u = threadIdx.x; u < total; u += WG) {
-            const int t = t0 + u / cph, ch = u % cph;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(src + (((int64_t)(p.row_off[r] + t - C) * p.Hkv + h) * p.D + ch * 8) * 2);
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    const int64_t row_bytes = (int64_t)p.Hkv * p.D * 2;
+    src += ((int64_t)(p.row_off[r] + t0 - C) * p.Hkv + h) * p.D * 2;
+    float amax = page_amax(src, row_bytes, t1 - t0, p.D / 8, threadIdx.x, WG);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                amax = fmaxf(amax, fabsf(__uint_as_float(w[x] << 16)));
-                amax = fmaxf(amax, fabsf(__uint_as_float(w[x] & 0xffff0000u)));
-            }
+    for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+    if (lane == 0) red[wave] = amax;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float a = red[0];
+        for (int w = 1; w < WG / 64; ++w) a = fmaxf(a, red[w]);
+        int e = exponent_for(a);
+        int e_old = e;
+        if (n_old > 0) {
+            const float s_old = scl[(int64_t)page * p.Hkv + h];
+            e_old = (int)(__float_as_uint(s_old) >> 23) - 127;
+            if (e < e_old) e = e_old;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-        if (lane == 0) red[wave] = amax;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float a = red[0];
-            for (int w = 1; w < WG / 64; ++w) a = fmaxf(a, red[w]);
-            int e = exponent_for(a);
-            int e_old = e;
-            if (n_old > 0) {
-                const float s_old = scl[(int64_t)page * p.Hkv + h];
-                e_old = (int)(__float_as_uint(s_old) >> 23) - 127;
-                if (e < e_old) e = e_old;
-            }
-            e_sh[0] = e;
-            e_sh[1] = e_old;
-            scl[(int64_t)page * p.Hkv + h] = __uint_as_float((uint32_t)(e + 127) << 23);
-        }
-        __syncthreads();
-        const int e = e_sh[0], e_old = e_sh[1];
-        uint8_t* pg = dst + ((((int64_t)page * p.Hkv + h) << p.logP)) * p.D;
-        // 2. re-encode the slots that were already valid when the exponent rises
-        if (n_old > 0 && e > e_old) {
-            const float f = __uint_as_float((uint32_t)(e_old - e + 127) << 23);     // 2^(e_old - e)
-            const int tot_old = n_old * (p.D / 4);
-            for (int u = threadIdx.x; u < tot_old; u += WG) {
-                uint32_t* q4 = reinterpret_cast<uint32_t*>(pg) + u;
-                const uint32_t w = *q4;
-                const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(w, false);
-                const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8(w, true);
-                *q4 = encode4(lo.x * f, lo.y * f, hi.x * f, hi.y * f);
-            }
-        }
-        // 3. encode the new tokens: x * 2^-e, |.| <= 448 by construction
-        const float inv = __uint_as_float((uint32_t)(127 - e) << 23);
-        for (int u = threadIdx.x; u < total; u += WG) {
-            const int t = t0 + u / cph, ch = u % cph;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(src + (((int64_t)(p.row_off[r] + t - C) * p.Hkv + h) * p.D + ch * 8) * 2);
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            float f[8];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                f[2 * x] = __uint_as_float(w[x] << 16) * inv;
-                f[2 * x + 1] = __uint_as_float(w[x] & 0xffff0000u) * inv;
-            }
-            u32x2 o;
-            o.x = encode4(f[0], f[1], f[2], f[3]);
-            o.y = encode4(f[4], f[5], f[6], f[7]);
-            *reinterpret_cast<u32x2*>(pg + (int64_t)(t & (p.P - 1)) * p.D + ch * 8) = o;
-        }
+        e_sh[0] = e;
+        e_sh[1] = e_old;
+        scl[(int64_t)page * p.Hkv + h] = __uint_as_float((uint32_t)(e + 127) << 23);
     }
+    __syncthreads();
+    const int e = e_sh[0], e_old = e_sh[1];
+    uint8_t* pg = dst + ((((int64_t)page * p.Hkv + h) << p.logP)) * p.D;
+    if (n_old > 0 && e > e_old) page_reencode(pg, n_old, p.D, e_old, e, threadIdx.x, WG);
+    page_encode(pg + (int64_t)(t0 & (p.P - 1)) * p.D, src, row_bytes, t1 - t0, p.D, e, threadIdx.x, WG);
 }
 
 // Work-list upload: the workgroups read the host-built plan straight out of pinned host memory
@@ -1480,23 +1750,48 @@ hipError_t launch_attn(const AttnParams& p, int D, int kvt, int grid, hipStream_
     return hipErrorInvalidValue;
 }
 
+template <int D, int KVT>
+static hipError_t launch_rows_t(const AttnParams& p, const RowTable& t, int grid, hipStream_t st) {
+    // d = 64: two workgroups of 8 waves fit a CU as they are.
+    if constexpr (D == 128) {
+        if (t.small && t.max_rows <= (KVT == KV_FP8 ? LEAN_ROWS : 16)) {
+            hipLaunchKernelGGL((decode_rows_kernel<D, KVT, 4>), dim3(grid), dim3(256), 0, st, p, t);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((decode_rows_kernel<D, KVT, 8>), dim3(grid), dim3(512), 0, st, p, t);
+    return hipGetLastError();
+}
+
+hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid, hipStream_t st) {
+    if (t.D == 128 && kvt == KV_BF16) return launch_rows_t<128, KV_BF16>(p, t, grid, st);
+    if (t.D == 64 && kvt == KV_BF16) return launch_rows_t<64, KV_BF16>(p, t, grid, st);
+    if (t.D == 128 && kvt == KV_FP8) return launch_rows_t<128, KV_FP8>(p, t, grid, st);
+    if (t.D == 64 && kvt == KV_FP8) return launch_rows_t<64, KV_FP8>(p, t, grid, st);
+    return hipErrorInvalidValue;
+}
+
 // max_rows: rows of the tallest tile; max_splits: splits of the most finely split one
-hipError_t launch_combine(const AttnParams& p, int D, int ncombs, int max_rows, int max_splits, hipStream_t st) {
+// t: the launch went by table (ncombs: split tiles in it), or null
+template <int D, int CR>
+static void launch_combine_t(const AttnParams& p, const RowTable* t, int ncombs, int max_rows, hipStream_t st) {
+    const int ny = (max_rows + CR - 1) / CR;
+    if (t)
+        hipLaunchKernelGGL((combine_rows_kernel<D, CR>), dim3(t->n * t->Hkv, ny), dim3(WG), 0, st, p, *t);
+    else
+        hipLaunchKernelGGL((combine_kernel<D, CR>), dim3(ncombs, ny), dim3(WG), 0, st, p);
+}
+
+hipError_t launch_combine(const AttnParams& p, const RowTable* t, int D, int ncombs, int max_rows, int max_splits, hipStream_t st) {
     if (ncombs <= 0) return hipSuccess;
     // many splits and a launch that would otherwise leave most of the chip idle: let thread slices share the splits
     const bool sliced = max_splits > 16 && (int64_t)ncombs * ((max_rows + COMB_ROWS - 1) / COMB_ROWS) < 512;
-    const int cr = sliced ? COMB_ROWS_SLICED : COMB_ROWS;
-    const dim3 grid(ncombs, (max_rows + cr - 1) / cr);
     if (D == 128) {
-        if (sliced)
-            hipLaunchKernelGGL((combine_kernel<128, COMB_ROWS_SLICED>), grid, dim3(WG), 0, st, p);
-        else
-            hipLaunchKernelGGL((combine_kernel<128, COMB_ROWS>), grid, dim3(WG), 0, st, p);
+        if (sliced) launch_combine_t<128, COMB_ROWS_SLICED>(p, t, ncombs, max_rows, st);
+        else launch_combine_t<128, COMB_ROWS>(p, t, ncombs, max_rows, st);
     } else {
-        if (sliced)
-            hipLaunchKernelGGL((combine_kernel<64, COMB_ROWS_SLICED>), grid, dim3(WG), 0, st, p);
-        else
-            hipLaunchKernelGGL((combine_kernel<64, COMB_ROWS>), grid, dim3(WG), 0, st, p);
+        if (sliced) launch_combine_t<64, COMB_ROWS_SLICED>(p, t, ncombs, max_rows, st);
+        else launch_combine_t<64, COMB_ROWS>(p, t, ncombs, max_rows, st);
     }
     return hipGetLastError();
 }

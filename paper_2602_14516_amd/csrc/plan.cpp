@@ -28,6 +28,88 @@ struct QBlock {            // a query block before splitting
 
 }  // namespace
 
+namespace {
+
+// The row table of a batch of decode rows alone (out.reqs holds the rows).
+void build_table(const Shape& s, int32_t chunk, bool append_items, Plan& out) {
+    RowTable& t = out.table;
+    t.chunk = chunk;
+    t.Hkv = s.Hkv;
+    t.G = s.Hq / s.Hkv;
+    t.D = s.D;
+    t.sum_L = (int32_t)out.sum_L;
+    int n = 0;
+    std::pair<int32_t, int32_t> by_rest[ROW_TABLE_MAX];        // (keys of the remainder, request)
+    for (size_t r = 0; r < out.reqs.size(); ++r)
+        if (out.reqs[r].L > 0) by_rest[n++] = {(out.reqs[r].C + out.reqs[r].L) % chunk, (int32_t)r};
+    std::stable_sort(by_rest, by_rest + n, [](const auto& a, const auto& b) { return a.first > b.first; });
+    t.n = n;
+    int32_t whole = 0, rests = 0;
+    int64_t keys_sum = 0;
+    t.max_rows = 0;
+    for (int i = 0; i < n; ++i) {
+        const ReqInfo& r = out.reqs[by_rest[i].second];
+        const int32_t keys = r.C + r.L, pieces = (int32_t)ceil_div(keys, chunk), slot = r.L * t.G * (s.D + 2);
+        t.e[i] = RowEntry{r.C, r.row_off, by_rest[i].second | r.L << 24, whole, -1};
+        keys_sum += (int64_t)keys * s.Hkv;
+        t.max_rows = std::max(t.max_rows, r.L * t.G);
+        whole += keys / chunk * s.Hkv;
+        rests += by_rest[i].first > 0 ? s.Hkv : 0;
+        if (pieces > 1) {
+            t.e[i].part_off = (int32_t)out.partial_floats;
+            out.partial_floats += (int64_t)slot * pieces * s.Hkv;
+            out.num_combs += s.Hkv;
+        }
+    }
+    t.n_whole = whole;
+    t.n_items = whole + rests;
+    // Small workgroups pay where rows are cut into two or more items per CU and a CU's share of the keys is small enough for
+    // the items' fixed costs to show, since neighbours on the CU hide them.  us per call, 8 waves -> 4, rows of 0.4-4, 1.6-16
+    // and 3.2-32 k tokens over 8 KV heads, 25 rows (1.7, 6.9, 14 k keys per CU): bf16 48.7 -> 44.8, 147.7 -> 143.3, 313 -> 316;
+    // 8-bit 33.8 -> 28.1, 86.6 -> 83.1, 175.7 -> 183.9; 40 rows of 1.6-16 k (11 k keys per CU): 230 -> 235, 129.9 -> 133.8.  Rows
+    // that are not cut: 40 rows of 0.2-2 k 8-bit 28.1 -> 33.4, 96 bf16 rows of 2-16 k 552 -> 578; one item per CU: 8 rows of
+    // 2-16 k 8-bit 33.8 -> 39.4.
+    t.small = t.n_items >= 512 && 2 * n * s.Hkv < 3 * 256 && keys_sum <= 8192 * 256;
+    out.by_table = true;
+    out.num_narrow = t.n_items;
+    out.num_append = append_items ? ceil_div(out.sum_L, APPEND_ITEM_ROWS) : 0;
+    out.num_items = out.num_narrow + out.num_append;
+    out.grid = (int32_t)out.num_items;
+    out.total_bytes = std::max<int64_t>(256, round_up(out.partial_floats * 4, 256));
+}
+
+// Append items: consecutive runs of packed rows, whatever request they belong to (a decode batch of 96 rows is two items,
+// not 96); each names the request and token its first row belongs to.
+void add_append_items(const Plan& plan, std::vector<Item>& items) {
+    int r = 0;
+    for (int64_t row = 0; row < plan.sum_L; row += APPEND_ITEM_ROWS) {
+        while (row >= (int64_t)plan.reqs[r].row_off + plan.reqs[r].L) ++r;
+        items.push_back(Item{r, pack_heads(0, 0, 0, KIND_APPEND), (int32_t)(row - plan.reqs[r].row_off),
+                             (int32_t)std::min<int64_t>(APPEND_ITEM_ROWS, plan.sum_L - row), 0, 0, -1, plan.reqs[r].C,
+                             plan.reqs[r].row_off, {0, 0, 0}});
+    }
+}
+
+}  // namespace
+
+void plan_items(const Plan& plan, std::vector<Item>& out) {
+    if (!plan.by_table) {
+        out = plan.items;
+        return;
+    }
+    out.clear();
+    const RowTable& t = plan.table;
+    int row = 0;
+    for (int i = 0; i < t.n_items; ++i) {
+        if (i < t.n_whole)
+            while (row + 1 < t.n && t.e[row + 1].first <= i) ++row;
+        else
+            row = (i - t.n_whole) / t.Hkv;
+        out.push_back(table_item(t, t.e[row], i));
+    }
+    if (plan.num_append > 0) add_append_items(plan, out);
+}
+
 void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int32_t* incr_len,
                 const PlanOptions& opt, Plan& out) {
     out = Plan();
@@ -40,6 +122,15 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
         off += incr_len[r];
     }
     out.sum_L = off;
+
+    // A batch of decode rows alone whose list travels in the kernel's arguments (see RowTable)
+    bool by_table = opt.force_kv_splits <= 0 && nhb == 1 && num_reqs < (1 << 24);
+    int active = 0;
+    for (int r = 0; r < num_reqs && by_table; ++r) {
+        by_table = (int64_t)incr_len[r] * G <= 32;
+        active += incr_len[r] > 0;
+    }
+    by_table = by_table && active > 0 && active <= ROW_TABLE_MAX;
 
     // 1. query blocks
     std::vector<QBlock> qb;
@@ -57,6 +148,11 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     for (int r = 0; r < num_reqs; ++r) {
         const int C = ctx_len[r], L = incr_len[r];
         if (L <= 0) continue;
+        if (by_table) {
+            narrow_keys += (int64_t)s.Hkv * (C + L);
+            note(narrow_runs, C + L);
+            continue;
+        }
         for (int kvh = 0; kvh < s.Hkv; ++kvh) {
             for (int hb = 0; hb < nhb; ++hb) {
                 const int g0 = hb * 32;
@@ -146,14 +242,23 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     if (opt.force_kv_splits <= 0) {
         const int64_t slots = opt.wg_slots;
         if (narrow_keys > 0) {
-            // Two or more rows per slot: whole rows balance well by themselves (longest first); only a row longer
-            // than a slot's share of the keys is cut.
-            int64_t n_blocks = 0;
-            for (const auto& r : narrow_runs) n_blocks += r.second;
-            if (n_blocks >= 2 * slots)
-                narrow_chunk = std::max<int64_t>(MIN_NARROW_CHUNK, round_up(ceil_div(narrow_keys, slots), KV_TILE));
-            else
+            // Three or more (row, KV head) blocks for every two slots: whole rows balance well by themselves (longest first),
+            // since half of the slots streaming is enough to keep HBM busy to the end; only where a row is a quarter longer
+            // than a slot's share of the keys are rows cut, to that share (a cut costs the launch a combine pass, 5 us).
+            // Measured for decode rows over 8 KV heads, cut as for fewer blocks -> whole: 48 rows of 1-6 k tokens 113 -> 104 us
+            // (8-bit cache 68 -> 59), 50 equal rows 107 -> 103 (64 -> 61), 62 equal rows 125 -> 121 (71 -> 69); 40 rows of
+            // 0.5-6 k are better cut (91 against 101 us; 53 against 89).
+            int64_t n_blocks = 0, longest = 0;
+            for (const auto& r : narrow_runs) {
+                n_blocks += r.second;
+                longest = std::max<int64_t>(longest, r.first);
+            }
+            if (2 * n_blocks >= (s.D == 64 ? 4 : 3) * slots) {
+                const int64_t share = std::max<int64_t>(MIN_NARROW_CHUNK, round_up(ceil_div(narrow_keys, slots), KV_TILE));
+                if (4 * longest > 5 * share) narrow_chunk = share;
+            } else {
                 narrow_chunk = choose_chunk(narrow_runs, slots, KV_TILE, MIN_NARROW_CHUNK, NARROW_ITEM_KEYS, 0);
+            }
         }
         // tiles: cut only when fewer than two per slot exist
         if (n_wide > 0 && n_wide < 2 * slots) {
@@ -168,6 +273,11 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
                 wide_chunk = std::max<int64_t>(MIN_WIDE_CHUNK_MIXED, round_up(ceil_div(max_keys, want), KV_TILE));
             }
         }
+    }
+
+    if (by_table) {
+        build_table(s, (int32_t)std::min<int64_t>(narrow_chunk, 1 << 30), opt.append_items, out);
+        return;
     }
 
     // 3. items
@@ -370,20 +480,14 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
         }
     }
     out.items.swap(sorted);
+    out.num_combs = (int64_t)out.combs.size();
 
-    // 4b. append items: consecutive runs of packed rows, whatever request they belong to (a decode batch of 96
-    //     rows is two items, not 96); each names the request and token its first row belongs to.
+    // 4b. append items
     if (opt.append_items) {
-        int r = 0;
-        for (int64_t row = 0; row < out.sum_L; row += APPEND_ITEM_ROWS) {
-            while (row >= (int64_t)out.reqs[r].row_off + out.reqs[r].L) ++r;
-            Item it{r, pack_heads(0, 0, 0, KIND_APPEND), (int32_t)(row - out.reqs[r].row_off),
-                    (int32_t)std::min<int64_t>(APPEND_ITEM_ROWS, out.sum_L - row), 0, 0, -1, out.reqs[r].C, out.reqs[r].row_off,
-                    {0, 0, 0}};
-            out.items.push_back(it);
-            ++out.num_append;
-        }
+        add_append_items(out, out.items);
+        out.num_append = ceil_div(out.sum_L, APPEND_ITEM_ROWS);
     }
+    out.num_items = (int64_t)out.items.size();
 
     // 5. byte layout
     out.off_reqs = 0;

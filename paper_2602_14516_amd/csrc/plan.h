@@ -54,13 +54,71 @@ struct CombItem {         // 32 B, one per query tile whose key range was split
     int32_t pad;
 };
 
-inline int32_t pack_heads(int kvh, int g0, int gn, int kind) {
+#if defined(__HIP__)
+#define AMPD_HD __attribute__((host)) __attribute__((device)) inline __attribute__((always_inline))
+#else
+#define AMPD_HD inline
+#endif
+
+AMPD_HD int32_t pack_heads(int kvh, int g0, int gn, int kind) {
     return kvh | (g0 << 8) | (gn << 16) | (kind << 24);
 }
 
 struct Shape {
     int Hq, Hkv, D, P;
 };
+
+// The work list of a launch of decode rows alone, small enough to travel in the kernel's arguments: no list in the
+// workspace, no staging buffer and no upload in front of the launch.  One entry per row with new tokens; a row's key range
+// is cut into pieces of `chunk` keys and a remainder.  Items in launch order: the whole pieces of all rows, then the
+// remainders, longest first (rows are sorted by their remainder), each row's items by piece and KV head.
+constexpr int ROW_TABLE_MAX = 128;
+struct RowEntry {         // 20 B
+    int32_t C, row_off;
+    int32_t req_L;        // req | L << 24 (L <= 32)
+    int32_t first;        // item index of the row's first whole piece (= whole pieces of the rows before it)
+    int32_t part_off;     // float offset of the row's first partial slot, or -1: the key range is not cut
+};
+struct RowTable {
+    int32_t n, chunk;     // entries; keys per piece
+    int32_t n_whole, n_items;   // items that are whole pieces; all attention items (append items follow them)
+    int32_t sum_L, Hkv, G, D;
+    int32_t max_rows;     // query rows of the tallest item
+    int32_t small;        // workgroups of 4 waves, several to a CU, where the kernel has them (see build_table)
+    RowEntry e[ROW_TABLE_MAX];
+};
+
+// Item idx (< n_items) of the table; row: its entry (see row_of_item).
+AMPD_HD Item table_item(const RowTable& t, const RowEntry& e, int idx) {
+    const int L = e.req_L >> 24, keys = e.C + L, whole = keys / t.chunk;
+    const int pieces = whole + (whole * t.chunk < keys ? 1 : 0);
+    int piece, kvh;
+    if (idx < t.n_whole) {
+        piece = (idx - e.first) / t.Hkv;
+        kvh = idx - e.first - piece * t.Hkv;
+    } else {
+        piece = whole;
+        kvh = (idx - t.n_whole) % t.Hkv;
+    }
+    Item it;
+    it.req = e.req_L & 0xffffff;
+    it.heads = pack_heads(kvh, 0, t.G, KIND_NARROW);
+    it.q0 = 0;
+    it.nq = L;
+    it.kv_begin = piece * t.chunk;
+    it.kv_end = it.kv_begin + t.chunk < keys ? it.kv_begin + t.chunk : keys;
+    it.part_off = e.part_off < 0 ? -1 : e.part_off + (kvh * pieces + piece) * (L * t.G * (t.D + 2));
+    it.C = e.C;
+    it.row_off = e.row_off;
+    it.pad[0] = it.pad[1] = it.pad[2] = 0;
+    return it;
+}
+// The combine work of row e, KV head kvh (nsplit = 1: none).
+AMPD_HD CombItem table_comb(const RowTable& t, const RowEntry& e, int kvh) {
+    const int L = e.req_L >> 24, keys = e.C + L, pieces = (keys + t.chunk - 1) / t.chunk;
+    const int slot = L * t.G * (t.D + 2);
+    return CombItem{e.req_L & 0xffffff, pack_heads(kvh, 0, t.G, KIND_NARROW), 0, L, e.part_off + kvh * pieces * slot, pieces, slot, 0};
+}
 
 constexpr int APPEND_ITEM_ROWS = 64;   // packed rows (new tokens, all heads, K and V) that one append item moves
 
@@ -75,6 +133,11 @@ struct Plan {
     std::vector<ReqInfo> reqs;
     std::vector<Item> items;
     std::vector<CombItem> combs;
+    // A launch of decode rows alone (at most ROW_TABLE_MAX of them): the table stands for items and combs, which stay empty
+    // until materialize() writes the items out for a caller that wants to see them.
+    bool by_table = false;
+    RowTable table;
+    int64_t num_items = 0, num_combs = 0;
     int64_t num_wide = 0, num_narrow = 0, num_append = 0;
     int64_t partial_floats = 0;
     int64_t sum_L = 0;
@@ -88,6 +151,9 @@ struct Plan {
     int64_t off_reqs = 0, off_items = 0, off_combs = 0, off_queues = 0, plan_bytes = 0;
     int64_t off_partial = 0, total_bytes = 0;
 };
+
+// The items of a plan in launch order (a table's written out).
+void plan_items(const Plan& plan, std::vector<Item>& out);
 
 // ctx_len / incr_len must already be validated (non-negative, no overflow).
 void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int32_t* incr_len,
