@@ -191,25 +191,24 @@ ampd_status do_append(const ampd_kv_cache* c, const ampd_batch* b, const void* k
         p.req0 = r0;
         p.h0 = h0;
         p.hn = hn;
-        int max_touched = 0;
+        p.n = n;
+        int64_t pages = 0;
         for (int i = 0; i < n; ++i) {
             const int C = b->h_ctx_len[r0 + i], L = b->h_incr_len[r0 + i];
-            p.C[i] = C;
-            p.L[i] = L;
-            p.row_off[i] = (int32_t)row_off;
+            p.rows[i] = AppendRow{C, L, (int32_t)row_off, (int32_t)pages};
             row_off += L;
-            if (L > 0) max_touched = std::max(max_touched, (C + L - 1) / c->page_size - C / c->page_size + 1);
+            if (L > 0) pages += (C + L - 1) / c->page_size - C / c->page_size + 1;
         }
         if (mode == 0) {
-            if (up && up->bytes > 0 && max_touched > 0) {
+            if (up && up->bytes > 0 && pages > 0) {
                 p.up_src = up->src;
                 p.up_dst = up->dst;
                 p.up_n16 = (int32_t)((up->bytes + 15) / 16);
                 up->bytes = 0;
             }
-            HIP_TRY(launch_append(p, c->kv_dtype == AMPD_KV_FP8_E4M3 ? KV_FP8 : KV_BF16, max_touched, n, st));
+            HIP_TRY(launch_append(p, c->kv_dtype == AMPD_KV_FP8_E4M3 ? KV_FP8 : KV_BF16, pages, st));
         } else
-            HIP_TRY(launch_kv_move(p, mode == 2, max_touched, n, st));
+            HIP_TRY(launch_kv_move(p, mode == 2, pages, st));
     }
     return AMPD_OK;
 }

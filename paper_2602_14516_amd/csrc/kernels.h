@@ -34,6 +34,11 @@ struct AttnParams {
     int32_t nitems;
 };
 
+struct alignas(16) AppendRow {
+    int32_t C, L;
+    int32_t row_off;           // first packed row
+    int32_t pg_off;            // pages of the rows before it that new tokens fall into
+};
 struct AppendParams {
     const void* k_new;         // bf16 [sum L][Hkv][D]
     const void* v_new;
@@ -44,12 +49,15 @@ struct AppendParams {
     const int32_t* block_table;
     int32_t Hkv, D, P, logP, max_pages, req0;
     int32_t h0, hn;            // KV heads [h0, h0 + hn) of the pool; the packed rows hold hn heads
-    // Optional rider: the work list of the attention launch that follows, copied from pinned host memory
-    // into the workspace by one extra z-slice of this launch (up_n16 16-byte vectors; 0: none).
+    // Optional rider: the work list of the attention launch that follows, copied from pinned host memory into the workspace by
+    // the first up_blocks workgroups of this launch (up_n16 16-byte vectors; 0: none).
     const void* up_src;
     void* up_dst;
-    int32_t up_n16;
-    int32_t C[APPEND_MAX_REQS], L[APPEND_MAX_REQS], row_off[APPEND_MAX_REQS];
+    int32_t up_n16, up_blocks;
+    // One workgroup column per page that new tokens fall into: pages [pg0, pg0 + gridDim.x - up_blocks) of the n rows' pages
+    // laid end to end.
+    int32_t n, pg0;
+    AppendRow rows[APPEND_MAX_REQS];
 };
 
 // h_src: pinned, device-visible host memory; bytes is rounded up to 16
@@ -59,8 +67,9 @@ hipError_t launch_attn(const AttnParams& p, int D, int kvt, int grid, hipStream_
 hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid, hipStream_t st);
 // max_rows: the largest nq * heads among the split tiles (sizes the second grid dimension)
 hipError_t launch_combine(const AttnParams& p, const RowTable* t, int D, int ncombs, int max_rows, int max_splits, hipStream_t st);
-hipError_t launch_append(const AppendParams& p, int kvt, int max_pages_touched, int nreq, hipStream_t st);
+// pages: pages of the p.n rows that new tokens fall into; the launchers fill pg0 and up_blocks in p.  0: nothing is launched
+hipError_t launch_append(AppendParams& p, int kvt, int64_t pages, hipStream_t st);
 // bf16 only: pack = pages -> packed rows (k_new / v_new are written), otherwise packed rows -> pages
-hipError_t launch_kv_move(const AppendParams& p, bool pack, int max_pages_touched, int nreq, hipStream_t st);
+hipError_t launch_kv_move(AppendParams& p, bool pack, int64_t pages, hipStream_t st);
 
 }  // namespace ampd

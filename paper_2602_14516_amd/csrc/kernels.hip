@@ -34,6 +34,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -976,18 +977,27 @@ __device__ __forceinline__ uint32_t encode4(float a, float b, float c, float d) 
 __device__ __forceinline__ u32x4 new_chunk(const char* src, int64_t row_bytes, int u, int cph) {
     return *reinterpret_cast<const u32x4*>(src + (u / cph) * row_bytes + (u % cph) * 16);
 }
+__device__ __forceinline__ float chunk_amax(const u32x4& v) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    float amax = 0.0f;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) amax = fmaxf(amax, fmaxf(fabsf(__uint_as_float(w[x] << 16)), fabsf(__uint_as_float(w[x] & 0xffff0000u))));
+    return amax;
+}
+__device__ __forceinline__ u32x2 encode_chunk(const u32x4& v, float inv) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    float f[8];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        f[2 * x] = __uint_as_float(w[x] << 16) * inv;
+        f[2 * x + 1] = __uint_as_float(w[x] & 0xffff0000u) * inv;
+    }
+    return u32x2{encode4(f[0], f[1], f[2], f[3]), encode4(f[4], f[5], f[6], f[7])};
+}
 // this thread's largest magnitude
 __device__ __forceinline__ float page_amax(const char* src, int64_t row_bytes, int n, int cph, int t, int nthr) {
     float amax = 0.0f;
-    for (int u = t; u < n * cph; u += nthr) {
-        const u32x4 v = new_chunk(src, row_bytes, u, cph);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            amax = fmaxf(amax, fabsf(__uint_as_float(w[x] << 16)));
-            amax = fmaxf(amax, fabsf(__uint_as_float(w[x] & 0xffff0000u)));
-        }
-    }
+    for (int u = t; u < n * cph; u += nthr) amax = fmaxf(amax, chunk_amax(new_chunk(src, row_bytes, u, cph)));
     return amax;
 }
 // the page's first n_old slots held codes of exponent e_old: re-encode them for e > e_old
@@ -1005,20 +1015,8 @@ __device__ __forceinline__ void page_reencode(uint8_t* pg, int n_old, int D, int
 __device__ __forceinline__ void page_encode(uint8_t* dst, const char* src, int64_t row_bytes, int n, int D, int e, int t, int nthr) {
     const int cph = D / 8;
     const float inv = __uint_as_float((uint32_t)(127 - e) << 23);
-    for (int u = t; u < n * cph; u += nthr) {
-        const u32x4 v = new_chunk(src, row_bytes, u, cph);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        float f[8];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            f[2 * x] = __uint_as_float(w[x] << 16) * inv;
-            f[2 * x + 1] = __uint_as_float(w[x] & 0xffff0000u) * inv;
-        }
-        u32x2 o;
-        o.x = encode4(f[0], f[1], f[2], f[3]);
-        o.y = encode4(f[4], f[5], f[6], f[7]);
-        *reinterpret_cast<u32x2*>(dst + (u / cph) * D + (u % cph) * 8) = o;
-    }
+    for (int u = t; u < n * cph; u += nthr)
+        *reinterpret_cast<u32x2*>(dst + (u / cph) * D + (u % cph) * 8) = encode_chunk(new_chunk(src, row_bytes, u, cph), inv);
 }
 
 // The append of an item's own new tokens into an 8-bit cache (launches of decode rows alone: one item holds all pages of its
@@ -1659,96 +1657,130 @@ __global__ __launch_bounds__(WG) void combine_rows_kernel(const AttnParams p, co
 }
 
 // ---------------------------------------------------------------------------------------------
-// KV append / pack / unpack, bf16 cache: bit-exact copies.  grid = (pages touched, requests, 2 {K,V})
+// KV append / pack / unpack, as launches of their own.  Bound: HBM, and for small calls the chain row -> page id -> data.
+// One workgroup column per page that new tokens fall into, the rows' pages laid end to end: with a grid of (most pages of a
+// row) x (rows) instead, a prefill row of 45 pages next to 24 decode rows was 19 125 workgroups, 1 100 of them with work (8-bit append
+// 6.8 -> 3.9 us).
 
-// The z-slice past the K / V slices of an append launch carries the work list of the attention launch
-// that follows from pinned host memory into the workspace (saves a launch per call).
+// The workgroups in front of the pages' carry the work list of the attention launch that follows from pinned host memory into
+// the workspace (saves a launch per call).
 __device__ __forceinline__ void upload_rider(const AppendParams& p) {
     const u32x4* src = static_cast<const u32x4*>(p.up_src);
     u32x4* dst = static_cast<u32x4*>(p.up_dst);
-    const int nthreads = gridDim.x * gridDim.y * WG;
-    for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * WG + threadIdx.x; i < p.up_n16; i += nthreads) dst[i] = src[i];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < p.up_n16; i += p.up_blocks * blockDim.x) dst[i] = src[i];
 }
 
+struct PageJob {
+    int page;                  // physical page
+    int C, t0, t1;             // cached tokens of the row; positions [t0, t1) of it are this page's new tokens
+    int row;                   // packed row of token t0
+};
+// Every lane loads a row or two, and the row of this workgroup's page is then picked from the lanes: one trip to the arguments.
+__device__ __forceinline__ PageJob page_job(const AppendParams& p) {
+    const int idx = p.pg0 + (int)blockIdx.x - p.up_blocks, lane = threadIdx.x & 63;
+    static_assert(APPEND_MAX_REQS == 128, "two rows per lane");
+    const AppendRow lo = p.rows[lane];
+    AppendRow hi = {0, 0, 0, 0};
+    if (p.n > 64) hi = p.rows[lane + 64];
+    // the last row whose pages start at or before idx (rows without new tokens share their successor's start)
+    const int r = __popcll(__ballot(lane < p.n && lo.pg_off <= idx)) + __popcll(__ballot(lane + 64 < p.n && hi.pg_off <= idx)) - 1;
+    const AppendRow s = r < 64 ? lo : hi;
+    const int C = __builtin_amdgcn_readlane(s.C, r & 63), L = __builtin_amdgcn_readlane(s.L, r & 63);
+    const int lp = (C >> p.logP) + idx - __builtin_amdgcn_readlane(s.pg_off, r & 63);
+    PageJob j;
+    j.C = C;
+    j.t0 = max(C, lp << p.logP);
+    j.t1 = min(C + L, (lp + 1) << p.logP);
+    j.row = __builtin_amdgcn_readlane(s.row_off, r & 63) + j.t0 - C;
+    j.page = p.block_table[(int64_t)(p.req0 + r) * p.max_pages + lp];
+    return j;
+}
+
+// bf16 cache: bit-exact copies.  grid = (pages, 2 {K, V})
 // PACK = false: packed rows [tokens][hn][D] -> pages (append, or unpack of a received head share);
 // PACK = true:  pages -> packed rows (the send buffer of a KV transfer).
+// Chunks are numbered in page order (head, token, chunk), and four are in flight per thread: 8 700 tokens, 4 of 8 heads of 128,
+// pack and unpack together 18.6 -> 14.3 us, of which the non-temporal stores 2.4 (nothing reads the pages or rows back soon; with
+// non-temporal loads too 17).
 template <bool PACK>
 __global__ __launch_bounds__(WG) void kv_move_bf16_kernel(const AppendParams p) {
-    if (blockIdx.z == 2) {
-        upload_rider(p);
+    if ((int)blockIdx.x < p.up_blocks) {
+        if (blockIdx.y == 0) upload_rider(p);
         return;
     }
-    const int r = blockIdx.y;
-    const int C = p.C[r], L = p.L[r];
-    const int lp = (C >> p.logP) + blockIdx.x;               // logical page
-    const int t0 = max(C, lp << p.logP), t1 = min(C + L, (lp + 1) << p.logP);
-    if (t0 >= t1) return;
-    const int page = p.block_table[(int64_t)(p.req0 + r) * p.max_pages + lp];
-    const int cpt = p.hn * p.D / 8;                          // 16-byte chunks per packed token row
-    const int cph = p.D / 8;
-    char* rows = static_cast<char*>(const_cast<void*>(blockIdx.z ? p.v_new : p.k_new));
-    char* pool = static_cast<char*>(blockIdx.z ? p.v_pool : p.k_pool);
-    const int total = (t1 - t0) * cpt;
-    for (int u = threadIdx.x; u < total; u += WG) {
-        const int t = t0 + u / cpt, rem = u % cpt;
-        const int h = rem / cph, ch = rem % cph;
-        char* rp = rows + (((int64_t)(p.row_off[r] + t - C) * p.hn + h) * p.D + ch * 8) * 2;
-        char* pp = pool + (((((int64_t)page * p.Hkv + p.h0 + h) << p.logP) + (t & (p.P - 1))) * p.D + ch * 8) * 2;
-        if (PACK)
-            *reinterpret_cast<u32x4*>(rp) = *reinterpret_cast<const u32x4*>(pp);
-        else
-            *reinterpret_cast<u32x4*>(pp) = *reinterpret_cast<const u32x4*>(rp);
+    const PageJob j = page_job(p);
+    const int lc = p.D == 128 ? 4 : 3;                       // log2 of the 16-byte chunks per row and head
+    const int s0 = j.t0 & (p.P - 1), ns = j.t1 - j.t0, total = (p.hn * ns) << lc;
+    char* rows = static_cast<char*>(const_cast<void*>(blockIdx.y ? p.v_new : p.k_new)) + (int64_t)j.row * p.hn * p.D * 2;
+    char* pool = static_cast<char*>(blockIdx.y ? p.v_pool : p.k_pool) + ((((int64_t)j.page * p.Hkv + p.h0) << p.logP) + s0) * p.D * 2;
+    const float inv_ns = __builtin_amdgcn_rcpf((float)ns);   // y / ns = (y + 0.5) * inv_ns rounded down: y < 2^14, ns <= 64
+    constexpr int UN = 4;
+    for (int u0 = threadIdx.x; u0 < total; u0 += UN * WG) {
+        u32x4 x[UN];
+        uint32_t dst[UN];                                    // (offsets inside a page or its packed rows: below 2^23)
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            const int u = u0 + i * WG, y = u >> lc;
+            const int h = (int)(((float)y + 0.5f) * inv_ns), tok = y - h * ns, ch = u & ((1 << lc) - 1);
+            const uint32_t ro = ((uint32_t)(tok * p.hn + h) << (lc + 4)) + ch * 16, po = ((uint32_t)((h << p.logP) + tok) << (lc + 4)) + ch * 16;
+            dst[i] = PACK ? ro : po;
+            if (u < total) x[i] = *reinterpret_cast<const u32x4*>(PACK ? pool + po : rows + ro);
+        }
+#pragma unroll
+        for (int i = 0; i < UN; ++i)
+            if (u0 + i * WG < total) __builtin_nontemporal_store(x[i], reinterpret_cast<u32x4*>((PACK ? rows : pool) + dst[i]));
     }
 }
 
-// KV append, 8-bit cache.  grid = (pages touched, requests, 2 {K,V} x KV heads): one block per
-// (page, head), so that the chain amax of the new tokens -> exponent -> (re-encode old slots) -> encode,
-// which is a few dependent memory round trips, runs for all heads at once.
+// 8-bit cache.  grid = (pages, K and V of the KV heads over the workgroup's waves): a wave takes one (page, head, K or V)
+// with all its new tokens in registers: amax -> exponent -> (re-encode old slots) -> encode, one trip to memory in front and
+// one behind.  (A workgroup per tile, which read the tokens twice and passed the exponent through LDS, and a grid padded to the
+// longest row: 8 700 tokens over 8 heads of 128 15.2 -> 11.6 us, 8.2 at the rate of a copy.)
+template <int D, int P>
 __global__ __launch_bounds__(WG) void append_fp8_kernel(const AppendParams p) {
-    __shared__ float red[WG / 64];
-    __shared__ int e_sh[2];
-    if ((int)blockIdx.z == 2 * p.Hkv) {
-        upload_rider(p);
+    constexpr int CPH = D / 8, NCH = P * CPH / 64;           // 8-token-element chunks per token; chunks per lane
+    if ((int)blockIdx.x < p.up_blocks) {
+        if (blockIdx.y == 0) upload_rider(p);
         return;
     }
-    const int r = blockIdx.y;
-    const int C = p.C[r], L = p.L[r];
-    const int lp = (C >> p.logP) + blockIdx.x;
-    const int t0 = max(C, lp << p.logP), t1 = min(C + L, (lp + 1) << p.logP);
-    if (t0 >= t1) return;
-    const int page = p.block_table[(int64_t)(p.req0 + r) * p.max_pages + lp];
-    const int n_old = max(0, C - (lp << p.logP));
-    const int is_v = blockIdx.z & 1, h = blockIdx.z >> 1;
-    const char* src = static_cast<const char*>(is_v ? p.v_new : p.k_new);
-    uint8_t* dst = static_cast<uint8_t*>(is_v ? p.v_pool : p.k_pool);
-    float* scl = is_v ? p.v_scale : p.k_scale;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t row_bytes = (int64_t)p.Hkv * p.D * 2;
-    src += ((int64_t)(p.row_off[r] + t0 - C) * p.Hkv + h) * p.D * 2;
-    float amax = page_amax(src, row_bytes, t1 - t0, p.D / 8, threadIdx.x, WG);
+    const int lane = threadIdx.x & 63;
+    const int unit = __builtin_amdgcn_readfirstlane((int)(blockIdx.y * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+    if (unit >= 2 * p.Hkv) return;
+    const PageJob j = page_job(p);
+    const int is_v = unit & 1, h = unit >> 1, n = j.t1 - j.t0, s0 = j.t0 & (P - 1);
+    const int64_t row_bytes = (int64_t)p.Hkv * D * 2;
+    const char* src = static_cast<const char*>(is_v ? p.v_new : p.k_new) + ((int64_t)j.row * p.Hkv + h) * D * 2;
+    uint8_t* pg = static_cast<uint8_t*>(is_v ? p.v_pool : p.k_pool) + ((int64_t)j.page * p.Hkv + h) * (P * D);
+    float* scl = (is_v ? p.v_scale : p.k_scale) + (int64_t)j.page * p.Hkv + h;
+    const int n_old = max(0, j.C - (j.t0 & ~(P - 1)));       // slots that already hold tokens
+    const float s_old = n_old > 0 ? *scl : 0.0f;
+    u32x4 x[NCH];
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) {
+        const int u = lane + 64 * k;
+        x[k] = u32x4{0, 0, 0, 0};
+        if (u / CPH < n) x[k] = new_chunk(src, row_bytes, u, CPH);
+    }
+    float amax = 0.0f;
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) amax = fmaxf(amax, chunk_amax(x[k]));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-    if (lane == 0) red[wave] = amax;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float a = red[0];
-        for (int w = 1; w < WG / 64; ++w) a = fmaxf(a, red[w]);
-        int e = exponent_for(a);
-        int e_old = e;
-        if (n_old > 0) {
-            const float s_old = scl[(int64_t)page * p.Hkv + h];
-            e_old = (int)(__float_as_uint(s_old) >> 23) - 127;
-            if (e < e_old) e = e_old;
-        }
-        e_sh[0] = e;
-        e_sh[1] = e_old;
-        scl[(int64_t)page * p.Hkv + h] = __uint_as_float((uint32_t)(e + 127) << 23);
+    int e = exponent_for(amax);
+    if (n_old > 0) {
+        const int e_old = (int)(__float_as_uint(s_old) >> 23) - 127;
+        if (e > e_old)
+            page_reencode(pg, n_old, D, e_old, e, lane, 64);
+        else
+            e = e_old;
     }
-    __syncthreads();
-    const int e = e_sh[0], e_old = e_sh[1];
-    uint8_t* pg = dst + ((((int64_t)page * p.Hkv + h) << p.logP)) * p.D;
-    if (n_old > 0 && e > e_old) page_reencode(pg, n_old, p.D, e_old, e, threadIdx.x, WG);
-    page_encode(pg + (int64_t)(t0 & (p.P - 1)) * p.D, src, row_bytes, t1 - t0, p.D, e, threadIdx.x, WG);
+    const float inv = __uint_as_float((uint32_t)(127 - e) << 23);
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) {
+        const int u = lane + 64 * k;
+        if (u / CPH < n) *reinterpret_cast<u32x2*>(pg + (s0 + u / CPH) * D + (u % CPH) * 8) = encode_chunk(x[k], inv);
+    }
+    if (lane == 0) *scl = __uint_as_float((uint32_t)(e + 127) << 23);
 }
 
 // Work-list upload: the workgroups read the host-built plan straight out of pinned host memory
@@ -1830,23 +1862,31 @@ hipError_t launch_combine(const AttnParams& p, const RowTable* t, int D, int nco
     return hipGetLastError();
 }
 
-hipError_t launch_append(const AppendParams& p, int kvt, int max_pages_touched, int nreq, hipStream_t st) {
-    if (nreq <= 0 || max_pages_touched <= 0) return hipSuccess;               // (the caller keeps a rider for later)
-    const int rider = p.up_n16 > 0 ? 1 : 0;
-    if (kvt == KV_BF16)
-        hipLaunchKernelGGL(kv_move_bf16_kernel<false>, dim3(max_pages_touched, nreq, 2 + rider), dim3(WG), 0, st, p);
-    else
-        hipLaunchKernelGGL(append_fp8_kernel, dim3(max_pages_touched, nreq, 2 * p.Hkv + rider), dim3(WG), 0, st, p);
+// f(workgroup columns): one launch per MAX_PAGES pages (a grid holds fewer than 2^32 threads)
+template <class F>
+static hipError_t for_pages(AppendParams& p, int64_t pages, F&& f) {
+    constexpr int64_t MAX_PAGES = 1 << 22;
+    for (int64_t at = 0; at < pages; at += MAX_PAGES) {
+        p.pg0 = (int32_t)at;
+        p.up_blocks = at == 0 ? std::min((p.up_n16 + WG - 1) / WG, 64) : 0;
+        f((unsigned)(std::min(MAX_PAGES, pages - at) + p.up_blocks));
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_kv_move(const AppendParams& p, bool pack, int max_pages_touched, int nreq, hipStream_t st) {
-    if (nreq <= 0 || max_pages_touched <= 0) return hipSuccess;
-    if (pack)
-        hipLaunchKernelGGL(kv_move_bf16_kernel<true>, dim3(max_pages_touched, nreq, 2), dim3(WG), 0, st, p);
-    else
-        hipLaunchKernelGGL(kv_move_bf16_kernel<false>, dim3(max_pages_touched, nreq, 2), dim3(WG), 0, st, p);
-    return hipGetLastError();
+hipError_t launch_append(AppendParams& p, int kvt, int64_t pages, hipStream_t st) {
+    if (kvt == KV_BF16)
+        return for_pages(p, pages, [&](unsigned nx) { hipLaunchKernelGGL(kv_move_bf16_kernel<false>, dim3(nx, 2), dim3(WG), 0, st, p); });
+    void (*kern)(AppendParams) = nullptr;
+    if (p.D == 128) kern = p.P == 16 ? append_fp8_kernel<128, 16> : p.P == 32 ? append_fp8_kernel<128, 32> : append_fp8_kernel<128, 64>;
+    else kern = p.P == 16 ? append_fp8_kernel<64, 16> : p.P == 32 ? append_fp8_kernel<64, 32> : append_fp8_kernel<64, 64>;
+    const int waves = std::min(WG / 64, 2 * p.Hkv);
+    return for_pages(p, pages, [&](unsigned nx) { hipLaunchKernelGGL(kern, dim3(nx, (2 * p.Hkv + waves - 1) / waves), dim3(64 * waves), 0, st, p); });
+}
+
+hipError_t launch_kv_move(AppendParams& p, bool pack, int64_t pages, hipStream_t st) {
+    auto kern = pack ? kv_move_bf16_kernel<true> : kv_move_bf16_kernel<false>;
+    return for_pages(p, pages, [&](unsigned nx) { hipLaunchKernelGGL(kern, dim3(nx, 2), dim3(WG), 0, st, p); });
 }
 
 }  // namespace ampd
