@@ -61,11 +61,11 @@ ampd_status validate(const ampd_kv_cache* c, const ampd_batch* b, bool need_pool
 // the call with the same lengths, and a serving loop often repeats a batch shape; both then plan once.
 namespace {
 struct PlanKey {
-    int32_t Hq = 0, Hkv = 0, D = 0, P = 0, splits = 0;
+    int32_t Hq = 0, Hkv = 0, D = 0, P = 0, splits = 0, kv_bytes = 0;
     bool append_items = false;
     std::vector<int32_t> ctx, incr;
     bool operator==(const PlanKey& o) const {
-        return Hq == o.Hq && Hkv == o.Hkv && D == o.D && P == o.P && splits == o.splits && append_items == o.append_items &&
+        return Hq == o.Hq && Hkv == o.Hkv && D == o.D && P == o.P && splits == o.splits && kv_bytes == o.kv_bytes && append_items == o.append_items &&
                ctx == o.ctx && incr == o.incr;
     }
 };
@@ -77,6 +77,7 @@ thread_local bool t_plan_valid = false;
 ampd_status make_plan(const ampd_kv_cache* c, const ampd_batch* b, const ampd_plan_options* o, bool with_append, const Plan** plan) {
     PlanOptions po;
     po.append_items = with_append && c->kv_dtype == AMPD_KV_BF16;
+    po.kv_bytes = c->kv_dtype == AMPD_KV_FP8_E4M3 ? 1 : 2;
     if (o) {
         if (o->force_kv_splits < 0) return AMPD_ERR_INVALID_ARG;
         for (int i = 0; i < 7; ++i)
@@ -86,6 +87,7 @@ ampd_status make_plan(const ampd_kv_cache* c, const ampd_batch* b, const ampd_pl
     PlanKey key;
     key.Hq = c->num_q_heads; key.Hkv = c->num_kv_heads; key.D = c->head_dim; key.P = c->page_size;
     key.splits = po.force_kv_splits;
+    key.kv_bytes = po.kv_bytes;
     key.append_items = po.append_items;
     key.ctx.assign(b->h_ctx_len, b->h_ctx_len + b->num_reqs);
     key.incr.assign(b->h_incr_len, b->h_incr_len + b->num_reqs);

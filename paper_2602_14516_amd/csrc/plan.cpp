@@ -190,6 +190,7 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     // share of the keys plus half a longest piece; every item adds its fixed cost (item_keys, in keys streamed), and
     // every piece of a cut block the cost of its partial result (split_keys: written, and read again by the combine pass).
     int64_t narrow_chunk = 1 << 30, wide_chunk = 1 << 30;
+    bool wide_first = false;                               // all tiles before all decode rows
     auto choose_chunk = [&](const std::vector<std::pair<int32_t, int32_t>>& runs, int64_t slots, int64_t granule,
                             int64_t min_chunk, int64_t item_keys, int64_t split_keys) {
         auto count_items = [&](int64_t chunk, int64_t* pieces_of_cut_blocks = nullptr) {
@@ -271,6 +272,37 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
                 for (const auto& r : wide_runs) max_keys = std::max<int64_t>(max_keys, r.first);
                 const int64_t want = ceil_div(2 * slots, n_wide);
                 wide_chunk = std::max<int64_t>(MIN_WIDE_CHUNK_MIXED, round_up(ceil_div(max_keys, want), KV_TILE));
+                // Tiles that fit about one round of the slots, whole or in a few pieces: they all start first, and the slots
+                // they leave (or the first to finish) stream the decode rows meanwhile.  The launch then lasts as long as the
+                // longest piece or a slot's share of everything, so the fewest pieces that meet those two ends are best: a
+                // piece costs a start and a partial result.  Where the longest piece would outlast the share by a fifth (whole
+                // tiles, which need no combine pass: by three tenths), the cut above stays.  us per call, before -> so:
+                // 24 rows of 0.7-7 k tokens next to a prefill of 701 over 2 900 (8 KV heads): 8-bit 108 -> 90, bf16 127 -> 110;
+                // next to one of 200 over 6 000: 87 -> 72 and 106 -> 96; 21 rows of 1.4-14 k next to three of up to 2 682
+                // (one KV head) 201 -> 194 and 193 -> 179.  Tiles first when they are more than that: 96 rows next to 8
+                // long prefills 1 627 -> 1 793, since all decode rows then stream at once.
+                const int64_t stage_ns = s.D == 128 ? 3500 : 2200, key_ns = (opt.kv_bytes == 1 ? 9 : 13) * (s.D == 128 ? 10 : 6);
+                int64_t n_rows = 0, best = -1;
+                for (const auto& r : narrow_runs) n_rows += r.second;
+                const int64_t narrow_ns = narrow_keys * key_ns / 10 + std::max<int64_t>(n_rows, std::min<int64_t>(2 * slots, narrow_keys / NARROW_ITEM_KEYS)) * 5000;
+                for (int64_t k = 1; k <= 8; ++k) {
+                    const int64_t chunk = round_up(ceil_div(max_keys, k), WIDE_STAGE_KEYS);
+                    if (k > 1 && chunk < MIN_WIDE_CHUNK_MIXED) break;
+                    int64_t pieces = 0, stages = 0;
+                    for (const auto& r : wide_runs) {
+                        pieces += ceil_div(r.first, chunk) * r.second;
+                        stages += (r.first / chunk * (chunk / WIDE_STAGE_KEYS) + ceil_div(r.first % chunk, WIDE_STAGE_KEYS)) * r.second;
+                    }
+                    if (10 * pieces > 11 * slots) break;
+                    const int64_t longest = ceil_div(std::min(chunk, max_keys), WIDE_STAGE_KEYS) * stage_ns + 7000;
+                    const int64_t share = (stages * stage_ns + pieces * 7000 + narrow_ns) / slots;
+                    const int64_t cost = std::max(longest, share) + (k > 1 ? 3000 + 20 * pieces : 0);
+                    if ((best < 0 || cost < best) && 10 * longest <= (k > 1 ? 12 : 13) * share) {
+                        best = cost;
+                        wide_chunk = chunk;
+                        wide_first = true;
+                    }
+                }
             }
         }
     }
@@ -331,7 +363,8 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     //         than the others.
     //    Narrow items stream their key range exactly once, so they only need balance: longest first.  In a
     //    mixed batch the two kinds alternate in runs of NUM_XCD in proportion to their total cost, so that at
-    //    any time some CUs run compute-bound tiles while others stream decode rows.
+    //    any time some CUs run compute-bound tiles while others stream decode rows (or, see wide_first, the tiles
+    //    go first because they leave slots for that).
     //    Everything is stable and depends on the lengths only.
     std::vector<int32_t> wide_ix, narrow_ix;
     double wide_cost = 0, narrow_cost = 0;
@@ -464,6 +497,7 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
             bool take_wide;
             if (iw >= wide_ix.size()) take_wide = false;
             else if (in >= narrow_ix.size()) take_wide = true;
+            else if (wide_first) take_wide = true;
             else take_wide = dw * narrow_cost <= dn * wide_cost;      // the kind that lags behind its share
             for (int k = 0; k < NUM_XCD; ++k) {
                 if (take_wide ? iw >= wide_ix.size() : in >= narrow_ix.size()) break;

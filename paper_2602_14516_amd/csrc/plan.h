@@ -125,6 +125,7 @@ constexpr int APPEND_ITEM_ROWS = 64;   // packed rows (new tokens, all heads, K 
 struct PlanOptions {
     int force_kv_splits = 0;
     int wg_slots = 256;   // workgroups resident at once: one per CU
+    int kv_bytes = 2;     // bytes of a cached element
     bool append_items = false;   // the page writes of the call ride in the attention launch (bf16 cache): append items
                                  // of APPEND_ITEM_ROWS packed rows each close the work list
 };
