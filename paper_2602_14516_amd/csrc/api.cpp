@@ -249,7 +249,8 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
     uint32_t* slot_flag = nullptr;     // the attention launch below releases the staging slot through these
     uint32_t slot_seq = 0;
 
-    if (use_static || !plan.by_table) {
+    const bool in_args = plan.by_table || plan.by_tiles;               // the work list travels in the kernels' arguments
+    if (use_static || !in_args) {
         std::lock_guard<std::mutex> lk(g_mu);
         DeviceState* d = nullptr;
         if (use_static) {
@@ -261,7 +262,7 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
         } else {
             HIP_TRY(ensure_device(&d));
         }
-        if (!plan.by_table) {                                          // (a table travels in the kernels' arguments)
+        if (!in_args) {
             Slot* s = nullptr;
             PendingUpload up;
             ampd_status vs = stage_plan(*d, plan, workspace, !use_static, &s, &up);
@@ -307,7 +308,9 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
     const int kvt = c->kv_dtype == AMPD_KV_FP8_E4M3 ? KV_FP8 : KV_BF16;
 
     if (timing) HIP_TRY(hipEventRecord(t_ev[1], st));
-    HIP_TRY(plan.by_table ? launch_rows(p, plan.table, kvt, plan.grid, st) : launch_attn(p, c->head_dim, kvt, plan.grid, st));
+    HIP_TRY(plan.by_table   ? launch_rows(p, plan.table, kvt, plan.grid, st)
+            : plan.by_tiles ? launch_tiles(p, plan.tiles, plan.grid, st)
+                            : launch_attn(p, c->head_dim, kvt, plan.grid, st));
     if (timing) HIP_TRY(hipEventRecord(t_ev[2], st));
     int comb_rows = 0, comb_splits = 0;
     for (const CombItem& ci : plan.combs) {
@@ -321,7 +324,8 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
         comb_rows = std::max(comb_rows, L * t.G);
         comb_splits = std::max(comb_splits, (t.e[i].C + L + t.chunk - 1) / t.chunk);
     }
-    HIP_TRY(launch_combine(p, plan.by_table ? &plan.table : nullptr, c->head_dim, (int)plan.num_combs, comb_rows, comb_splits, st));
+    HIP_TRY(launch_combine(p, plan.by_table ? &plan.table : nullptr, plan.by_tiles ? &plan.tiles : nullptr, c->head_dim, (int)plan.num_combs,
+                           comb_rows, comb_splits, st));
     if (timing) {
         HIP_TRY(hipEventRecord(t_ev[3], st));
         t_valid = true;

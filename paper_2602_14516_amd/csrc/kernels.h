@@ -65,8 +65,12 @@ hipError_t launch_upload(const void* h_src, void* d_dst, size_t bytes, hipStream
 hipError_t launch_attn(const AttnParams& p, int D, int kvt, int grid, hipStream_t st);
 // a batch of decode rows alone, whose list travels in the arguments; p.k_new: the call appends (both kinds of cache)
 hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid, hipStream_t st);
+// a small launch of tiles alone over a bf16 cache, likewise
+hipError_t launch_tiles(const AttnParams& p, const TileTable& t, int grid, hipStream_t st);
 // max_rows: the largest nq * heads among the split tiles (sizes the second grid dimension)
-hipError_t launch_combine(const AttnParams& p, const RowTable* t, int D, int ncombs, int max_rows, int max_splits, hipStream_t st);
+// t, tt: the launch went by this table (at most one of them), or null
+hipError_t launch_combine(const AttnParams& p, const RowTable* t, const TileTable* tt, int D, int ncombs, int max_rows, int max_splits,
+                          hipStream_t st);
 // pages: pages of the p.n rows that new tokens fall into; the launchers fill pg0 and up_blocks in p.  0: nothing is launched
 hipError_t launch_append(AppendParams& p, int kvt, int64_t pages, hipStream_t st);
 // bf16 only: pack = pages -> packed rows (k_new / v_new are written), otherwise packed rows -> pages

@@ -1346,19 +1346,18 @@ __device__ __forceinline__ void copy_new_rows(const AttnParams& p, int total, in
     }
 }
 
-__device__ __forceinline__ void append_body(const AttnParams& p, const ItemCtx& ic, int D, int tid) {
+// rows [first_row, first_row + nrows) of the packed rows; req_of(r): the r-th row of the batch, r: one at or before first_row's
+template <class F>
+__device__ __forceinline__ void append_body(const AttnParams& p, int first_row, int nrows, int r, F&& req_of, int D, int tid) {
     const int cpt = p.Hkv * D / 8;                           // 16-byte chunks per packed row (one of K or V)
     const int cph = D / 8;
-    const int first_row = ic.row_off + ic.q0;                // packed row of the item's first token
-    const int total = ic.nq * cpt;
-    int r = ic.req;                                          // request of the row this thread is at: rows only move forward
-    ReqInfo ri = p.reqs[r];
-    copy_new_rows<AWG>(p, total, tid, [&](int u, int64_t& src, int64_t& dst) {
+    ReqInfo ri = req_of(r);                                  // request of the row this thread is at: rows only move forward
+    copy_new_rows<AWG>(p, nrows * cpt, tid, [&](int u, int64_t& src, int64_t& dst) {
         const int row = first_row + u / cpt, rem = u % cpt;
-        while (row >= ri.row_off + ri.L) ri = p.reqs[++r];   // (requests with L = 0 are stepped over)
+        while (row >= ri.row_off + ri.L) ri = req_of(++r);   // (requests with L = 0 are stepped over)
         const int h = rem / cph, ch = rem % cph;
         const int t = ri.C + (row - ri.row_off);
-        const int page = p.block_table[(int64_t)r * p.max_pages + (t >> p.logP)];
+        const int page = p.block_table[(int64_t)ri.req * p.max_pages + (t >> p.logP)];
         src = ((int64_t)row * p.Hkv + h) * D + ch * 8;
         dst = ((((int64_t)page * p.Hkv + h) << p.logP) + (t & (p.P - 1))) * D + ch * 8;
     });
@@ -1415,7 +1414,7 @@ __device__ __forceinline__ void run_item(const AttnParams& p, int idx, uint32_t 
             narrow_body<D, KVT, 32, ATTN_WAVES>(p, ic, smem, tid);
     }
     else if (KVT == KV_BF16)
-        append_body(p, ic, D, tid);
+        append_body(p, ic.row_off + ic.q0, ic.nq, ic.req, [&](int r) { return p.reqs[r]; }, D, tid);
 }
 
 // One workgroup per work item when the items fit one round on the CUs (gridDim.x = number of items).  Otherwise
@@ -1457,6 +1456,23 @@ __global__ __launch_bounds__(AWG, 1) void attn_kernel(const AttnParams p) {
         __syncthreads();                                   // (s_next is written again at the end of the next item)
         if (idx < 0) return;
     }
+}
+
+// A small launch of tiles alone over a bf16 cache, whose list travels in the arguments (see TileTable): one workgroup per tile or
+// piece, then the append items.
+template <int D>
+__global__ __launch_bounds__(AWG, 1) void attn_tiles_kernel(const AttnParams p, const TileTable t) {
+    __shared__ __attribute__((aligned(16))) char smem_raw[Geo<D>::SMEM];
+    const uint32_t smem = (uint32_t)(uintptr_t)LDS_PTR(char, smem_raw);
+    const int idx = blockIdx.x, tid = threadIdx.x;
+    if (idx >= t.n_items) {
+        const int first_row = (idx - t.n_items) * t.append_rows;
+        append_body(p, first_row, min(t.append_rows, t.sum_L - first_row), 0, [&](int r) { return t.rows[r]; }, D, tid);
+        return;
+    }
+    const uint32_t code = t.items[idx];
+    if (code == TILE_NULL) return;                           // a filler that keeps the following items on their XCD
+    wide_body<D, KV_BF16>(p, item_ctx<KV_BF16>(p, tile_item(t, code)), smem, tid);
 }
 
 // The launch of a batch of decode rows alone whose work list travels in the arguments (see RowTable): one workgroup of NW
@@ -1655,6 +1671,10 @@ __global__ __launch_bounds__(WG) void combine_rows_kernel(const AttnParams p, co
     const RowEntry e = t.e[blockIdx.x / t.Hkv];
     if (e.part_off >= 0) combine_tile<D, CR>(p, table_comb(t, e, blockIdx.x % t.Hkv), e.row_off);
 }
+template <int D, int CR>
+__global__ __launch_bounds__(WG) void combine_tiles_kernel(const AttnParams p, const TileTable t) {
+    combine_tile<D, CR>(p, tile_comb(t, blockIdx.x), t.rows[t.combs[blockIdx.x].code & 15].row_off);
+}
 
 // ---------------------------------------------------------------------------------------------
 // KV append / pack / unpack, as launches of their own.  Bound: HBM, and for small calls the chain row -> page id -> data.
@@ -1837,27 +1857,36 @@ hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_tiles(const AttnParams& p, const TileTable& t, int grid, hipStream_t st) {
+    if (t.D == 128) hipLaunchKernelGGL((attn_tiles_kernel<128>), dim3(grid), dim3(AWG), 0, st, p, t);
+    else hipLaunchKernelGGL((attn_tiles_kernel<64>), dim3(grid), dim3(AWG), 0, st, p, t);
+    return hipGetLastError();
+}
+
 // max_rows: rows of the tallest tile; max_splits: splits of the most finely split one
-// t: the launch went by table (ncombs: split tiles in it), or null
+// t, tt: the launch went by this table (ncombs: split tiles in it), or null
 template <int D, int CR>
-static void launch_combine_t(const AttnParams& p, const RowTable* t, int ncombs, int max_rows, hipStream_t st) {
+static void launch_combine_t(const AttnParams& p, const RowTable* t, const TileTable* tt, int ncombs, int max_rows, hipStream_t st) {
     const int ny = (max_rows + CR - 1) / CR;
     if (t)
         hipLaunchKernelGGL((combine_rows_kernel<D, CR>), dim3(t->n * t->Hkv, ny), dim3(WG), 0, st, p, *t);
+    else if (tt)
+        hipLaunchKernelGGL((combine_tiles_kernel<D, CR>), dim3(ncombs, ny), dim3(WG), 0, st, p, *tt);
     else
         hipLaunchKernelGGL((combine_kernel<D, CR>), dim3(ncombs, ny), dim3(WG), 0, st, p);
 }
 
-hipError_t launch_combine(const AttnParams& p, const RowTable* t, int D, int ncombs, int max_rows, int max_splits, hipStream_t st) {
+hipError_t launch_combine(const AttnParams& p, const RowTable* t, const TileTable* tt, int D, int ncombs, int max_rows, int max_splits,
+                          hipStream_t st) {
     if (ncombs <= 0) return hipSuccess;
     // many splits and a launch that would otherwise leave most of the chip idle: let thread slices share the splits
     const bool sliced = max_splits > 16 && (int64_t)ncombs * ((max_rows + COMB_ROWS - 1) / COMB_ROWS) < 512;
     if (D == 128) {
-        if (sliced) launch_combine_t<128, COMB_ROWS_SLICED>(p, t, ncombs, max_rows, st);
-        else launch_combine_t<128, COMB_ROWS>(p, t, ncombs, max_rows, st);
+        if (sliced) launch_combine_t<128, COMB_ROWS_SLICED>(p, t, tt, ncombs, max_rows, st);
+        else launch_combine_t<128, COMB_ROWS>(p, t, tt, ncombs, max_rows, st);
     } else {
-        if (sliced) launch_combine_t<64, COMB_ROWS_SLICED>(p, t, ncombs, max_rows, st);
-        else launch_combine_t<64, COMB_ROWS>(p, t, ncombs, max_rows, st);
+        if (sliced) launch_combine_t<64, COMB_ROWS_SLICED>(p, t, tt, ncombs, max_rows, st);
+        else launch_combine_t<64, COMB_ROWS>(p, t, tt, ncombs, max_rows, st);
     }
     return hipGetLastError();
 }

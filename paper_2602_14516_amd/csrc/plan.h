@@ -29,7 +29,7 @@ constexpr int NUM_QUEUES = 8;      // accelerator dies (XCDs): workgroup i of a 
 constexpr int APPEND_MAX_REQS = 128;   // requests per append launch (their lengths travel as kernel arguments)
 
 struct ReqInfo {          // 16 B, one per request, device-visible
-    int32_t C, L, row_off, pad;
+    int32_t C, L, row_off, req;
 };
 
 struct Item {             // 48 B, one per attention workgroup, device-visible
@@ -120,6 +120,49 @@ AMPD_HD CombItem table_comb(const RowTable& t, const RowEntry& e, int kvh) {
     return CombItem{e.req_L & 0xffffff, pack_heads(kvh, 0, t.G, KIND_NARROW), 0, L, e.part_off + kvh * pieces * slot, pieces, slot, 0};
 }
 
+// The work list of a small launch of tiles alone, in the kernel's arguments for the same reason: one word per item and 8 bytes
+// per cut tile.
+constexpr int TILE_TABLE_ROWS = 16, TILE_TABLE_ITEMS = 256, TILE_TABLE_COMBS = 128;
+constexpr uint32_t TILE_NULL = 0xffffffffu;
+struct TileComb {
+    uint32_t code;            // as an item's, piece 0
+    int32_t part_off;         // float offset of split 0
+};
+struct TileTable {
+    int32_t n_rows, n_items, n_combs;
+    int32_t chunk, tq;        // keys per piece; tokens of a full tile (a row's first tile takes the remainder)
+    int32_t G, D, sum_L;
+    int32_t append_rows;      // packed rows per append item
+    ReqInfo rows[TILE_TABLE_ROWS];          // rows with new tokens
+    uint32_t items[TILE_TABLE_ITEMS];       // row | kvh << 4 | tile << 10 | piece << 18 | cut tile << 25, or TILE_NULL
+    TileComb combs[TILE_TABLE_COMBS];
+};
+
+// Tile and piece of a code.
+AMPD_HD Item tile_item(const TileTable& t, uint32_t code) {
+    const ReqInfo& r = t.rows[code & 15];
+    const int kvh = (code >> 4) & 63, tile = (code >> 10) & 255, piece = (code >> 18) & 127;
+    const int rest = r.L % t.tq, first = rest ? rest : t.tq;
+    Item it;
+    it.req = r.req;
+    it.heads = pack_heads(kvh, 0, t.G, KIND_WIDE);
+    it.q0 = tile ? first + (tile - 1) * t.tq : 0;
+    it.nq = tile ? t.tq : first;
+    const int keys = r.C + it.q0 + it.nq;
+    it.kv_begin = piece * t.chunk;
+    it.kv_end = keys - it.kv_begin > t.chunk ? it.kv_begin + t.chunk : keys;
+    it.part_off = keys > t.chunk ? t.combs[code >> 25].part_off + piece * (it.nq * t.G * (t.D + 2)) : -1;
+    it.C = r.C;
+    it.row_off = r.row_off;
+    it.pad[0] = it.pad[1] = it.pad[2] = 0;
+    return it;
+}
+AMPD_HD CombItem tile_comb(const TileTable& t, int i) {
+    const Item it = tile_item(t, t.combs[i].code);
+    const int keys = it.C + it.q0 + it.nq;
+    return CombItem{it.req, it.heads, it.q0, it.nq, t.combs[i].part_off, (keys + t.chunk - 1) / t.chunk, it.nq * t.G * (t.D + 2), 0};
+}
+
 constexpr int APPEND_ITEM_ROWS = 64;   // packed rows (new tokens, all heads, K and V) that one append item moves
 
 struct PlanOptions {
@@ -138,6 +181,9 @@ struct Plan {
     // until materialize() writes the items out for a caller that wants to see them.
     bool by_table = false;
     RowTable table;
+    // A small launch of tiles alone over a bf16 cache: `tiles` says the same as items and combs.
+    bool by_tiles = false;
+    TileTable tiles;
     int64_t num_items = 0, num_combs = 0;
     int64_t num_wide = 0, num_narrow = 0, num_append = 0;
     int64_t partial_floats = 0;
