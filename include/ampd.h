@@ -165,7 +165,8 @@ ampd_status ampd_kv_unpack(const ampd_kv_cache *cache, const ampd_batch *batch, 
  * launch runs first and attention reads the quantised pages; in a batch of decode rows alone
  * (every row has at most 32 query rows per KV head; up to 128 rows with new tokens) the items
  * that read a row's last pages quantise its new tokens themselves, and the work list travels
- * in the kernel's arguments.
+ * in the kernel's arguments (as it does for up to 256 prefill tiles or pieces of at most 16
+ * rows alone over a bf16 cache).
  * q: DEVICE bf16 [sum L][Hq][d];  out: DEVICE bf16 [sum L][Hq][d].
  * workspace: DEVICE, 256-byte aligned, >= ampd_workspace_bytes(). */
 ampd_status ampd_incr_prefill_attn(const ampd_kv_cache *cache, const ampd_batch *batch,
