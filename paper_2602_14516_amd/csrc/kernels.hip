@@ -1055,10 +1055,10 @@ __device__ __forceinline__ void append_item_pages(const AttnParams& p, const Ite
     }
 }
 
-// The same for a row with one new token (a decode step), by the one wave that will read the token's page, without holding up
-// the others: start() issues the loads before the wave streams its first block, finish() encodes and stores when the wave is
-// about to fetch the row's last block, which is the only one that holds the token.  Lanes 0 .. D/8 - 1 carry K, as many
-// after them V.  (Done by the whole workgroup in front of its stream instead, the append cost a launch of 608 items 6 us.)
+// The same for a row with one new token (a decode step) whose page's cached tokens all lie in the row's last block (see
+// page_in_last_block: finish() may re-encode every one of them, and no other wave may be reading them), by the one wave that
+// streams that block, without holding up the others: start() issues the loads before the wave streams its first block, finish()
+// encodes and stores when the wave is about to fetch the last block.  Lanes 0 .. D/8 - 1 carry K, as many after them V.  (Done by the whole workgroup in front of its stream instead, the append cost a launch of 608 items 6 us.)
 template <int D>
 struct NewToken {
     static constexpr int CPK = D / 8;
@@ -1168,7 +1168,7 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
     };
     if (wave < nblocks) ld.fetch_pages(p, ic, ic.kv_begin + wave * 32, lane);
     if (QUANT && p.k_new && ic.kv_end > ic.C) {           // uniform
-        if (ONE_TOKEN && ic.nq == 1) {
+        if (ONE_TOKEN && ic.nq == 1 && page_in_last_block(ic.C, p.P)) {
             pending = wave == (nblocks - 1) % NW;
             if (pending) nt.start(p, ic, lane);
             if (pending && wave == nblocks - 1) nt.start_scale(p, ic, lane);

@@ -163,6 +163,11 @@ AMPD_HD CombItem tile_comb(const TileTable& t, int i) {
     return CombItem{it.req, it.heads, it.q0, it.nq, t.combs[i].part_off, (keys + t.chunk - 1) / t.chunk, it.nq * t.G * (t.D + 2), 0};
 }
 
+// Whether the page slots up to position C (a row's one new token) all lie in the 32-key block of a narrow item that holds the
+// token.  Blocks start at multiples of 32 and pages at multiples of P, so only the upper half of a 64-slot page shares its page
+// with the block before it.
+AMPD_HD bool page_in_last_block(int C, int P) { return ((C & (P - 1)) & 32) == 0; }
+
 constexpr int APPEND_ITEM_ROWS = 64;   // packed rows (new tokens, all heads, K and V) that one append item moves
 
 struct PlanOptions {

@@ -82,3 +82,47 @@ def test_decode_rows_8bit(name, C, L, Hq, Hkv, d, P):
                                       int(C[r]), int(L[r]), scale) for r in range(len(C))]
     mx, mean = errs(from_dev_bits(out), ref, off)
     assert mx <= TOL_BF16[0] and mean <= TOL_BF16[1], (mx, mean)
+
+
+@pytest.mark.parametrize("P", [16, 32, 64])
+@pytest.mark.parametrize("Hq,Hkv,d", [(32, 8, 128), (8, 2, 64)])
+def test_one_new_token_raises_the_page_exponent(Hq, Hkv, d, P):
+    """8-bit cache: the token's page also holds cached tokens, in the row's last 32-key block or in the one before it too, and all
+    of them are re-encoded while the row is being read (history 2^-6 of the new tokens' size: every exponent rises).  Attention
+    in the same launch is bit for bit what attention alone reads from the finished pages with the same cut, and the oracle's."""
+    print(f"case: one new token, d {d}, P {P}", flush=True)
+    rng = np.random.default_rng(29)
+    C = np.array([b * 64 + s for b in (0, 5, 9) for s in (0, 1, 15, 31, 32, 33, 40, 63)], np.int32)   # up to 20 blocks, 8 waves
+    L = np.ones_like(C)
+    pages = C // P + 1
+    perm = rng.permutation(int(pages.sum()) + 2).astype(np.int32)
+    bt = np.full((len(C), int(pages.max())), -1, np.int32)
+    o = 0
+    for r in range(len(C)):
+        bt[r, :pages[r]] = perm[o:o + pages[r]]
+        o += pages[r]
+    scale = 1.0 / np.sqrt(d)
+    pool = Fp8Pool(len(perm), Hq, Hkv, d, P, scale)
+    d_bt = torch.from_numpy(bt).cuda()
+
+    def rows(n, mult):
+        return W.f32_to_bf16_bits(rng.standard_normal((n, Hkv, d), dtype=np.float32) * np.float32(mult))
+
+    k, v = rows(int(C.sum()), 2.0 ** -6), rows(int(C.sum()), 2.0 ** -6)
+    A.kv_append(pool.cache, np.zeros_like(C), C, d_bt, to_dev_bits(k), to_dev_bits(v))
+    pool.reference_append(bt, np.zeros_like(C), C, k, v)
+    q = W.f32_to_bf16_bits(rng.standard_normal((len(C), Hq, d), dtype=np.float32))
+    k, v = rows(len(C), 1.0), rows(len(C), 1.0)
+    out = A.mixed_batch_attn(pool.cache, C, L, d_bt, to_dev_bits(q), to_dev_bits(k), to_dev_bits(v), block_table_host=bt)
+    torch.cuda.synchronize()
+    pool.reference_append(bt, C, L, k, v)
+    pool.assert_equal()
+    again = A.paged_attn(pool.cache, C, L, d_bt, to_dev_bits(q))
+    assert np.array_equal(from_dev_bits(out), from_dev_bits(again))
+    off = np.arange(len(C) + 1)
+    ref = [oracle.attn_oracle_request(W.bf16_bits_to_f64(q[r:r + 1]),
+                                      oracle.fp8_dequant_request(pool.h_k, pool.h_ks, bt[r], int(C[r] + 1), P),
+                                      oracle.fp8_dequant_request(pool.h_v, pool.h_vs, bt[r], int(C[r] + 1), P),
+                                      int(C[r]), 1, scale) for r in range(len(C))]
+    mx, mean = errs(from_dev_bits(out), ref, off)
+    assert mx <= TOL_BF16[0] and mean <= TOL_BF16[1], (mx, mean)
