@@ -85,7 +85,7 @@ def test_decode_rows_8bit(name, C, L, Hq, Hkv, d, P):
 
 
 @pytest.mark.parametrize("P", [16, 32, 64])
-@pytest.mark.parametrize("Hq,Hkv,d", [(32, 8, 128), (8, 2, 64)])
+@pytest.mark.parametrize("Hq,Hkv,d", [(32, 8, 128), (32, 8, 64)])
 def test_one_new_token_raises_the_page_exponent(Hq, Hkv, d, P):
     """8-bit cache: the token's page also holds cached tokens, in the row's last 32-key block or in the one before it too, and all
     of them are re-encoded while the row is being read (history 2^-6 of the new tokens' size: every exponent rises).  Attention
