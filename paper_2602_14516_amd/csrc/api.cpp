@@ -250,7 +250,7 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
     uint32_t slot_seq = 0;
 
     const bool in_args = plan.by_table || plan.by_tiles;               // the work list travels in the kernels' arguments
-    if (use_static || !in_args) {
+    {
         std::lock_guard<std::mutex> lk(g_mu);
         DeviceState* d = nullptr;
         if (use_static) {
@@ -260,7 +260,7 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
             d = &g_dev[dev];
             workspace = d->static_ws;
         } else {
-            HIP_TRY(ensure_device(&d));
+            HIP_TRY(ensure_device(&d));            // also where this launch needs no slot: a later call finds the device set up
         }
         if (!in_args) {
             Slot* s = nullptr;
