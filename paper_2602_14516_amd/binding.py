@@ -8,6 +8,7 @@ from __future__ import annotations
 import ctypes
 import os
 import struct
+import types
 from dataclasses import dataclass
 
 import numpy as np
@@ -72,58 +73,56 @@ class _HostOnly:
         raise RuntimeError(f"{self._name} is not part of a host-only build of libampd")
 
 
+def _declare(f, cp, bp):
+    """Result and argument types of the entry points that f holds; cp, bp: of an ampd_kv_cache / ampd_batch argument."""
+    vp, sz, i32, i64 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32, ctypes.c_int64
+    op = ctypes.POINTER(_Opts)
+    attn = [cp, bp, vp, vp, vp, vp, vp, sz, vp]
+    for name, res, args in (
+            ("ampd_workspace_bytes", sz, [cp, bp]),
+            ("ampd_workspace_bytes_opts", sz, [cp, bp, op]),
+            ("ampd_kv_append", i32, [cp, bp, vp, vp, vp]),
+            ("ampd_kv_pack", i32, [cp, bp, i32, i32, vp, vp, vp]),
+            ("ampd_kv_unpack", i32, [cp, bp, i32, i32, vp, vp, vp]),
+            ("ampd_incr_prefill_attn", i32, attn),
+            ("ampd_mixed_batch_attn", i32, attn),
+            ("ampd_incr_prefill_attn_opts", i32, attn + [op]),
+            ("ampd_mixed_batch_attn_opts", i32, attn + [op]),
+            ("ampd_paged_attn", i32, [cp, bp, vp, vp, vp, sz, vp, op]),
+            ("ampd_init", i32, []),
+            ("ampd_static_workspace_limit", sz, []),
+            ("ampd_mixed_batch_attn_static", i32, [cp, bp, vp, vp, vp, vp, vp]),
+            ("ampd_plan_describe", i32, [cp, bp, op, ctypes.POINTER(_PlanInfo)]),
+            ("ampd_plan_items", i64, [cp, bp, op, vp, i64]),
+            ("ampd_set_timing", None, [ctypes.c_int]),
+            ("ampd_last_timing", i32, [ctypes.POINTER(ctypes.c_float)] * 3),
+            ("ampd_status_string", ctypes.c_char_p, [i32]),
+            ("ampd_version", ctypes.c_char_p, [])):
+        fn = getattr(f, name)
+        fn.restype = res
+        fn.argtypes = args
+
+
 def _load():
+    """The library, and its entry points once more as functions that take the two structures by address."""
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: build it with `python paper_2602_14516_amd/build.py` "
                           "(there is no fallback path)")
     L = ctypes.CDLL(LIB_PATH)
-    if os.environ.get("AMPD_HOST_ONLY") == "1":
-        for name in EXPORTED_SYMBOLS:
-            if name not in HOST_ONLY_SYMBOLS:
-                setattr(L, name, _HostOnly(name))
-    vp, sz, i32, i64 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32, ctypes.c_int64
-    cp = bp = vp                       # the address of an ampd_kv_cache / ampd_batch: byref(structure) or its packed bytes
-    op = ctypes.POINTER(_Opts)
-    L.ampd_workspace_bytes.restype = sz
-    L.ampd_workspace_bytes.argtypes = [cp, bp]
-    L.ampd_workspace_bytes_opts.restype = sz
-    L.ampd_workspace_bytes_opts.argtypes = [cp, bp, op]
-    L.ampd_kv_append.restype = i32
-    L.ampd_kv_append.argtypes = [cp, bp, vp, vp, vp]
-    for name in ("ampd_kv_pack", "ampd_kv_unpack"):
-        f = getattr(L, name)
-        f.restype = i32
-        f.argtypes = [cp, bp, i32, i32, vp, vp, vp]
-    for name in ("ampd_incr_prefill_attn", "ampd_mixed_batch_attn"):
-        f = getattr(L, name)
-        f.restype = i32
-        f.argtypes = [cp, bp, vp, vp, vp, vp, vp, sz, vp]
-        f = getattr(L, name + "_opts")
-        f.restype = i32
-        f.argtypes = [cp, bp, vp, vp, vp, vp, vp, sz, vp, op]
-    L.ampd_paged_attn.restype = i32
-    L.ampd_paged_attn.argtypes = [cp, bp, vp, vp, vp, sz, vp, op]
-    L.ampd_init.restype = i32
-    L.ampd_init.argtypes = []
-    L.ampd_static_workspace_limit.restype = sz
-    L.ampd_static_workspace_limit.argtypes = []
-    L.ampd_mixed_batch_attn_static.restype = i32
-    L.ampd_mixed_batch_attn_static.argtypes = [cp, bp, vp, vp, vp, vp, vp]
-    L.ampd_plan_describe.restype = i32
-    L.ampd_plan_describe.argtypes = [cp, bp, op, ctypes.POINTER(_PlanInfo)]
-    L.ampd_plan_items.restype = i64
-    L.ampd_plan_items.argtypes = [cp, bp, op, vp, i64]
-    L.ampd_set_timing.restype = None
-    L.ampd_set_timing.argtypes = [ctypes.c_int]
-    L.ampd_last_timing.restype = i32
-    L.ampd_last_timing.argtypes = [ctypes.POINTER(ctypes.c_float)] * 3
-    L.ampd_status_string.restype = ctypes.c_char_p
-    L.ampd_status_string.argtypes = [i32]
-    L.ampd_version.restype = ctypes.c_char_p
-    return L
+    packed = types.SimpleNamespace()
+    host_only = os.environ.get("AMPD_HOST_ONLY") == "1"
+    for name in EXPORTED_SYMBOLS:
+        if host_only and name not in HOST_ONLY_SYMBOLS:
+            setattr(L, name, _HostOnly(name))
+            setattr(packed, name, _HostOnly(name))
+        else:
+            setattr(packed, name, L[name])          # a function object of its own
+    _declare(L, ctypes.POINTER(_Cache), ctypes.POINTER(_Batch))
+    _declare(packed, ctypes.c_void_p, ctypes.c_void_p)
+    return L, packed
 
 
-lib = _load()
+lib, _packed = _load()
 
 
 def status_string(s: int) -> str:
@@ -182,7 +181,8 @@ def _batch(ctx_len, incr_len, block_table_dev, block_table_host=None, max_pages=
     return b, (ctx, inc, bth)          # keep the host arrays alive for the duration of the call
 
 
-# The two structures of a call as packed bytes, which ctypes hands over by address.  A decode step of one row takes 9 us on the
+# The two structures of a call as packed bytes, which the functions in _packed take by address (lib's own take the structures and
+# check their types).  A decode step of one row takes 9 us on the
 # GPU, and building the ctypes structures (numpy's .ctypes, one conversion per field) took a third of the 14.5 us that calls of it
 # were apart; packed, they are 10.5 us apart (one short prefill 13.2 -> 10.4, a pack and an unpack of 8 700 tokens 20.8 -> 18.3).
 _pack_cache = struct.Struct("@6iq4Pfi").pack
@@ -274,7 +274,7 @@ def kv_append(cache: KVCache, ctx_len, incr_len, block_table, k_new, v_new, *, s
               block_table_host=None) -> None:
     b, keep = _batch_arg(ctx_len, incr_len, block_table, block_table_host)
     c = _cache_arg(cache)
-    _check(lib.ampd_kv_append(c, b, _ptr(k_new), _ptr(v_new), _stream_ptr(stream)),
+    _check(_packed.ampd_kv_append(c, b, _ptr(k_new), _ptr(v_new), _stream_ptr(stream)),
            "ampd_kv_append")
 
 
@@ -283,7 +283,7 @@ def kv_pack(cache: KVCache, first_token, num_tokens, block_table, head_begin, he
     """Pages -> packed rows [sum tokens, head_count, d] for KV heads [head_begin, head_begin + head_count)."""
     b, keep = _batch_arg(first_token, num_tokens, block_table, block_table_host)
     c = _cache_arg(cache)
-    _check(lib.ampd_kv_pack(c, b, int(head_begin), int(head_count), _ptr(k_out), _ptr(v_out),
+    _check(_packed.ampd_kv_pack(c, b, int(head_begin), int(head_count), _ptr(k_out), _ptr(v_out),
                             _stream_ptr(stream)), "ampd_kv_pack")
 
 
@@ -292,7 +292,7 @@ def kv_unpack(cache: KVCache, first_token, num_tokens, block_table, head_begin, 
     """Packed rows -> pages, the inverse of kv_pack."""
     b, keep = _batch_arg(first_token, num_tokens, block_table, block_table_host)
     c = _cache_arg(cache)
-    _check(lib.ampd_kv_unpack(c, b, int(head_begin), int(head_count), _ptr(k_in), _ptr(v_in),
+    _check(_packed.ampd_kv_unpack(c, b, int(head_begin), int(head_count), _ptr(k_in), _ptr(v_in),
                               _stream_ptr(stream)), "ampd_kv_unpack")
 
 
@@ -318,9 +318,9 @@ def _attn_call(fn_name, cache, ctx_len, incr_len, block_table, q, k_new, v_new, 
     if out is None:
         out = torch.empty_like(q)
     if workspace is None:
-        need = int(lib.ampd_workspace_bytes_opts(c, b, o))
+        need = int(_packed.ampd_workspace_bytes_opts(c, b, o))
         workspace = _temp_workspace(need, q, stream)
-    fn = getattr(lib, fn_name + "_opts")
+    fn = getattr(_packed, fn_name + "_opts")
     _check(fn(c, b, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out), _ptr(workspace),
               workspace.numel() * workspace.element_size(), _stream_ptr(stream), o), fn_name)
     return out
@@ -354,7 +354,7 @@ def mixed_batch_attn_static(cache: KVCache, ctx_len, incr_len, block_table, q, k
     """mixed_batch_attn on the library's static workspace: the call allocates nothing (out is required)."""
     b, keep = _batch_arg(ctx_len, incr_len, block_table, block_table_host)
     c = _cache_arg(cache)
-    _check(lib.ampd_mixed_batch_attn_static(c, b, _ptr(q), _ptr(k_new), _ptr(v_new),
+    _check(_packed.ampd_mixed_batch_attn_static(c, b, _ptr(q), _ptr(k_new), _ptr(v_new),
                                             _ptr(out), _stream_ptr(stream)), "ampd_mixed_batch_attn_static")
     return out
 
@@ -369,9 +369,9 @@ def paged_attn(cache: KVCache, ctx_len, incr_len, block_table, q, *, out=None, w
     if out is None:
         out = torch.empty_like(q)
     if workspace is None:
-        need = int(lib.ampd_workspace_bytes_opts(c, b, o))
+        need = int(_packed.ampd_workspace_bytes_opts(c, b, o))
         workspace = _temp_workspace(need, q, stream)
-    _check(lib.ampd_paged_attn(c, b, _ptr(q), _ptr(out), _ptr(workspace),
+    _check(_packed.ampd_paged_attn(c, b, _ptr(q), _ptr(out), _ptr(workspace),
                                workspace.numel() * workspace.element_size(), _stream_ptr(stream), o),
            "ampd_paged_attn")
     return out

@@ -29,3 +29,16 @@ def test_packed_arguments_equal_the_structures(n, fp8, scale):
         got = b._Batch.from_buffer_copy(arg)
         assert len(arg) == ctypes.sizeof(b._Batch)
         assert [getattr(got, f) for f, _ in b._Batch._fields_] == [getattr(s, f) for f, _ in b._Batch._fields_]
+
+
+def test_the_library_s_own_functions_check_the_structures():
+    cache = b.KVCache(8, 2, 64, 16, None, None, 0.125).c_struct()
+    batch, keep = b._batch([100, 5], [1, 7], None, max_pages=8)
+    want = b.lib.ampd_workspace_bytes(ctypes.byref(cache), ctypes.byref(batch))
+    assert want > 0
+    assert b.lib.ampd_workspace_bytes(cache, batch) == want                 # a structure itself, as a POINTER argument takes it
+    assert b.lib.ampd_workspace_bytes(ctypes.pointer(cache), ctypes.pointer(batch)) == want
+    for wrong in ((ctypes.byref(batch), ctypes.byref(cache)), (batch, cache), (bytes(cache), bytes(batch)), (cache, 64)):
+        with pytest.raises(ctypes.ArgumentError):
+            b.lib.ampd_workspace_bytes(*wrong)
+    assert b._packed.ampd_workspace_bytes(bytes(cache), bytes(batch)) == want
