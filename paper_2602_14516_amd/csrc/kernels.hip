@@ -1752,20 +1752,24 @@ __global__ __launch_bounds__(WG) void kv_move_bf16_kernel(const AppendParams p) 
     }
 }
 
-// 8-bit cache.  grid = (pages, K and V of the KV heads over the workgroup's waves): a wave takes one (page, head, K or V)
+// 8-bit cache.  grid = (pages, K and V of the KV heads over the workgroup's waves): WPU waves take one (page, head, K or V)
 // with all its new tokens in registers: amax -> exponent -> (re-encode old slots) -> encode, one trip to memory in front and
-// one behind.  (A workgroup per tile, which read the tokens twice and passed the exponent through LDS, and a grid padded to the
-// longest row: 8 700 tokens over 8 heads of 128 15.2 -> 11.6 us, 8.2 at the rate of a copy.)
-template <int D, int P>
+// one behind.  Many units: a wave each (a workgroup each, which read the tokens twice, and a grid padded to the longest row:
+// 8 700 tokens over 8 heads of 128 15.2 -> 11.6 us, 8.2 at the rate of a copy).  Few: up to four waves share one, since a page of 64
+// tokens of 128 is 16 chunks per lane of one wave, all in a row.
+template <int D, int P, int WPU>
 __global__ __launch_bounds__(WG) void append_fp8_kernel(const AppendParams p) {
-    constexpr int CPH = D / 8, NCH = P * CPH / 64;           // 8-token-element chunks per token; chunks per lane
+    constexpr int CPH = D / 8, NCH = P * CPH / (64 * WPU);   // 8-token-element chunks per token; chunks per lane
+    static_assert(NCH >= 1, "every wave of a unit has a chunk per lane");
+    __shared__ float shared_amax[WG / 64], shared_scale[WG / 64];
     if ((int)blockIdx.x < p.up_blocks) {
         if (blockIdx.y == 0) upload_rider(p);
         return;
     }
     const int lane = threadIdx.x & 63;
-    const int unit = __builtin_amdgcn_readfirstlane((int)(blockIdx.y * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-    if (unit >= 2 * p.Hkv) return;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int unit = (int)(blockIdx.y * ((blockDim.x >> 6) / WPU)) + wave / WPU, t = (wave % WPU) * 64 + lane;
+    if (WPU == 1 && unit >= 2 * p.Hkv) return;               // (WPU > 1: the units fill their workgroups, see launch_append)
     const PageJob j = page_job(p);
     const int is_v = unit & 1, h = unit >> 1, n = j.t1 - j.t0, s0 = j.t0 & (P - 1);
     const int64_t row_bytes = (int64_t)p.Hkv * D * 2;
@@ -1773,11 +1777,11 @@ __global__ __launch_bounds__(WG) void append_fp8_kernel(const AppendParams p) {
     uint8_t* pg = static_cast<uint8_t*>(is_v ? p.v_pool : p.k_pool) + ((int64_t)j.page * p.Hkv + h) * (P * D);
     float* scl = (is_v ? p.v_scale : p.k_scale) + (int64_t)j.page * p.Hkv + h;
     const int n_old = max(0, j.C - (j.t0 & ~(P - 1)));       // slots that already hold tokens
-    const float s_old = n_old > 0 ? *scl : 0.0f;
+    float s_old = n_old > 0 && t < 64 ? *scl : 0.0f;
     u32x4 x[NCH];
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
-        const int u = lane + 64 * k;
+        const int u = t + 64 * WPU * k;
         x[k] = u32x4{0, 0, 0, 0};
         if (u / CPH < n) x[k] = new_chunk(src, row_bytes, u, CPH);
     }
@@ -1786,21 +1790,32 @@ __global__ __launch_bounds__(WG) void append_fp8_kernel(const AppendParams p) {
     for (int k = 0; k < NCH; ++k) amax = fmaxf(amax, chunk_amax(x[k]));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+    if constexpr (WPU > 1) {                                 // the unit's first wave has read the scale it will overwrite
+        const int w0 = wave / WPU * WPU;
+        if (lane == 0) {
+            shared_amax[wave] = amax;
+            shared_scale[wave] = s_old;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WPU; ++w) amax = fmaxf(amax, shared_amax[w0 + w]);
+        s_old = shared_scale[w0];
+    }
     int e = exponent_for(amax);
     if (n_old > 0) {
         const int e_old = (int)(__float_as_uint(s_old) >> 23) - 127;
         if (e > e_old)
-            page_reencode(pg, n_old, D, e_old, e, lane, 64);
+            page_reencode(pg, n_old, D, e_old, e, t, 64 * WPU);
         else
             e = e_old;
     }
     const float inv = __uint_as_float((uint32_t)(127 - e) << 23);
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
-        const int u = lane + 64 * k;
+        const int u = t + 64 * WPU * k;
         if (u / CPH < n) *reinterpret_cast<u32x2*>(pg + (s0 + u / CPH) * D + (u % CPH) * 8) = encode_chunk(x[k], inv);
     }
-    if (lane == 0) *scl = __uint_as_float((uint32_t)(e + 127) << 23);
+    if (t == 0) *scl = __uint_as_float((uint32_t)(e + 127) << 23);
 }
 
 // Work-list upload: the workgroups read the host-built plan straight out of pinned host memory
@@ -1903,14 +1918,29 @@ static hipError_t for_pages(AppendParams& p, int64_t pages, F&& f) {
     return hipGetLastError();
 }
 
+// Waves share units as long as there is no more than one unit per SIMD (4 x 256).  us a launch, one wave a unit -> shared, at 4-127,
+// 256-511, 1 024-2 047 and 2 048-4 095 units, d = 128: pages of 64 tokens 4.5 -> 3.4, 5.2 -> 4.2, 7.2 -> 6.8, 12.2 -> 13.0; of 32
+// 3.7 -> 3.1, 4.0 -> 3.4, 5.0 -> 4.9, 6.9 -> 8.0; of 16 3.4 -> 3.0, 3.6 -> 3.2, 4.2 -> 4.5, 6.1 -> 7.4.
+template <int D, int P>
+static hipError_t launch_append_fp8(AppendParams& p, int64_t pages, hipStream_t st) {
+    constexpr int SHARE = std::min(WG / 64, P * D / 512);    // waves that share a unit in small launches: a chunk per lane at least
+    const int units = 2 * p.Hkv;
+    if (pages * units <= 4 * 256)
+        return for_pages(p, pages, [&](unsigned nx) {
+            hipLaunchKernelGGL((append_fp8_kernel<D, P, SHARE>), dim3(nx, units * SHARE / 4), dim3(WG), 0, st, p);
+        });
+    const int waves = std::min(WG / 64, units);
+    return for_pages(p, pages, [&](unsigned nx) {
+        hipLaunchKernelGGL((append_fp8_kernel<D, P, 1>), dim3(nx, (units + waves - 1) / waves), dim3(64 * waves), 0, st, p);
+    });
+}
+
 hipError_t launch_append(AppendParams& p, int kvt, int64_t pages, hipStream_t st) {
     if (kvt == KV_BF16)
         return for_pages(p, pages, [&](unsigned nx) { hipLaunchKernelGGL(kv_move_bf16_kernel<false>, dim3(nx, 2), dim3(WG), 0, st, p); });
-    void (*kern)(AppendParams) = nullptr;
-    if (p.D == 128) kern = p.P == 16 ? append_fp8_kernel<128, 16> : p.P == 32 ? append_fp8_kernel<128, 32> : append_fp8_kernel<128, 64>;
-    else kern = p.P == 16 ? append_fp8_kernel<64, 16> : p.P == 32 ? append_fp8_kernel<64, 32> : append_fp8_kernel<64, 64>;
-    const int waves = std::min(WG / 64, 2 * p.Hkv);
-    return for_pages(p, pages, [&](unsigned nx) { hipLaunchKernelGGL(kern, dim3(nx, (2 * p.Hkv + waves - 1) / waves), dim3(64 * waves), 0, st, p); });
+    if (p.D == 128)
+        return p.P == 16 ? launch_append_fp8<128, 16>(p, pages, st) : p.P == 32 ? launch_append_fp8<128, 32>(p, pages, st) : launch_append_fp8<128, 64>(p, pages, st);
+    return p.P == 16 ? launch_append_fp8<64, 16>(p, pages, st) : p.P == 32 ? launch_append_fp8<64, 32>(p, pages, st) : launch_append_fp8<64, 64>(p, pages, st);
 }
 
 hipError_t launch_kv_move(AppendParams& p, bool pack, int64_t pages, hipStream_t st) {

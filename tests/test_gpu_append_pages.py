@@ -54,3 +54,36 @@ def test_append_pack_unpack_rows_and_pages(n, Hkv, d, P):
                 oracle.fp8_append_reference(pools[i], scales[i], b.block_table, c0, l0, from_dev_bits(x[i].contiguous()), P, in_place=True)
     for got, want in zip((dk, dv, ds, dt), pools + scales):
         assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,Hkv,units", [(7, 3, 66), (40, 8, 1024), (42, 8, 1056)])
+@pytest.mark.parametrize("P", [16, 32, 64])
+@pytest.mark.parametrize("d", [64, 128])
+def test_8bit_append_by_one_wave_or_several_a_page(d, P, n, Hkv, units):
+    """8-bit append of a launch with few (page, head, K or V) units, which several waves share (up to 1 024), and with more, one
+    wave each: pages with one new token, some, all; exponents that stay and that rise; codes and scales bit for bit."""
+    print("case:", d, P, units, flush=True)
+    g = np.random.default_rng(d + P + n)
+    C = np.array([0, 1, P - 1, P, P + P // 2, 3 * P - 1, 2 * P] * 6, np.int32)[:n]
+    L = np.array([1, P, 2, 2 * P + 3, P // 2, 1, P // 2 + 1] * 6, np.int32)[:n]
+    assert units == 2 * Hkv * int(((C + L - 1) // P - C // P + 1).sum())
+    pages = -(-(C + L) // P)
+    perm = g.permutation(int(pages.sum()) + 3).astype(np.int32)
+    bt = np.full((n, int(pages.max())), -1, np.int32)
+    o = 0
+    for r in range(n):
+        bt[r, :pages[r]] = perm[o:o + pages[r]]
+        o += pages[r]
+    pools = [np.full((len(perm), Hkv, P, d), 0x7F, np.uint8) for _ in range(2)]
+    scales = [np.full((len(perm), Hkv), np.nan, np.float32) for _ in range(2)]
+    dk, dv, ds, dt = (torch.from_numpy(a.copy()).cuda() for a in pools + scales)
+    cache = A.KVCache(Hkv, Hkv, d, P, dk, dv, 1.0, ds, dt, A.binding.AMPD_KV_FP8_E4M3)
+    d_bt = torch.from_numpy(bt).cuda()
+    for c0, l0 in ((np.zeros(n, np.int32), C), (C, L)):
+        mag = np.exp2(g.integers(-6, 7, size=(2, int(l0.sum()), Hkv, 1)))
+        x = torch.from_numpy((g.standard_normal((2, int(l0.sum()), Hkv, d)) * mag).astype(np.float32)).cuda().bfloat16()
+        A.kv_append(cache, c0, l0, d_bt, x[0].contiguous(), x[1].contiguous())
+        for i in range(2):
+            oracle.fp8_append_reference(pools[i], scales[i], bt, c0, l0, from_dev_bits(x[i].contiguous()), P, in_place=True)
+    for got, want in zip((dk, dv, ds, dt), pools + scales):
+        assert np.array_equal(got.cpu().numpy().view(np.uint8), want.view(np.uint8))
