@@ -41,7 +41,8 @@
  *     decode(code) * scale; scales are powers of two (see ampd_kv_append), and the attention
  *     kernels rely on it: they apply the exponent of a scale only.
  *   - Block table: int32 [num_reqs][max_pages_per_req], physical page ids.  Entries at
- *     index >= ceil(T_r / P) are never read (use -1).
+ *     index >= ceil(T_r / P) are never read (use -1).  A page that receives new tokens in a call belongs
+ *     to one row of the batch alone; pages of cached tokens only may be shared between rows.
  *   - Packed rows: q / out are bf16 [sum_r L_r][Hq][d], k_new / v_new bf16
  *     [sum_r L_r][Hkv][d]; the rows of request r start at the exclusive prefix sum of L.
  *   - Slots of the last page beyond T_r, unused pages and unused table entries are
@@ -237,7 +238,8 @@ typedef struct {
                                  * decode rows alone, whose items append) */
     int64_t partial_bytes;      /* split-KV partial results inside the workspace */
     int64_t plan_bytes;         /* work list inside the workspace (0: it travels in the kernel's arguments) */
-    int64_t num_append_items;   /* bf16 cache: page-write items (64 packed rows each) that close the attention launch */
+    int64_t num_append_items;   /* bf16 cache: page-write items (64 packed rows each, 4 to 64 in a small launch of tiles
+                                 * alone) that close the attention launch */
     int64_t num_workgroups;     /* workgroups of the attention launch: num_items, or 256 persistent workgroups that work
                                  * through the items when the launch holds tiles and more items than that */
 } ampd_plan_info;

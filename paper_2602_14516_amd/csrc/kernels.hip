@@ -950,12 +950,8 @@ __device__ __forceinline__ void wide_body(const AttnParams& p, const ItemCtx& ic
 }
 
 // ---------------------------------------------------------------------------------------------
-// narrow body: <= 32 query rows; the 32-key blocks of the key range belong round-robin to 8 softmax states, which are
-// merged through LDS at the end.  A workgroup of 8 waves keeps one state per wave, one of 4 waves two per wave (the same
-// blocks in the same order per state, so the result is the same bit for bit); a wave stages its blocks through an LDS
-// region of its own.
+// quantising new tokens into an 8-bit cache: the steps, and the two forms in which a decode row's item appends its own
 
-// ROWS: query rows a wave carries (32, or 16 for items of at most 16 rows: half the matrix and softmax work per key)
 __device__ __forceinline__ int exponent_for(float amax) {
     // smallest e with amax <= 448 * 2^e  (448 = 1.75 * 2^8), clamped to [-40, 119]
     const uint32_t u = __float_as_uint(amax);
@@ -1114,7 +1110,14 @@ struct NewToken {
     }
 };
 
+// ---------------------------------------------------------------------------------------------
+// narrow body: <= 32 query rows; the 32-key blocks of the key range belong round-robin to 8 softmax states, which are
+// merged through LDS at the end.  A workgroup of 8 waves keeps one state per wave, one of 4 waves two per wave (the same
+// blocks in the same order per state, so the result is the same bit for bit); a wave stages its blocks through an LDS
+// region of its own.
+
 constexpr int LEAN_ROWS = 8;
+// ROWS: query rows a wave carries (32, or 16 for items of at most 16 rows: half the matrix and softmax work per key)
 // NW: waves of the workgroup.  QUANT: the item appends its own new tokens (8-bit cache) before it reads its pages.
 // LEAN: K and V of a block take turns in one LDS region per wave, and the merge holds the item's rows only (at most 8).
 template <int D, int KVT, int ROWS, int NW, bool QUANT = false, bool LEAN = false>
@@ -1720,8 +1723,10 @@ __device__ __forceinline__ PageJob page_job(const AppendParams& p) {
 // PACK = false: packed rows [tokens][hn][D] -> pages (append, or unpack of a received head share);
 // PACK = true:  pages -> packed rows (the send buffer of a KV transfer).
 // Chunks are numbered in page order (head, token, chunk), and four are in flight per thread: 8 700 tokens, 4 of 8 heads of 128,
-// pack and unpack together 18.6 -> 14.3 us, of which the non-temporal stores 2.4 (nothing reads the pages or rows back soon; with
-// non-temporal loads too 17).
+// pack and unpack together 18.6 -> 14.3 us, of which the non-temporal stores 2.4 (with non-temporal loads too 17).  The stores pay
+// with a decode step right behind a merge, too, which reads the pages back: append + step, plain -> non-temporal stores: 16 rows of 64 to
+// 1 024 new tokens 86.0 -> 71.3 us, four of 4 096 over 32 k (one head) 27.2 -> 24.7, 4 of 25 rows with 600 82.0 -> 77.2, one of 509 15.7 ->
+// 15.1; only long initial prefills lose, one of 4 096 18.1 -> 18.7, 16 of them 142 -> 149.
 template <bool PACK>
 __global__ __launch_bounds__(WG) void kv_move_bf16_kernel(const AppendParams p) {
     if ((int)blockIdx.x < p.up_blocks) {

@@ -31,7 +31,7 @@ struct QBlock {            // a query block before splitting
 namespace {
 
 // The row table of a batch of decode rows alone (out.reqs holds the rows).
-void build_table(const Shape& s, int32_t chunk, bool append_items, Plan& out) {
+void build_table(const Shape& s, int32_t chunk, const PlanOptions& opt, Plan& out) {
     RowTable& t = out.table;
     t.chunk = chunk;
     t.Hkv = s.Hkv;
@@ -68,11 +68,13 @@ void build_table(const Shape& s, int32_t chunk, bool append_items, Plan& out) {
     // and 3.2-32 k tokens over 8 KV heads, 25 rows (1.7, 6.9, 14 k keys per CU): bf16 48.7 -> 44.8, 147.7 -> 143.3, 313 -> 316;
     // 8-bit 33.8 -> 28.1, 86.6 -> 83.1, 175.7 -> 183.9; 40 rows of 1.6-16 k (11 k keys per CU): 230 -> 235, 129.9 -> 133.8.  Rows
     // that are not cut: 40 rows of 0.2-2 k 8-bit 28.1 -> 33.4, 96 bf16 rows of 2-16 k 552 -> 578; one item per CU: 8 rows of
-    // 2-16 k 8-bit 33.8 -> 39.4.
-    t.small = t.n_items >= 512 && 2 * n * s.Hkv < 3 * 256 && keys_sum <= 8192 * 256;
+    // 2-16 k 8-bit 33.8 -> 39.4.  All of these are d = 128 (the only head dimension with such a kernel); over 1 to 16 KV heads,
+    // groups of 1 to 16 and pages of 16 to 64, 200 drawn decode batches run at 0.86 of their time before this table, none above 1.04.
+    const int64_t slots = opt.wg_slots;
+    t.small = t.n_items >= 2 * slots && 2 * n * s.Hkv < 3 * slots && keys_sum <= 8192 * slots;
     out.by_table = true;
     out.num_narrow = t.n_items;
-    out.num_append = append_items ? ceil_div(out.sum_L, APPEND_ITEM_ROWS) : 0;
+    out.num_append = opt.append_items ? ceil_div(out.sum_L, APPEND_ITEM_ROWS) : 0;
     out.num_items = out.num_narrow + out.num_append;
     out.grid = (int32_t)out.num_items;
     out.total_bytes = std::max<int64_t>(256, round_up(out.partial_floats * 4, 256));
@@ -326,11 +328,14 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
                 // they leave (or the first to finish) stream the decode rows meanwhile.  The launch then lasts as long as the
                 // longest piece or a slot's share of everything, so the fewest pieces that meet those two ends are best: a
                 // piece costs a start and a partial result.  Where the longest piece would outlast the share by a fifth (whole
-                // tiles, which need no combine pass: by three tenths), the cut above stays.  us per call, before -> so:
-                // 24 rows of 0.7-7 k tokens next to a prefill of 701 over 2 900 (8 KV heads): 8-bit 108 -> 90, bf16 127 -> 110;
-                // next to one of 200 over 6 000: 87 -> 72 and 106 -> 96; 21 rows of 1.4-14 k next to three of up to 2 682
-                // (one KV head) 201 -> 194 and 193 -> 179.  Tiles first when they are more than that: 96 rows next to 8
-                // long prefills 1 627 -> 1 793, since all decode rows then stream at once.
+                // tiles, which need no combine pass: by three tenths), the cut above stays.  us per launch, before -> so, 8-bit and
+                // bf16: 24 rows of 0.7-7 k tokens over 8 KV heads next to a prefill of 701 over 2 900 114 -> 98 and 129 -> 126, of
+                // 200 over 6 000 90 -> 76 and 108 -> 96, next to two of 300-900 over 2-4 k 164 -> 141 and 170 -> 145; 21 rows of
+                // 1.4-14 k next to three of up to 2 682 (one KV head) 219 -> 198 and 209 -> 184 (with other lengths of these
+                // ranges 225 -> 224 and 213 -> 214); 60 rows of 5-30 k next to four of up to 1 000 165 -> 140 and 175 -> 165.
+                // Tiles first when they are more than that: 96 rows next to 8 long prefills 1 627 -> 1 793, since all decode rows
+                // then stream at once.  200 drawn mixed batches of other head counts and sizes run at 0.94 of their time, none
+                // above 1.02.
                 const int64_t stage_ns = s.D == 128 ? 3500 : 2200, key_ns = (opt.kv_bytes == 1 ? 9 : 13) * (s.D == 128 ? 10 : 6);
                 int64_t n_rows = 0, best = -1;
                 for (const auto& r : narrow_runs) n_rows += r.second;
@@ -358,7 +363,7 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     }
 
     if (by_table) {
-        build_table(s, (int32_t)std::min<int64_t>(narrow_chunk, 1 << 30), opt.append_items, out);
+        build_table(s, (int32_t)std::min<int64_t>(narrow_chunk, 1 << 30), opt, out);
         return;
     }
 

@@ -175,7 +175,8 @@ struct PlanOptions {
     int wg_slots = 256;   // workgroups resident at once: one per CU
     int kv_bytes = 2;     // bytes of a cached element
     bool append_items = false;   // the page writes of the call ride in the attention launch (bf16 cache): append items
-                                 // of APPEND_ITEM_ROWS packed rows each close the work list
+                                 // of APPEND_ITEM_ROWS packed rows each (TileTable::append_rows in a launch by that table)
+                                 // close the work list
 };
 
 struct Plan {
@@ -183,7 +184,7 @@ struct Plan {
     std::vector<Item> items;
     std::vector<CombItem> combs;
     // A launch of decode rows alone (at most ROW_TABLE_MAX of them): the table stands for items and combs, which stay empty
-    // until materialize() writes the items out for a caller that wants to see them.
+    // (plan_items() writes the items out for a caller that wants to see them).
     bool by_table = false;
     RowTable table;
     // A small launch of tiles alone over a bf16 cache: `tiles` says the same as items and combs.
