@@ -25,3 +25,12 @@ def test_attention_kernels_keep_two_waves_per_simd_and_fit_the_lds(resources):
     for name, r in attn.items():
         assert r["Occupancy [waves/SIMD]"] >= 2, (name, r)    # 8 waves of one workgroup on 4 SIMDs
         assert r["LDS Size [bytes/block]"] <= 160 * 1024, (name, r)
+
+
+def test_small_decode_workgroups_fit_a_cu_side_by_side(resources):
+    """The 4-wave decode kernels (one wave per SIMD and workgroup) are for hiding an item's latencies behind its neighbours':
+    two of them to a CU over a bf16 cache, three over an 8-bit one."""
+    for kv, at_once in ((0, 2), (1, 3)):
+        (r,) = [r for n, r in resources.items() if f"decode_rows_kernelILi128ELi{kv}ELi4E" in n]
+        assert r["Occupancy [waves/SIMD]"] >= at_once, r
+        assert at_once * r["LDS Size [bytes/block]"] <= 160 * 1024, r
