@@ -196,7 +196,7 @@ def trace_replay(torch, A, W, max_ticks=None):
             "pool_pages": tr.num_pages, "kv_dtype": "fp8-e4m3 + fp32 scale per (page, head)",
             "wall_s": wall, "host_enqueue_s": enq, "stream_span_s": gpu, "algorithmic_TFLOP": flops / 1e12, "algorithmic_GB": by / 1e9,
             "TFLOPs": flops / wall / 1e12, "GBps": by / wall / 1e9, "calls_per_s": len(ticks) / wall,
-            "note": "one Python-driven C-ABI call per tick (plan, quantising append carrying the work list, attention, combine); the ticks are small, so the host call path and the launches are of the same order"}
+            "note": "one Python-driven C-ABI call per tick (plan; decode ticks: attention with the append inside, combine; ticks with a prefill: quantising append carrying the work list, attention, combine); the ticks are small, so the host call path and the launches are of the same order"}
 
 
 def data_dependence(torch, A, W, steps=100, warmup=20):

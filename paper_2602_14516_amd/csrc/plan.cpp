@@ -69,7 +69,7 @@ void build_table(const Shape& s, int32_t chunk, const PlanOptions& opt, Plan& ou
     // 8-bit 33.8 -> 28.1, 86.6 -> 83.1, 175.7 -> 183.9; 40 rows of 1.6-16 k (11 k keys per CU): 230 -> 235, 129.9 -> 133.8.  Rows
     // that are not cut: 40 rows of 0.2-2 k 8-bit 28.1 -> 33.4, 96 bf16 rows of 2-16 k 552 -> 578; one item per CU: 8 rows of
     // 2-16 k 8-bit 33.8 -> 39.4.  All of these are d = 128 (the only head dimension with such a kernel); over 1 to 16 KV heads,
-    // groups of 1 to 16 and pages of 16 to 64, 200 drawn decode batches run at 0.86 of their time before this table, none above 1.04.
+    // groups of 1 to 16 and pages of 16 to 64, 200 drawn decode batches run at 0.86 of their time before this table, the worst at 1.04.
     const int64_t slots = opt.wg_slots;
     t.small = t.n_items >= 2 * slots && 2 * n * s.Hkv < 3 * slots && keys_sum <= 8192 * slots;
     out.by_table = true;
