@@ -1461,11 +1461,20 @@ __global__ __launch_bounds__(AWG, 1) void attn_kernel(const AttnParams p) {
     }
 }
 
+template <int D, int NW, bool LEAN>
+constexpr int rows_smem() {
+    constexpr int kv = NW * (LEAN ? 1 : 2) * Geo<D>::B32;
+    constexpr int merge = ATTN_WAVES * (LEAN ? LEAN_ROWS : NW == ATTN_WAVES ? 32 : 16) * ((D + 4) * 4 + 8);
+    return kv > merge ? kv : merge;
+}
+
 // A small launch of tiles alone over a bf16 cache, whose list travels in the arguments (see TileTable): one workgroup per tile or
-// piece, then the append items.
-template <int D>
-__global__ __launch_bounds__(AWG, 1) void attn_tiles_kernel(const AttnParams p, const TileTable t) {
-    __shared__ __attribute__((aligned(16))) char smem_raw[Geo<D>::SMEM];
+// piece, then the append items.  KIND_NARROW: blocks of at most 32 query rows instead of tiles of 256 (see take_blocks for where).  Bound there:
+// the chain item -> page ids -> keys, whose latency eight waves with a block of 32 keys each pass once per 256 keys, where a tile's
+// stage of 128 waits for its own loads (one row of 32 tokens over 256, d = 64: 7.9 -> 6.8 us; of 64 over 1 024, 8 KV heads of 128: 22.6 -> 14.6).
+template <int D, int KIND>
+__global__ __launch_bounds__(AWG, KIND == KIND_NARROW && D == 64 ? 4 : 1) void attn_tiles_kernel(const AttnParams p, const TileTable t) {
+    __shared__ __attribute__((aligned(16))) char smem_raw[KIND == KIND_NARROW ? rows_smem<D, ATTN_WAVES, false>() : Geo<D>::SMEM];
     const uint32_t smem = (uint32_t)(uintptr_t)LDS_PTR(char, smem_raw);
     const int idx = blockIdx.x, tid = threadIdx.x;
     if (idx >= t.n_items) {
@@ -1475,7 +1484,13 @@ __global__ __launch_bounds__(AWG, 1) void attn_tiles_kernel(const AttnParams p, 
     }
     const uint32_t code = t.items[idx];
     if (code == TILE_NULL) return;                           // a filler that keeps the following items on their XCD
-    wide_body<D, KV_BF16>(p, item_ctx<KV_BF16>(p, tile_item(t, code)), smem, tid);
+    const ItemCtx ic = item_ctx<KV_BF16>(p, tile_item(t, code));
+    if constexpr (KIND == KIND_WIDE)
+        wide_body<D, KV_BF16>(p, ic, smem, tid);
+    else if (ic.nq * ic.gn <= 16)
+        narrow_body<D, KV_BF16, 16, ATTN_WAVES>(p, ic, smem, tid);
+    else
+        narrow_body<D, KV_BF16, 32, ATTN_WAVES>(p, ic, smem, tid);
 }
 
 // The launch of a batch of decode rows alone whose work list travels in the arguments (see RowTable): one workgroup of NW
@@ -1515,12 +1530,6 @@ __device__ __forceinline__ void append_table_rows(const AttnParams& p, const Row
     });
 }
 
-template <int D, int NW, bool LEAN>
-constexpr int rows_smem() {
-    constexpr int kv = NW * (LEAN ? 1 : 2) * Geo<D>::B32;
-    constexpr int merge = ATTN_WAVES * (LEAN ? LEAN_ROWS : NW == ATTN_WAVES ? 32 : 16) * ((D + 4) * 4 + 8);
-    return kv > merge ? kv : merge;
-}
 template <int D, int KVT, int NW>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : NW < ATTN_WAVES && KVT == KV_FP8 ? 3 : 2) void decode_rows_kernel(const AttnParams p, const RowTable t) {
     constexpr bool LEAN = NW < ATTN_WAVES && KVT == KV_FP8;
@@ -1878,8 +1887,9 @@ hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid
 }
 
 hipError_t launch_tiles(const AttnParams& p, const TileTable& t, int grid, hipStream_t st) {
-    if (t.D == 128) hipLaunchKernelGGL((attn_tiles_kernel<128>), dim3(grid), dim3(AWG), 0, st, p, t);
-    else hipLaunchKernelGGL((attn_tiles_kernel<64>), dim3(grid), dim3(AWG), 0, st, p, t);
+    auto kern = t.kind == KIND_NARROW ? (t.D == 128 ? attn_tiles_kernel<128, KIND_NARROW> : attn_tiles_kernel<64, KIND_NARROW>)
+                                      : (t.D == 128 ? attn_tiles_kernel<128, KIND_WIDE> : attn_tiles_kernel<64, KIND_WIDE>);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(AWG), 0, st, p, t);
     return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 #include "plan.h"
 
 #include <algorithm>
+#include <array>
 #include <utility>
 
 namespace ampd {
@@ -29,6 +30,133 @@ struct QBlock {            // a query block before splitting
 }  // namespace
 
 namespace {
+
+// Whether a small launch with prefill rows goes as blocks of at most 32 query rows throughout (narrow items, whose 8 waves share
+// the keys) instead of tiles of 256, and the chunk that their key ranges are cut to.
+// Blocks are eight times as many workgroups, each of them 256 keys further in 1.75 us where a tile takes 3 us for 128: while they fit
+// one round of the CUs they take half of the tiles' time, and shorter ranges need no cut and no combine pass; but eight of them read
+// the keys that one tile reads, and together they do only a third of its work per time.  Both ways are priced in ns, from launches of
+// 1 and 4 rows of 16 to 512 new tokens over 0 to 16 k, five head geometries and both caches (us, tiles -> blocks, 8-bit and bf16: 32 tokens
+// over 256, 8 heads of 64 15.9 -> 12.6 and 11.0 -> 9.8; 64 over 1 024, 8 KV heads, groups of 4 27.0 -> 17.7 and 22.6 -> 14.6; 256 over
+// 2 048, the same 39.6 -> 28.8 and 34.2 -> 25.8; four times 64 over 4 096 46.7 -> 42.9 and 42.8 -> 42.7, 16 k 82 -> 133 and 88 -> 170; 512
+// over 1 024 44.1 -> 37.3 and, with more items than the table in the arguments holds, 38.4 -> 43.0).
+bool take_blocks(const Shape& s, const std::vector<ReqInfo>& reqs, const PlanOptions& opt, int64_t* chunk_out) {
+    const int tq = 32 / (s.Hq / s.Hkv), tile = ATTN_WAVES * tq;
+    const bool d64 = s.D == 64, fp8 = opt.kv_bytes == 1;
+    const int64_t slots = opt.wg_slots;
+    struct Run { int32_t keys; int64_t n; };                   // n blocks or tiles of about that many keys
+    std::vector<Run> runs, few, full, half;                    // few: rows that are one block either way, cut by the rule for decode
+    int64_t n_blocks = 0, longest_full = 0, longest_half = 0;  // rows; half: tiles of at most 128 query rows, half the work a stage
+    for (const ReqInfo& r : reqs) {
+        if (r.L <= 0) continue;
+        const int64_t nb = ceil_div(r.L, tq) * s.Hkv, nt = ceil_div(r.L, tile);
+        n_blocks += nb;
+        if (n_blocks > (fp8 ? 2 : 1) * slots) return false;
+        (r.L <= tq ? few : runs).push_back(Run{r.C + r.L, nb});
+        if (r.L <= tq) continue;
+        const bool last_half = 2 * (r.L - (nt - 1) * tile) <= tile;
+        if (nt > last_half) {
+            full.push_back(Run{r.C + r.L, (nt - last_half) * s.Hkv});
+            longest_full = std::max<int64_t>(longest_full, r.C + r.L);
+        }
+        if (last_half) {
+            half.push_back(Run{nt > 1 ? r.C + r.L % tile : r.C + r.L, s.Hkv});
+            longest_half = std::max<int64_t>(longest_half, half.back().keys);
+        }
+    }
+    if (full.empty() && half.empty()) return false;
+    auto pieces = [](const std::vector<Run>& v, int64_t chunk) {
+        int64_t n = 0;
+        for (const Run& r : v) n += ceil_div(r.keys, chunk) * r.n;
+        return n;
+    };
+    // blocks: rounds of 256 keys, whole or in pieces that fit one round (and the table); the pieces of a row's blocks read its
+    // keys from the memory-side cache, at 8 TB/s
+    const int64_t round_ns = d64 ? 1030 : 1750;
+    auto price = [&](const std::vector<Run>& v, int64_t* chunk) {
+        int64_t blocks = 0, longest = 0, bytes = 0, best = -1;
+        for (const Run& r : v) {
+            blocks += r.n;
+            longest = std::max<int64_t>(longest, r.keys);
+            bytes += r.keys * r.n * 2 * s.D * opt.kv_bytes;
+        }
+        for (int64_t rounds = 1;; rounds += 1 + rounds / 8) {
+            const bool whole = 256 * rounds >= longest;
+            const int64_t n = whole ? blocks : pieces(v, 256 * rounds);
+            if (whole || (n <= slots && blocks <= TILE_TABLE_COMBS)) {
+                const int64_t one = std::min(rounds, ceil_div(longest, 256)) * round_ns;
+                const int64_t all = n > slots ? pieces(v, 256) * round_ns * 11 / (10 * slots) + 1000 : 0;     // (several rounds end unevenly)
+                const int64_t cost = (d64 ? 4700 : 6500) + n * 5 + (whole ? std::max(one, all) : std::max(one, bytes / 8000) + 4000 + n * 8);
+                if (best < 0 || cost < best) {
+                    best = cost;
+                    *chunk = whole ? 1 << 30 : 256 * rounds;
+                }
+            }
+            if (whole) return best;
+        }
+    };
+    int64_t best = price(runs, chunk_out);
+    // tiles: stages of 128 keys, whole or in pieces of four stages or more that fit one round
+    int64_t best_tiles = -1;
+    for (int64_t stages = 4;; stages += 1 + stages / 8) {
+        const int64_t chunk = WIDE_STAGE_KEYS * stages;
+        const bool whole = chunk >= std::max(longest_full, longest_half);
+        const int64_t nf = pieces(full, chunk), nh = pieces(half, chunk);
+        if (whole || nf + nh <= slots) {
+            const int64_t full_ns = (d64 ? 1950 : 3000) + (2 * nf + nh) * (d64 ? 50 : 200) / slots, half_ns = d64 ? 1050 : 1650;
+            const int64_t work = std::max(std::min(stages, ceil_div(longest_full, WIDE_STAGE_KEYS)) * full_ns,
+                                          std::min(stages, ceil_div(longest_half, WIDE_STAGE_KEYS)) * half_ns);
+            const int64_t cost = (d64 ? 5200 : 6600) + work * (fp8 ? 23 : 20) / 20 + (fp8 ? 1200 : 0) + (whole ? 0 : 4000 + (2 * nf + nh) * (d64 ? 12 : 22));
+            if (best_tiles < 0 || cost < best_tiles) best_tiles = cost;
+        }
+        if (whole) break;
+    }
+    if (!few.empty()) {
+        // Next to decode rows: only where the tiles last longer than those would alone (otherwise the launch is a matter of cutting
+        // the decode rows well: 76 rows of 2.5-6 k tokens next to two of up to 30 34.5 -> 43.6); tiles would need a list in the
+        // workspace there (bf16: an upload launch).
+        int64_t chunk;
+        const int64_t others = price(few, &chunk);
+        if (others > best_tiles) return false;
+        best = std::max(std::max(best, others), (d64 ? 4700 : 6500) + (pieces(runs, 256) + pieces(few, 256)) * round_ns * 11 / (10 * slots) + 1000);
+        best_tiles += fp8 ? 0 : 4000;
+    }
+    return 100 * best <= 97 * best_tiles;
+}
+
+// The launch order of blocks that fit one round: the eight that would make one tile read the same keys at the same rate, so they go
+// next to each other on one die, as tiles of one stream do; -1 pads the shorter dies' queues.  False when a die would get more of them
+// than it has slots.
+bool order_blocks(const std::vector<Item>& items, int G, int64_t slots, std::vector<int32_t>& ix) {
+    const int tile = ATTN_WAVES * (32 / G);
+    if ((int64_t)items.size() > slots) return false;
+    std::vector<std::pair<std::array<int32_t, 4>, int32_t>> by_key;    // (row, KV head, piece, tile): items of one group
+    for (size_t i = 0; i < items.size(); ++i) {
+        const Item& it = items[i];
+        by_key.push_back({{it.req, it.heads & 0xff, it.kv_begin, it.q0 / tile}, (int32_t)i});
+    }
+    std::stable_sort(by_key.begin(), by_key.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
+    std::vector<std::vector<int32_t>> groups;
+    for (size_t i = 0; i < by_key.size(); ++i) {
+        if (i == 0 || by_key[i].first != by_key[i - 1].first) groups.emplace_back();
+        groups.back().push_back(by_key[i].second);
+    }
+    std::stable_sort(groups.begin(), groups.end(), [](const auto& a, const auto& b) { return a.size() > b.size(); });
+    std::vector<int32_t> queue[NUM_XCD];
+    size_t longest = 0;
+    for (const auto& g : groups) {
+        int best = 0;
+        for (int x = 1; x < NUM_XCD; ++x)
+            if (queue[x].size() < queue[best].size()) best = x;
+        queue[best].insert(queue[best].end(), g.begin(), g.end());
+        longest = std::max(longest, queue[best].size());
+    }
+    if ((int64_t)longest > slots / NUM_XCD) return false;
+    for (size_t j = 0; j < longest; ++j)
+        for (int x = 0; x < NUM_XCD; ++x) ix.push_back(j < queue[x].size() ? queue[x][j] : -1);
+    while (!ix.empty() && ix.back() < 0) ix.pop_back();
+    return true;
+}
 
 // The row table of a batch of decode rows alone (out.reqs holds the rows).
 void build_table(const Shape& s, int32_t chunk, const PlanOptions& opt, Plan& out) {
@@ -94,15 +222,17 @@ void add_append_items(const Plan& plan, int rows, std::vector<Item>& items) {
 
 // The tile table of a plan of uncut or evenly cut tiles (out.items without append items, out.combs in the order of their
 // partial results); false when it does not fit.
-bool build_tiles(const Shape& s, int32_t chunk, Plan& out) {
+bool build_tiles(const Shape& s, int32_t chunk, int32_t few_chunk, bool blocks, Plan& out) {
     TileTable& t = out.tiles;
     const int G = s.Hq / s.Hkv;
-    if (out.num_wide == 0 || out.num_narrow > 0 || G > 32 || s.Hkv > 64 || out.items.size() > (size_t)TILE_TABLE_ITEMS ||
+    if ((blocks ? out.num_wide : out.num_narrow) > 0 || G > 32 || s.Hkv > 64 || out.items.size() > (size_t)TILE_TABLE_ITEMS ||
         out.combs.size() > (size_t)TILE_TABLE_COMBS)
         return false;
     t.n_rows = 0;
     t.chunk = chunk;
-    t.tq = ATTN_WAVES * (32 / G);
+    t.few_chunk = few_chunk;
+    t.tq = (blocks ? 1 : ATTN_WAVES) * (32 / G);
+    t.kind = blocks ? KIND_NARROW : KIND_WIDE;
     t.G = G;
     t.D = s.D;
     t.sum_L = (int32_t)out.sum_L;
@@ -116,9 +246,11 @@ bool build_tiles(const Shape& s, int32_t chunk, Plan& out) {
         row_of[r.req] = t.n_rows;
         t.rows[t.n_rows++] = r;
     }
+    bool fits = true;                      // (a row of more than 256 tiles, a tile of more than 128 pieces: no)
     auto code_of = [&](int32_t req, int32_t heads, int32_t q0, int32_t nq, int32_t kv_begin) {
         const uint32_t tile = q0 == 0 ? 0 : (uint32_t)((q0 + nq + t.tq - 1) / t.tq - 1);   // (the first tile holds the remainder)
-        return (uint32_t)row_of[req] | (uint32_t)(heads & 0xff) << 4 | tile << 10 | (uint32_t)(kv_begin / chunk) << 18;
+        if (tile > 255) fits = false;
+        return (uint32_t)row_of[req] | (uint32_t)(heads & 0xff) << 4 | tile << 10 | (uint32_t)(kv_begin / tile_chunk(t, out.reqs[req].L)) << 18;
     };
     t.n_combs = (int32_t)out.combs.size();
     for (int i = 0; i < t.n_combs; ++i) {
@@ -139,7 +271,7 @@ bool build_tiles(const Shape& s, int32_t chunk, Plan& out) {
         }
         t.items[i] = code;
     }
-    return true;
+    return fits;
 }
 
 }  // namespace
@@ -185,6 +317,8 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     by_table = by_table && active > 0 && active <= ROW_TABLE_MAX;
 
     // 1. query blocks
+    int64_t block_chunk = 1 << 30;
+    const bool blocks = !by_table && opt.force_kv_splits <= 0 && nhb == 1 && take_blocks(s, out.reqs, opt, &block_chunk);
     std::vector<QBlock> qb;
     int64_t narrow_keys = 0;
     int64_t n_wide = 0;
@@ -217,11 +351,13 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
                 } else {
                     // A tile that is not full costs its workgroup nearly as much per key as a full one, so the
                     // remainder of the row goes into the FIRST tile, which sees the fewest keys.
-                    const int tq = ATTN_WAVES * tq_wave;
+                    const int kind = blocks ? KIND_NARROW : KIND_WIDE;
+                    const int tq = blocks ? tq_wave : ATTN_WAVES * tq_wave;
                     const int first = L % tq ? L % tq : tq;
                     for (int q0 = 0; q0 < L; q0 += q0 ? tq : first) {
                         const int nq = q0 ? tq : first;
-                        qb.push_back(QBlock{r, pack_heads(kvh, g0, gn, KIND_WIDE), q0, nq, C + q0 + nq, nq * gn, KIND_WIDE});
+                        qb.push_back(QBlock{r, pack_heads(kvh, g0, gn, kind), q0, nq, C + q0 + nq, nq * gn, kind});
+                        if (blocks) continue;
                         ++n_wide;
                         if (kvh == 0) note(wide_runs, C + q0 + nq);
                     }
@@ -375,7 +511,7 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
         if (opt.force_kv_splits > 0)
             chunk = std::max<int64_t>(KV_TILE, round_up(ceil_div(b.nkeys, opt.force_kv_splits), KV_TILE));
         else
-            chunk = b.kind == KIND_WIDE ? wide_chunk : narrow_chunk;
+            chunk = b.kind == KIND_WIDE ? wide_chunk : blocks && out.reqs[b.req].L > 32 / G ? block_chunk : narrow_chunk;
         const int nsplit = (int)ceil_div(b.nkeys, chunk);
         const int32_t slot = b.rows * (s.D + 2);                // floats per partial slot
         int64_t part0 = -1;
@@ -423,7 +559,9 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     //    Everything is stable and depends on the lengths only.
     std::vector<int32_t> wide_ix, narrow_ix;
     double wide_cost = 0, narrow_cost = 0;
-    {
+    if (blocks && order_blocks(out.items, G, opt.wg_slots, wide_ix)) {
+        // (blocks that would make one tile, next to each other on one die)
+    } else {
         std::vector<Cost> nar;
         struct Stream { int64_t cost = 0; int64_t max_keys = 0; std::vector<Cost> items; };
         std::vector<Stream> streams;
@@ -574,7 +712,8 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     // Over a bf16 cache nothing runs in front of the attention launch that could carry the list along: a small one of tiles alone
     // travels in the arguments instead of an upload launch (5 us: one prefill of 32 tokens 10.4 -> 7.6 us a call, one
     // of 509 tokens over 4 099 55.8 -> 49.5 with the small append items).
-    out.by_tiles = opt.force_kv_splits <= 0 && opt.kv_bytes == 2 && build_tiles(s, (int32_t)std::min<int64_t>(wide_chunk, 1 << 30), out);
+    out.by_tiles = opt.force_kv_splits <= 0 && opt.kv_bytes == 2 && build_tiles(s, (int32_t)std::min<int64_t>(blocks ? block_chunk : wide_chunk, 1 << 30),
+                                                                                   (int32_t)std::min<int64_t>(narrow_chunk, 1 << 30), blocks, out);
 
     // 4b. append items
     if (opt.append_items) {

@@ -5,7 +5,7 @@
 // request (T_dec).  From these lengths alone the planner derives, per request and KV head:
 //   * wide items   -- tiles of up to 256 query rows (tokens x grouped heads) whose 8 waves
 //                     share K/V tiles staged in LDS (compute-bound prefill work), and
-//   * narrow items -- blocks of at most 32 query rows (decode rows, very short chunks)
+//   * narrow items -- blocks of at most 32 query rows (decode rows, very short chunks, and all rows of a small launch)
 //                     whose 8 waves split the key range (bandwidth-bound work),
 //   * append items -- (bf16 cache, append-then-attend calls) runs of packed new rows to be copied into
 //                     their pages by the same launch; they close the work list, where they fill the CUs
@@ -120,8 +120,8 @@ AMPD_HD CombItem table_comb(const RowTable& t, const RowEntry& e, int kvh) {
     return CombItem{e.req_L & 0xffffff, pack_heads(kvh, 0, t.G, KIND_NARROW), 0, L, e.part_off + kvh * pieces * slot, pieces, slot, 0};
 }
 
-// The work list of a small launch of tiles alone, in the kernel's arguments for the same reason: one word per item and 8 bytes
-// per cut tile.
+// The work list of a small launch of tiles alone, or of blocks of at most 32 query rows alone, in the kernel's arguments for the
+// same reason: one word per item and 8 bytes per cut tile (or block: "tile" below is either).
 constexpr int TILE_TABLE_ROWS = 16, TILE_TABLE_ITEMS = 256, TILE_TABLE_COMBS = 128;
 constexpr uint32_t TILE_NULL = 0xffffffffu;
 struct TileComb {
@@ -133,10 +133,14 @@ struct TileTable {
     int32_t chunk, tq;        // keys per piece; tokens of a full tile (a row's first tile takes the remainder)
     int32_t G, D, sum_L;
     int32_t append_rows;      // packed rows per append item
+    int32_t kind;             // KIND_WIDE, or KIND_NARROW: blocks of at most 32 query rows
+    int32_t few_chunk;        // ... then: keys per piece of a row that is one block (a decode row)
     ReqInfo rows[TILE_TABLE_ROWS];          // rows with new tokens
     uint32_t items[TILE_TABLE_ITEMS];       // row | kvh << 4 | tile << 10 | piece << 18 | cut tile << 25, or TILE_NULL
     TileComb combs[TILE_TABLE_COMBS];
 };
+
+AMPD_HD int32_t tile_chunk(const TileTable& t, int32_t L) { return t.kind == KIND_NARROW && L <= t.tq ? t.few_chunk : t.chunk; }
 
 // Tile and piece of a code.
 AMPD_HD Item tile_item(const TileTable& t, uint32_t code) {
@@ -145,13 +149,13 @@ AMPD_HD Item tile_item(const TileTable& t, uint32_t code) {
     const int rest = r.L % t.tq, first = rest ? rest : t.tq;
     Item it;
     it.req = r.req;
-    it.heads = pack_heads(kvh, 0, t.G, KIND_WIDE);
+    it.heads = pack_heads(kvh, 0, t.G, t.kind);
     it.q0 = tile ? first + (tile - 1) * t.tq : 0;
     it.nq = tile ? t.tq : first;
-    const int keys = r.C + it.q0 + it.nq;
-    it.kv_begin = piece * t.chunk;
-    it.kv_end = keys - it.kv_begin > t.chunk ? it.kv_begin + t.chunk : keys;
-    it.part_off = keys > t.chunk ? t.combs[code >> 25].part_off + piece * (it.nq * t.G * (t.D + 2)) : -1;
+    const int keys = r.C + it.q0 + it.nq, chunk = tile_chunk(t, r.L);
+    it.kv_begin = piece * chunk;
+    it.kv_end = keys - it.kv_begin > chunk ? it.kv_begin + chunk : keys;
+    it.part_off = keys > chunk ? t.combs[code >> 25].part_off + piece * (it.nq * t.G * (t.D + 2)) : -1;
     it.C = r.C;
     it.row_off = r.row_off;
     it.pad[0] = it.pad[1] = it.pad[2] = 0;
@@ -159,8 +163,8 @@ AMPD_HD Item tile_item(const TileTable& t, uint32_t code) {
 }
 AMPD_HD CombItem tile_comb(const TileTable& t, int i) {
     const Item it = tile_item(t, t.combs[i].code);
-    const int keys = it.C + it.q0 + it.nq;
-    return CombItem{it.req, it.heads, it.q0, it.nq, t.combs[i].part_off, (keys + t.chunk - 1) / t.chunk, it.nq * t.G * (t.D + 2), 0};
+    const int keys = it.C + it.q0 + it.nq, chunk = tile_chunk(t, t.rows[t.combs[i].code & 15].L);
+    return CombItem{it.req, it.heads, it.q0, it.nq, t.combs[i].part_off, (keys + chunk - 1) / chunk, it.nq * t.G * (t.D + 2), 0};
 }
 
 // Whether the page slots up to position C (a row's one new token) all lie in the 32-key block of a narrow item that holds the
