@@ -66,6 +66,24 @@ def kernel_resources() -> dict:
     return out
 
 
+FAST_LIB = os.path.join(HERE, "_fastcall.so")
+FAST_SRC = os.path.join(CSRC, "fastcall.cpp")
+
+
+def build_fastcall(force: bool = False) -> str:
+    """Compile the binding's extension module (host code against Python and torch, no GPU code) with g++."""
+    deps = [FAST_SRC, os.path.join(INCLUDE, "ampd.h")]
+    if force or not os.path.exists(FAST_LIB) or any(os.path.getmtime(d) > os.path.getmtime(FAST_LIB) for d in deps):
+        import sysconfig
+        import torch
+        t = os.path.dirname(torch.__file__)
+        subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"],
+                               "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+                               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", FAST_SRC, "-o", FAST_LIB,
+                               "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{os.path.join(t, 'lib')}"])
+    return FAST_LIB
+
+
 SCHED_LIB = os.path.join(HERE, "libampd_sched.so")
 SCHED_SRC = os.path.join(CSRC, "sched.cpp")
 SCHED_HDR = os.path.join(INCLUDE, "ampd_sched.h")
@@ -105,3 +123,4 @@ def build_host_sanitized(address: bool = True):
 if __name__ == "__main__":
     print(build_sched(force=True))
     print(build(force=True, verbose=True))
+    print(build_fastcall(force=True))

@@ -1,0 +1,196 @@
+// The binding's calls with every argument of its usual kind (torch tensors, int32 numpy arrays, a KVCache of plain numbers): the
+// ampd_kv_cache and ampd_batch structures are filled and the entry point is called without an interpreted step per field.  call()
+// returns the status, or None, before anything is called, when an argument is of another kind: the binding then takes its general path.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <cfloat>
+#include <climits>
+#include <cmath>
+
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "ampd.h"
+
+namespace {
+
+PyObject *s_num_q_heads, *s_num_kv_heads, *s_head_dim, *s_page_size, *s_kv_dtype, *s_k_pool, *s_v_pool, *s_k_scale, *s_v_scale, *s_softmax_scale;
+PyObject *g_device = nullptr, *g_raw_stream = nullptr;   // torch's functions: current device; raw stream of a device
+
+struct Ref {                                             // an owned reference
+    PyObject* o;
+    explicit Ref(PyObject* p) : o(p) {}
+    ~Ref() { Py_XDECREF(o); }
+    Ref(const Ref&) = delete;
+    Ref& operator=(const Ref&) = delete;
+};
+
+struct Lengths {                                         // a one-dimensional contiguous int32 array
+    Py_buffer b;
+    bool held = false;
+    bool take(PyObject* o) {
+        if (PyObject_GetBuffer(o, &b, PyBUF_ND | PyBUF_FORMAT) != 0) {
+            PyErr_Clear();
+            return false;
+        }
+        held = true;
+        return b.ndim == 1 && b.itemsize == 4 && b.format && b.format[0] == 'i' && b.format[1] == 0 && b.shape[0] <= INT_MAX;
+    }
+    ~Lengths() {
+        if (held) PyBuffer_Release(&b);
+    }
+};
+
+bool int_attr(PyObject* o, PyObject* name, int32_t* out) {
+    Ref v(PyObject_GetAttr(o, name));
+    if (!v.o || !PyLong_CheckExact(v.o)) return false;
+    int over = 0;
+    const long x = PyLong_AsLongAndOverflow(v.o, &over);
+    if (over || x < INT_MIN || x > INT_MAX) return false;
+    *out = (int32_t)x;
+    return true;
+}
+
+bool tensor(PyObject* o, const at::Tensor** t) {
+    if (!THPVariable_CheckExact(o)) return false;
+    *t = &THPVariable_Unpack(o);
+    return (*t)->defined();
+}
+bool address(PyObject* o, void** p) {
+    const at::Tensor* t;
+    if (!tensor(o, &t)) return false;
+    *p = t->data_ptr();
+    return true;
+}
+bool address_attr(PyObject* o, PyObject* name, void** p, bool may_be_none, int64_t* first_dim = nullptr) {
+    Ref v(PyObject_GetAttr(o, name));
+    if (!v.o) return false;
+    if (may_be_none && v.o == Py_None) {
+        *p = nullptr;
+        return true;
+    }
+    if (!address(v.o, p)) return false;
+    if (first_dim) {
+        const at::Tensor& t = THPVariable_Unpack(v.o);
+        if (t.dim() < 1) return false;
+        *first_dim = t.size(0);
+    }
+    return true;
+}
+
+bool current_stream(void** stream) {
+    Ref dev(PyObject_CallNoArgs(g_device));
+    if (!dev.o) return false;
+    Ref raw(PyObject_CallOneArg(g_raw_stream, dev.o));
+    if (!raw.o) return false;
+    *stream = PyLong_AsVoidPtr(raw.o);
+    return !PyErr_Occurred();
+}
+
+typedef ampd_status (*AttnFn)(const ampd_kv_cache*, const ampd_batch*, const void*, const void*, const void*, void*, void*, size_t, void*,
+                              const ampd_plan_options*);
+typedef ampd_status (*AppendFn)(const ampd_kv_cache*, const ampd_batch*, const void*, const void*, void*);
+typedef ampd_status (*MoveFn)(const ampd_kv_cache*, const ampd_batch*, int32_t, int32_t, const void*, const void*, void*);
+
+// call(entry point's address, cache, ctx_len, incr_len, block_table, rest...); rest: q, k_new, v_new, out, workspace (attention);
+// k, v (append); head_begin, head_count, k, v (pack, unpack).  Runs on torch's current stream.  False: not of the usual kind.
+bool run(PyObject* const* a, Py_ssize_t n, ampd_status* status) {
+    if (n != 7 && n != 9 && n != 10) return false;
+    if (!g_device || !PyLong_CheckExact(a[0])) return false;
+    void* fn = PyLong_AsVoidPtr(a[0]);
+    if (!fn) return false;
+    ampd_kv_cache c = {};
+    PyObject* cache = a[1];
+    if (!int_attr(cache, s_num_q_heads, &c.num_q_heads) || !int_attr(cache, s_num_kv_heads, &c.num_kv_heads) ||
+        !int_attr(cache, s_head_dim, &c.head_dim) || !int_attr(cache, s_page_size, &c.page_size) || !int_attr(cache, s_kv_dtype, &c.kv_dtype))
+        return false;
+    void *k, *v, *ks, *vs;
+    if (!address_attr(cache, s_k_pool, &k, false, &c.num_pages) || !address_attr(cache, s_v_pool, &v, false) ||
+        !address_attr(cache, s_k_scale, &ks, true) || !address_attr(cache, s_v_scale, &vs, true))
+        return false;
+    c.k_pool = k;
+    c.v_pool = v;
+    c.k_scale = static_cast<float*>(ks);
+    c.v_scale = static_cast<float*>(vs);
+    {
+        Ref f(PyObject_GetAttr(cache, s_softmax_scale));
+        if (!f.o || !PyFloat_CheckExact(f.o)) return false;
+        const double x = PyFloat_AS_DOUBLE(f.o);
+        if (!(std::fabs(x) <= FLT_MAX)) return false;
+        c.softmax_scale = (float)x;
+    }
+    Lengths ctx, incr;
+    if (!ctx.take(a[2]) || !incr.take(a[3]) || ctx.b.shape[0] != incr.b.shape[0]) return false;
+    const at::Tensor* bt;
+    if (!tensor(a[4], &bt) || bt->dim() != 2 || !bt->is_cuda() || bt->size(1) > INT_MAX) return false;
+    ampd_batch b = {};
+    b.num_reqs = (int32_t)ctx.b.shape[0];
+    b.max_pages_per_req = (int32_t)bt->size(1);
+    b.h_ctx_len = static_cast<const int32_t*>(ctx.b.buf);
+    b.h_incr_len = static_cast<const int32_t*>(incr.b.buf);
+    b.d_block_table = static_cast<const int32_t*>(bt->data_ptr());
+    int32_t heads[2] = {0, 0};
+    for (int i = 0; n == 9 && i < 2; ++i) {
+        if (!PyLong_CheckExact(a[5 + i])) return false;
+        int over = 0;
+        const long x = PyLong_AsLongAndOverflow(a[5 + i], &over);
+        if (over || x < INT_MIN || x > INT_MAX) return false;
+        heads[i] = (int32_t)x;
+    }
+    void* p[5];
+    const int first = n == 9 ? 7 : 5;
+    for (int i = first; i < n; ++i)
+        if (!address(a[i], &p[i - first])) return false;
+    const size_t ws_bytes = n == 10 ? THPVariable_Unpack(a[9]).nbytes() : 0;
+    void* stream;
+    if (!current_stream(&stream)) return false;
+    Py_BEGIN_ALLOW_THREADS
+    if (n == 10) *status = reinterpret_cast<AttnFn>(fn)(&c, &b, p[0], p[1], p[2], p[3], p[4], ws_bytes, stream, nullptr);
+    else if (n == 9) *status = reinterpret_cast<MoveFn>(fn)(&c, &b, heads[0], heads[1], p[0], p[1], stream);
+    else *status = reinterpret_cast<AppendFn>(fn)(&c, &b, p[0], p[1], stream);
+    Py_END_ALLOW_THREADS
+    return true;
+}
+
+PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    ampd_status st = AMPD_OK;
+    bool done = false;
+    try {
+        done = run(args, n, &st);
+    } catch (...) {                                      // a tensor without storage, say: the general path reports it
+        done = false;
+    }
+    if (done) return PyLong_FromLong(st);
+    PyErr_Clear();
+    Py_RETURN_NONE;
+}
+
+// streams(current device, raw stream of a device): torch's functions
+PyObject* streams(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    if (n != 2 || !PyCallable_Check(args[0]) || !PyCallable_Check(args[1])) {
+        PyErr_SetString(PyExc_TypeError, "two functions");
+        return nullptr;
+    }
+    Py_INCREF(args[0]);
+    Py_INCREF(args[1]);
+    g_device = args[0];
+    g_raw_stream = args[1];
+    Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {{"call", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(call)), METH_FASTCALL, nullptr},
+                         {"streams", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(streams)), METH_FASTCALL, nullptr},
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__fastcall() {
+    struct { PyObject** at; const char* name; } names[] = {
+        {&s_num_q_heads, "num_q_heads"}, {&s_num_kv_heads, "num_kv_heads"}, {&s_head_dim, "head_dim"}, {&s_page_size, "page_size"},
+        {&s_kv_dtype, "kv_dtype"}, {&s_k_pool, "k_pool"}, {&s_v_pool, "v_pool"}, {&s_k_scale, "k_scale"}, {&s_v_scale, "v_scale"},
+        {&s_softmax_scale, "softmax_scale"}};
+    for (auto& n : names)
+        if (!(*n.at = PyUnicode_InternFromString(n.name))) return nullptr;
+    return PyModule_Create(&module);
+}
