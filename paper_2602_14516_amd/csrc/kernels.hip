@@ -54,7 +54,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(uintptr_t)(p))
-#define GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+typedef const __attribute__((address_space(1))) u32x4* GlobalChunk;
 
 constexpr int WG = 256;                 // append / combine kernels
 constexpr int AWG = 64 * ATTN_WAVES;    // attention kernel: 8 waves, one workgroup per CU
@@ -93,6 +94,12 @@ __device__ __forceinline__ float max_xor32(float x) {
 __device__ __forceinline__ float sum_xor32(float x) {
     const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// A wave-uniform global address in scalar registers.
+__device__ __forceinline__ GlobalBytes scalar_base(const char* p) {
+    const uint64_t a = (uint64_t)p;
+    return (GlobalBytes)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a));
 }
 
 // 8 stored elements -> 8 bf16 (as a 16-byte vector) for LDS.
@@ -563,7 +570,7 @@ __device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" :
 //                 registers; the data is in LDS once the vector-memory counter has drained,
 //                 which the barrier that ends a pipeline step waits for.
 //   DMA = false: global -> registers (fetch_kv) -> LDS (commit), widening 8-bit codes.
-template <int D, int KVT, int NTHR, int NKEYS, bool FRESH_SCALES = false>
+template <int D, int KVT, int NTHR, int NKEYS>
 struct Loader {
     using G_ = Geo<D>;
     static constexpr int KPW = G_::KPW;
@@ -579,19 +586,7 @@ struct Loader {
     static constexpr int ES = RawChunk<KVT>::ES;
     int pg[NPASS];
     RawChunk<KVT> k[NPASS], v[NPASS];
-    // 8-bit cache: the page scales of the tile.  One per pass in general; the one-wave loader of narrow items (32 keys from a
-    // multiple of 32) sees at most two pages (page size >= 16), and keeps two scales instead of eight per operand.
-    static constexpr bool TWO_SCALES = NW == 1 && NKEYS == 32;
-    static constexpr int NSC = TWO_SCALES ? 2 : NPASS;
-    float ks[NSC], vs[NSC];
-    __device__ __forceinline__ float k_scale_of(const AttnParams& p, int ps) const {
-        if constexpr (TWO_SCALES) return ps * KPP < p.P ? ks[0] : ks[1];
-        else return ks[ps];
-    }
-    __device__ __forceinline__ float v_scale_of(const AttnParams& p, int ps) const {
-        if constexpr (TWO_SCALES) return ps * KPP < p.P ? vs[0] : vs[1];
-        else return vs[ps];
-    }
+    float ks[NPASS], vs[NPASS];                       // 8-bit cache: the page scales of the passes
 
     // t: thread index inside the group of NTHR threads.  The block table is read through the
     // scalar cache (it is constant for the duration of the kernel): scalar loads do not count
@@ -661,67 +656,46 @@ struct Loader {
         return (uint32_t)(((l >> 2) % KPW) * p.Hkv * D * 2 + ((l / (4 * KPW)) * 4 + (l & 3)) * 16);
     }
 
-    // FRESH_SCALES: this workgroup may have written the scale itself (see append_item_pages), so it is read through the
-    // vector memory path; the scalar cache would not see the store.
-    __device__ __forceinline__ static float scale_at(const float* s) {
-        if constexpr (FRESH_SCALES) return __hip_atomic_load(s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else return *s;
-    }
     // ---- register-staged path
     // FULL: the whole tile lies inside the key range and in the pages
-    template <bool FULL, bool DO_K, bool DO_V>
+    template <bool FULL>
     __device__ __forceinline__ void fetch_kv_impl(const AttnParams& p, const ItemCtx& ic, int kbase, int t) {
         const uint32_t lo = lane_off(t);
 #pragma unroll
         for (int ps = 0; ps < NPASS; ++ps) {
             const Row r = row_of(p, ic, kbase, t, ps);
-            // the scale slot this pass fills: its own, or (two scales) slot 0 from the first pass and slot 1 from the pass
-            // of key 16, the first of the second page when pages hold 16 keys (with larger pages slot 1 is never read)
-            const int sl = !TWO_SCALES ? ps : ps == 0 ? 0 : ps == 16 / KPP ? 1 : -1;
-            if (sl >= 0) {
-                if (DO_K) ks[sl] = 1.0f;
-                if (DO_V) vs[sl] = 1.0f;
-                if (KVT == KV_FP8 && (FULL || r.key0 < ic.kv_end)) {   // (a group past the key range has no page)
-                    if (DO_K) ks[sl] = scale_at(p.k_scale + (int64_t)r.page * p.Hkv + ic.kvh);
-                    if (DO_V) vs[sl] = scale_at(p.v_scale + (int64_t)r.page * p.Hkv + ic.kvh);
-                }
+            ks[ps] = vs[ps] = 1.0f;
+            if (KVT == KV_FP8 && (FULL || r.key0 < ic.kv_end)) {      // (a group past the key range has no page)
+                ks[ps] = p.k_scale[(int64_t)r.page * p.Hkv + ic.kvh];
+                vs[ps] = p.v_scale[(int64_t)r.page * p.Hkv + ic.kvh];
             }
             const int key = r.key0 + lane_key(t);
             if (FULL || (key < ic.kv_end && key < ic.c_rows)) {
-                if (DO_K) k[ps].load(r.kb, lo);
-                if (DO_V) v[ps].load(r.vb, lo);
+                k[ps].load(r.kb, lo);
+                v[ps].load(r.vb, lo);
             } else if (KVT == KV_BF16 && key < ic.kv_end) {      // a new token of this call: read its packed row
                 const Row n = new_row_of(p, ic, r);
                 const uint32_t nlo = new_lane_off(p, t);
-                if (DO_K) k[ps].load(n.kb, nlo);
-                if (DO_V) v[ps].load(n.vb, nlo);
+                k[ps].load(n.kb, nlo);
+                v[ps].load(n.vb, nlo);
             } else {
-                if (DO_K) k[ps].zero();                          // keys past the item's end: zeros, so
-                if (DO_V) v[ps].zero();                          // that 0-weights never meet NaN garbage
+                k[ps].zero();                                    // keys past the item's end: zeros, so
+                v[ps].zero();                                    // that 0-weights never meet NaN garbage
             }
         }
     }
-    template <bool DO_K = true, bool DO_V = true>
     __device__ __forceinline__ void fetch_kv(const AttnParams& p, const ItemCtx& ic, int kbase, int t) {
         if (kbase + NKEYS <= min(ic.kv_end, ic.c_rows))          // uniform: whole tile inside the key range, in pages
-            fetch_kv_impl<true, DO_K, DO_V>(p, ic, kbase, t);
+            fetch_kv_impl<true>(p, ic, kbase, t);
         else
-            fetch_kv_impl<false, DO_K, DO_V>(p, ic, kbase, t);
+            fetch_kv_impl<false>(p, ic, kbase, t);
     }
     // kl / vl: LDS byte addresses of this tile's K and V
-    __device__ __forceinline__ void commit_k(const AttnParams& p, uint32_t kl, int t) const {
-#pragma unroll
-        for (int ps = 0; ps < NPASS; ++ps) put(k[ps], k_scale_of(p, ps), kl + slot_of(ps, t));
-    }
-    __device__ __forceinline__ void commit_v(const AttnParams& p, uint32_t vl, int t) const {
-#pragma unroll
-        for (int ps = 0; ps < NPASS; ++ps) put(v[ps], v_scale_of(p, ps), vl + slot_of(ps, t));
-    }
-    __device__ __forceinline__ void commit(const AttnParams& p, uint32_t kl, uint32_t vl, int t) const {
+    __device__ __forceinline__ void commit(uint32_t kl, uint32_t vl, int t) const {
 #pragma unroll
         for (int ps = 0; ps < NPASS; ++ps) {
-            put(k[ps], k_scale_of(p, ps), kl + slot_of(ps, t));
-            put(v[ps], v_scale_of(p, ps), vl + slot_of(ps, t));
+            put(k[ps], ks[ps], kl + slot_of(ps, t));
+            put(v[ps], vs[ps], vl + slot_of(ps, t));
         }
     }
     __device__ __forceinline__ static uint32_t slot_of(int ps, int t) {
@@ -918,7 +892,7 @@ __device__ __forceinline__ void wide_body(const AttnParams& p, const ItemCtx& ic
         ld.fetch_pages(p, ic, k_lo, tid);
         ld.fetch_kv(p, ic, k_lo, tid);
         if (ntiles > 1) ld.fetch_pages(p, ic, k_lo + KT, tid);
-        ld.commit(p, smem, smem + G_::KTILE, tid);
+        ld.commit(smem, smem + G_::KTILE, tid);
         __syncthreads();
         auto step = [&](int t, auto masked) {
             const uint32_t cur = smem + (t & 1) * G_::WIDE_STAGE;
@@ -929,7 +903,7 @@ __device__ __forceinline__ void wide_body(const AttnParams& p, const ItemCtx& ic
                 if (t + 2 < ntiles) ld.fetch_pages(p, ic, k_lo + (t + 2) * KT, tid);
             }
             compute(t, cur, masked);
-            if (more) ld.commit(p, nxt, nxt + G_::KTILE, tid);
+            if (more) ld.commit(nxt, nxt + G_::KTILE, tid);
             __syncthreads();
         };
         for (int t = 0; t < t_diag; ++t) step(t, std::false_type{});
@@ -1105,12 +1079,114 @@ struct NewToken {
 // blocks in the same order per state, so the result is the same bit for bit); a wave stages its blocks through an LDS
 // region of its own.
 
+// K/V loader of one wave of a narrow item: 32-key blocks (from a multiple of 32), global -> registers -> the wave's LDS region.
+// A wave alone issues an instruction every four cycles or more, and the block loop used to be bound by that: page ids, branches and
+// 64-bit addresses for every 1 KB load were half of its instructions.  A block touches at most two pages (page size >= 16), so it
+// takes one address per half block, the loads of a half differ in their immediate offset only, and one vector load fetches
+// the page ids of the wave's next 8 blocks (scalar loads share their counter with LDS reads and return out of order: the first
+// fragment read of every block waited for the next block's page ids).  bf16 d = 128: 240 instructions a block instead of 330.
+// Four rows over 36-70 k keys in 8 bits 26.6 -> 25.9 us, 64 decode rows next to 8 prefill rows 89.3 -> 87.3 us; 90 drawn batches:
+// decode at d = 128 0.98 of its time before, at d = 64 (a block always was two or four loads a side) 1.00, mixed 0.99, small prefill 0.98.
+template <int D, int KVT>
+struct BlockLoader {
+    using G_ = Geo<D>;
+    using T = Loader<D, KVT, 64, 32>;                 // the lane's place in a load and in LDS
+    static constexpr int ES = RawChunk<KVT>::ES;
+    static constexpr int KPL = 1024 / (D * ES);       // keys per load
+    static constexpr int LPH = 16 / KPL;              // loads per half block
+    static constexpr int NL = 2 * LPH;
+    static_assert(KPL == T::KPP && LPH >= 1 && 1024 * LPH <= 4096, "a half block is addressed by immediate offsets");
+    RawChunk<KVT> k[NL], v[NL];
+    static constexpr int IDS = 8;                     // blocks whose page ids one load fetches
+    int ids;                                          // lane 2 n + h: page of half h of the wave's block j / IDS * IDS + n
+    int page[2];                                      // of the block that is fetched next
+    int64_t off[2];                                   // byte offset of the fetched block's halves in the pools
+    float scale[4];                                   // 8-bit cache: [h]: K's scale of half h's page, [2 + h]: V's
+    float sc[4];                                      // the same of the block that is being committed
+
+    // page ids of the wave's blocks j .. j + IDS - 1 (j a multiple of IDS); past the key range: the last key's page
+    __device__ __forceinline__ void fetch_ids(const AttnParams& p, const ItemCtx& ic, int first_key, int step, int j, int lane) {
+        const int key = first_key + (j + (lane >> 1) % IDS) * step + (lane & 1) * 16;
+        ids = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(ic.bt_row) + (uint32_t)(min(key, ic.kv_end - 1) >> p.logP) * 4u);
+    }
+    __device__ __forceinline__ void take_pages(int j) {
+        page[0] = __builtin_amdgcn_readlane(ids, 2 * (j % IDS));
+        page[1] = __builtin_amdgcn_readlane(ids, 2 * (j % IDS) + 1);
+    }
+    __device__ __forceinline__ void locate(const AttnParams& p, const ItemCtx& ic, int kbase) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            off[h] = ((((int64_t)page[h] * p.Hkv + ic.kvh) << p.logP) + ((kbase + 16 * h) & (p.P - 1))) * (D * ES);
+    }
+    __device__ __forceinline__ void fetch_scales(const AttnParams& p, const ItemCtx& ic) {
+        // through the vector memory path: this workgroup may have written one itself, see append_item_pages, and the scalar
+        // cache would not see the store.  Four loads of one address each: one of four addresses with the scales read out of its
+        // lanes costs 1.5 % at d = 64, 40 drawn decode batches.
+        if constexpr (KVT == KV_FP8) {
+#pragma unroll
+            for (int l = 0; l < 4; ++l)
+                scale[l] = __hip_atomic_load((l & 2 ? p.v_scale : p.k_scale) + ic.kvh + (int64_t)page[l & 1] * p.Hkv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    // Every block issues the same number of loads (so that waiting for the older of two operands never waits for the younger one as
+    // well): a slot past the key range is the last key's once more, and zeroed by commit_v.
+    template <bool DO_K, bool DO_V>
+    __device__ __forceinline__ void fetch_kv(const AttnParams& p, const ItemCtx& ic, int kbase, bool paced, int lane) {
+        uint32_t lo = T::lane_off(lane);
+        const bool plain = kbase + 32 <= min(ic.kv_end, ic.c_rows);     // uniform: all keys in pages (8-bit: or anything there)
+        if (plain) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const GlobalBytes ka = scalar_base(static_cast<const char*>(p.k_pool) + off[h]), va = scalar_base(static_cast<const char*>(p.v_pool) + off[h]);
+                asm("" : "+v"(lo));                                  // (with the scalar bases: 32-bit lane offsets, not 64-bit addresses per lane)
+#pragma unroll
+                for (int i = 0; i < LPH; ++i) {
+                    if (DO_K) k[h * LPH + i].v = __builtin_nontemporal_load((GlobalChunk)(ka + i * 1024 + lo));
+                    if (DO_V) v[h * LPH + i].v = __builtin_nontemporal_load((GlobalChunk)(va + i * 1024 + lo));
+                    if (paced) __builtin_amdgcn_s_sleep(4);           // (see build_table)
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else {
+            const int64_t row0 = ((int64_t)ic.row_off * p.Hkv + ic.kvh) * (D * ES);    // packed rows [token][Hkv][D]
+            const uint32_t chunk = lo - T::lane_key(lane) * (D * ES);
+#pragma unroll
+            for (int n = 0; n < NL; ++n) {
+                const int key = min(n * KPL + T::lane_key(lane), ic.kv_end - 1 - kbase);    // within the block
+                const bool is_new = KVT == KV_BF16 && kbase + key >= ic.c_rows;             // a new token of this call: its packed row
+                const int64_t at = is_new ? row0 + (int64_t)(kbase + key - ic.C) * (p.Hkv * D * ES) + chunk
+                                          : (key < 16 ? off[0] : off[1]) + (key & 15) * (D * ES) + chunk;
+                if (DO_K) k[n].load(static_cast<const char*>(is_new ? p.k_new : p.k_pool) + at, 0);
+                if (DO_V) v[n].load(static_cast<const char*>(is_new ? p.v_new : p.v_pool) + at, 0);
+                __builtin_amdgcn_sched_barrier(0);                   // (one address per lane at a time: registers)
+            }
+        }
+    }
+    __device__ __forceinline__ void commit_k(uint32_t kl, int lane) {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) sc[l] = KVT == KV_FP8 ? scale[l] : 1.0f;
+        // (a K row past the key range may hold anything: its logits are replaced by the causal select)
+#pragma unroll
+        for (int n = 0; n < NL; ++n) T::put(k[n], sc[n / LPH], kl + T::slot_of(0, lane) + n * (T::GPP * G_::GS));
+    }
+    // V rows past the key range: zeros, so that 0-weights never meet NaN garbage
+    __device__ __forceinline__ void commit_v(const ItemCtx& ic, int kbase, uint32_t vl, int lane) {
+        if (kbase + 32 > ic.kv_end) {                         // uniform
+#pragma unroll
+            for (int n = 0; n < NL; ++n)
+                if (kbase + n * KPL + T::lane_key(lane) >= ic.kv_end) v[n].zero();
+        }
+#pragma unroll
+        for (int n = 0; n < NL; ++n) T::put(v[n], sc[2 + n / LPH], vl + T::slot_of(0, lane) + n * (T::GPP * G_::GS));
+    }
+};
+
 constexpr int LEAN_ROWS = 8;
 // ROWS: query rows a wave carries (32, or 16 for items of at most 16 rows: half the matrix and softmax work per key)
 // NW: waves of the workgroup.  QUANT: the item appends its own new tokens (8-bit cache) before it reads its pages.
 // LEAN: K and V of a block take turns in one LDS region per wave, and the merge holds the item's rows only (at most 8).
 template <int D, int KVT, int ROWS, int NW, bool QUANT = false, bool LEAN = false>
-__device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& ic, uint32_t smem, int tid) {
+__device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& ic, uint32_t smem, int tid, bool paced = false) {
     using G_ = Geo<D>;
     constexpr bool R16 = ROWS == 16;
     constexpr int NACC = ATTN_WAVES / NW;
@@ -1123,6 +1199,13 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
     const int lim = valid ? ic.C + tok : 0x3fffffff;
     const int first_lim = ic.C + ic.q0;                  // smallest last-visible key among the rows
 
+    const int nblocks = (ic.kv_end - ic.kv_begin + 31) >> 5;
+    constexpr int STEP = 32 * NW;                         // the wave's block j: block wave + j * NW, keys key0 + j * STEP ..
+    const int key0 = ic.kv_begin + wave * 32;
+    const int nj = (nblocks - wave + NW - 1) / NW;        // the wave's blocks (<= 0: none)
+    // page ids before Q: loads return in order, and Q comes from HBM
+    BlockLoader<D, KVT> ld;
+    if (nj > 0) ld.fetch_ids(p, ic, key0, STEP, 0, lane);
     bf16x8 Q[R16 ? D / 32 : G_::NKK];
     std::conditional_t<R16, WaveAcc16<D>, WaveAcc<D>> acc[NACC];
     if constexpr (R16) {
@@ -1145,64 +1228,69 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
 
     const uint32_t kl = smem + wave * ((LEAN ? 1 : 2) * G_::B32);
     const uint32_t vl = LEAN ? kl : kl + G_::B32;
-    const int nblocks = (ic.kv_end - ic.kv_begin + 31) >> 5;
-    Loader<D, KVT, 64, 32, QUANT> ld;
-    auto first_block = [&]() {
-        ld.fetch_kv(p, ic, ic.kv_begin + wave * 32, lane);
-        if (wave + NW < nblocks) ld.fetch_pages(p, ic, ic.kv_begin + (wave + NW) * 32, lane);
-    };
     NewToken<D> nt;
     bool pending = false;                                 // this wave has a token to encode before it fetches the last block
-    auto encode_before = [&](int b) {
+    // block j, K and V or (LEAN) K alone: its pages are known; with every eighth block, the page ids of the next eight
+    auto fetch = [&](int j) {
         if constexpr (ONE_TOKEN) {
-            if (pending && b == nblocks - 1) nt.finish(p, ic, lane);
+            if (pending && j == nj - 1) nt.finish(p, ic, lane);
+        }
+        ld.locate(p, ic, key0 + j * STEP);
+        if ((j + 1) % ld.IDS == 0) ld.fetch_ids(p, ic, key0, STEP, j + 1, lane);
+        ld.fetch_scales(p, ic);
+        ld.template fetch_kv<true, !LEAN>(p, ic, key0 + j * STEP, paced, lane);
+    };
+    auto first_block = [&]() {
+        ld.take_pages(0);
+        fetch(0);
+        if constexpr (LEAN) {
+            ld.template fetch_kv<false, true>(p, ic, key0, paced, lane);
+            ld.take_pages(1);
         }
     };
-    if (wave < nblocks) ld.fetch_pages(p, ic, ic.kv_begin + wave * 32, lane);
     if (QUANT && p.k_new && ic.kv_end > ic.C) {           // uniform
         if (ONE_TOKEN && ic.nq == 1 && page_in_last_block(ic.C, p.P)) {
-            pending = wave == (nblocks - 1) % NW;
+            pending = nj > 0 && wave + (nj - 1) * NW == nblocks - 1;
             if (pending) nt.start(p, ic, lane);
-            if (pending && wave == nblocks - 1) nt.start_scale(p, ic, lane);
-            encode_before(wave);
-            if (wave < nblocks) first_block();
-            if (pending && wave != nblocks - 1) nt.start_scale(p, ic, lane);
+            if (pending && nj == 1) nt.start_scale(p, ic, lane);
+            if (nj > 0) first_block();
+            if (pending && nj > 1) nt.start_scale(p, ic, lane);
         } else {
             // blocks from nold on hold pages that get new tokens; the first blocks before them travel while the append runs
             const int nold = ((max(ic.C, ic.kv_begin) & ~(p.P - 1)) - ic.kv_begin) >> 5;
             if (wave < nold) first_block();
             append_item_pages<D, NW>(p, ic, tid);
             __syncthreads();
-            if (wave >= nold && wave < nblocks) first_block();
+            if (wave >= nold && nj > 0) first_block();
         }
-    } else if (wave < nblocks) {
+    } else if (nj > 0) {
         first_block();
     }
-    for (int b0 = wave; b0 < nblocks; b0 += ATTN_WAVES) {
+    for (int j0 = 0; j0 < nj; j0 += NACC) {
         static_for<0, NACC>([&](auto ac) {
             auto& st = acc[decltype(ac)::value];
-            const int b = b0 + decltype(ac)::value * NW;
-            if (b >= nblocks) return;
-            const int kbase = ic.kv_begin + b * 32;
-            const bool more = b + NW < nblocks;
+            const int j = j0 + decltype(ac)::value;
+            if (j >= nj) return;
+            const int kbase = key0 + j * STEP;
+            const bool more = j + 1 < nj;
             const int rel = lim - kbase - 4 * (R16 ? key_group16(lane >> 4) : lane >> 5);
             const bool masked = kbase + 31 > first_lim;
+            ld.commit_k(kl, lane);
             if constexpr (LEAN) {
-                ld.commit_k(p, kl, lane);
-                encode_before(b + NW);
-                if (more) ld.template fetch_kv<true, false>(p, ic, kbase + 32 * NW, lane);
+                if (more) fetch(j + 1);
                 const bf16x8 P = softmax16<D>(kl, Q, st, p.c_log2, rel, masked, lane);
-                ld.commit_v(p, vl, lane);
-                if (more) ld.template fetch_kv<false, true>(p, ic, kbase + 32 * NW, lane);
-                if (b + 2 * NW < nblocks) ld.fetch_pages(p, ic, kbase + 64 * NW, lane);
+                ld.commit_v(ic, kbase, vl, lane);
+                if (more) {
+                    ld.take_pages(j + 2);
+                    ld.template fetch_kv<false, true>(p, ic, kbase + STEP, paced, lane);
+                }
                 pv16<D>(vl, P, st, lane);
                 return;
             }
-            ld.commit(p, kl, vl, lane);
-            encode_before(b + NW);
+            ld.commit_v(ic, kbase, vl, lane);
             if (more) {
-                ld.fetch_kv(p, ic, kbase + 32 * NW, lane);
-                if (b + 2 * NW < nblocks) ld.fetch_pages(p, ic, kbase + 64 * NW, lane);
+                ld.take_pages(j + 1);
+                fetch(j + 1);
             }
             if constexpr (R16) {
                 const bf16x8 P = softmax16<D>(kl, Q, st, p.c_log2, rel, masked, lane);
@@ -1538,10 +1626,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : NW < ATTN_WAVES && KVT == KV
         row = (idx - t.n_whole) / t.Hkv;
     }
     const ItemCtx ic = item_ctx<KVT>(p, table_item(t, t.e[__builtin_amdgcn_readfirstlane(row)], idx));
+    // (only there a block is enough loads to matter: 8-bit decode batches of d = 64 lose 0.3 % by it, d = 128 0.2 %)
+    const bool paced = D == 128 && KVT == KV_BF16 && NW == ATTN_WAVES && t.paced;
     if (NW < ATTN_WAVES || ic.nq * ic.gn <= 16)
-        narrow_body<D, KVT, 16, NW, KVT == KV_FP8, LEAN>(p, ic, smem, tid);
+        narrow_body<D, KVT, 16, NW, KVT == KV_FP8, LEAN>(p, ic, smem, tid, paced);
     else
-        narrow_body<D, KVT, 32, NW, KVT == KV_FP8>(p, ic, smem, tid);
+        narrow_body<D, KVT, 32, NW, KVT == KV_FP8>(p, ic, smem, tid, paced);
 }
 
 // ---------------------------------------------------------------------------------------------
