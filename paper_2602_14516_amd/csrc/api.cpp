@@ -310,7 +310,7 @@ ampd_status do_attn(const ampd_kv_cache* c, const ampd_batch* b, const Plan& pla
     if (timing) HIP_TRY(hipEventRecord(t_ev[1], st));
     HIP_TRY(plan.by_table   ? launch_rows(p, plan.table, kvt, plan.grid, st)
             : plan.by_tiles ? launch_tiles(p, plan.tiles, plan.grid, st)
-                            : launch_attn(p, c->head_dim, kvt, plan.grid, st));
+                            : launch_attn(p, c->head_dim, kvt, plan.num_wide > 0, plan.grid, st));
     if (timing) HIP_TRY(hipEventRecord(t_ev[2], st));
     int comb_rows = 0, comb_splits = 0;
     for (const CombItem& ci : plan.combs) {

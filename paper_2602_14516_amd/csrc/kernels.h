@@ -62,7 +62,8 @@ struct AppendParams {
 
 // h_src: pinned, device-visible host memory; bytes is rounded up to 16
 hipError_t launch_upload(const void* h_src, void* d_dst, size_t bytes, hipStream_t st);
-hipError_t launch_attn(const AttnParams& p, int D, int kvt, int grid, hipStream_t st);
+// tiles: the list holds some (otherwise grid is the number of items)
+hipError_t launch_attn(const AttnParams& p, int D, int kvt, bool tiles, int grid, hipStream_t st);
 // a batch of decode rows alone, whose list travels in the arguments; p.k_new: the call appends (both kinds of cache)
 hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid, hipStream_t st);
 // a small launch of tiles alone over a bf16 cache, likewise

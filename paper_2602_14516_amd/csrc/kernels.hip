@@ -144,6 +144,8 @@ struct ItemCtx {
     int c_rows;                // keys from this position on are read from the packed new rows (k_new / v_new), not from
                                // the pages: C when the page writes of this call ride in the same launch, else "never"
     const int32_t* bt_row;     // block-table row of the request
+    bool rounded;              // a prefill row (more than 32 query rows per KV head): its sums are taken over the rounded probabilities, in
+                               // a block as in a tile; decode rows and short chunks, narrow in every launch, sum the fp32 ones
 };
 constexpr int NEVER = 0x3fffffff;
 
@@ -163,6 +165,7 @@ __device__ __forceinline__ ItemCtx item_ctx(const AttnParams& p, const Item& it)
     c.row_off = it.row_off;
     c.c_rows = KVT == KV_BF16 && p.k_new ? it.C : NEVER;
     c.bt_row = p.block_table + (int64_t)it.req * p.max_pages;
+    c.rounded = it.row_L * c.gn > 32;
     return c;
 }
 
@@ -229,9 +232,9 @@ __device__ __forceinline__ void raise_reference(WaveAcc<D>& st, float mx) {
     st.m = m_new;
 }
 
-// p = 2^(S*c - m); returns psum + this lane's sum; P = bf16(p) as the two B operands of the second product.  The sum is taken over the
-// ROUNDED probabilities, two per instruction (dot product of a bf16 pair with (1, 1) accumulated in fp32), which is also what
-// the second product adds up: where few keys are seen the roundings cancel (100 new tokens alone: error against 64 bits 1.834e-3 -> 1.811e-3).
+// p = 2^(S*c - m); returns psum + this lane's sum over the ROUNDED probabilities, two per instruction (dot product of a bf16 pair with
+// (1, 1) accumulated in fp32), which is also what the second product adds up; P = bf16(p) as the two B operands.  The rule of prefill rows:
+// tiles, and blocks that take a tile's place (see ItemCtx::rounded).
 __device__ __forceinline__ float exp32_dot(const f32x16& S, float c, float m_use, bf16x8 (&P)[2], float psum) {
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
@@ -242,6 +245,25 @@ __device__ __forceinline__ float exp32_dot(const f32x16& S, float c, float m_use
         P[i >> 3][(i + 1) & 7] = pr[1];
     }
     return psum;
+}
+
+// The same for a lane of a narrow item with its N logits in S: the sum is taken over the rounded probabilities where `rounded`
+// (uniform) says so, over the fp32 ones otherwise.  Both sums are taken: a branch would keep the reads of V from moving up past it.
+template <int N, class Logit, class Prob>
+__device__ __forceinline__ float exp_sum(float c, float m_use, bool rounded, Logit&& S, Prob&& P) {
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+    float sum = 0.0f, rounded_sum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < N; i += 2) {
+        const float p0 = fast_exp2(__builtin_fmaf(S(i), c, -m_use)), p1 = fast_exp2(__builtin_fmaf(S(i + 1), c, -m_use));
+        const bf16x2 pr = {(__bf16)p0, (__bf16)p1};
+        sum += p0;
+        sum += p1;
+        rounded_sum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, rounded_sum, false);
+        P(i, pr[0]);
+        P(i + 1, pr[1]);
+    }
+    return rounded ? rounded_sum : sum;
 }
 
 // O^T += V^T P^T for the 32 keys whose LDS tile starts at vl.
@@ -272,14 +294,14 @@ __device__ __forceinline__ void pv32(uint32_t vl, const bf16x8 (&P)[2], WaveAcc<
 // One 32-key block, straight: used by narrow items (bandwidth-bound, no pipelining needed).
 template <int D>
 __device__ __forceinline__ void block32(uint32_t kl, uint32_t vl, const bf16x8 (&Q)[Geo<D>::NKK], WaveAcc<D>& st,
-                                        float c, int rel, bool masked, int lane) {
+                                        float c, int rel, bool masked, bool rounded, int lane) {
     f32x16 S;
     bf16x8 P[2];
     qk32<D>(kl, Q, S, lane);
     if (masked) mask32(S, rel);                          // wave-uniform
     const float mx = rowmax32(S) * c;
     if (__any(mx > st.m + RESCALE_SLACK)) raise_reference<D>(st, mx);
-    st.l += exp32_dot(S, c, st.m == NEG_INF ? 0.0f : st.m, P, 0.0f);
+    st.l += exp_sum<16>(c, st.m == NEG_INF ? 0.0f : st.m, rounded, [&](int i) { return S[i]; }, [&](int i, __bf16 v) { P[i >> 3][i & 7] = v; });
     pv32<D>(vl, P, st, lane);
 }
 
@@ -369,23 +391,15 @@ __device__ __forceinline__ void pv16(uint32_t vl, const bf16x8& P, WaveAcc16<D>&
 
 // S^T and its softmax; P = the operand of the second product
 template <int D>
-__device__ __forceinline__ bf16x8 softmax16(uint32_t kl, const bf16x8 (&Q)[D / 32], WaveAcc16<D>& st, float c, int rel, bool masked, int lane) {
+__device__ __forceinline__ bf16x8 softmax16(uint32_t kl, const bf16x8 (&Q)[D / 32], WaveAcc16<D>& st, float c, int rel, bool masked, bool rounded, int lane) {
     f32x4 S[2];
     qk16<D>(kl, Q, S, lane);
     if (masked) mask16(S, rel);                          // wave-uniform
     float mx = fmaxf(fmaxf(fmaxf(S[0][0], S[0][1]), fmaxf(S[0][2], S[0][3])), fmaxf(fmaxf(S[1][0], S[1][1]), fmaxf(S[1][2], S[1][3])));
     mx = max_xor32(max_xor16(mx)) * c;
     if (__any(mx > st.m + RESCALE_SLACK)) raise_reference16<D>(st, mx);
-    const float m_use = st.m == NEG_INF ? 0.0f : st.m;
     bf16x8 P;
-    float psum = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float pv = fast_exp2(__builtin_fmaf(S[i >> 2][i & 3], c, -m_use));
-        psum += pv;
-        P[i] = (__bf16)pv;
-    }
-    st.l += psum;
+    st.l += exp_sum<8>(c, st.m == NEG_INF ? 0.0f : st.m, rounded, [&](int i) { return S[i >> 2][i & 3]; }, [&](int i, __bf16 v) { P[i] = v; });
     return P;
 }
 
@@ -1185,8 +1199,9 @@ constexpr int LEAN_ROWS = 8;
 // ROWS: query rows a wave carries (32, or 16 for items of at most 16 rows: half the matrix and softmax work per key)
 // NW: waves of the workgroup.  QUANT: the item appends its own new tokens (8-bit cache) before it reads its pages.
 // LEAN: K and V of a block take turns in one LDS region per wave, and the merge holds the item's rows only (at most 8).
+// rounded: see ItemCtx.  paced: see build_table.
 template <int D, int KVT, int ROWS, int NW, bool QUANT = false, bool LEAN = false>
-__device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& ic, uint32_t smem, int tid, bool paced = false) {
+__device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& ic, uint32_t smem, int tid, bool rounded, bool paced = false) {
     using G_ = Geo<D>;
     constexpr bool R16 = ROWS == 16;
     constexpr int NACC = ATTN_WAVES / NW;
@@ -1278,7 +1293,7 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
             ld.commit_k(kl, lane);
             if constexpr (LEAN) {
                 if (more) fetch(j + 1);
-                const bf16x8 P = softmax16<D>(kl, Q, st, p.c_log2, rel, masked, lane);
+                const bf16x8 P = softmax16<D>(kl, Q, st, p.c_log2, rel, masked, rounded, lane);
                 ld.commit_v(ic, kbase, vl, lane);
                 if (more) {
                     ld.take_pages(j + 2);
@@ -1293,10 +1308,10 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
                 fetch(j + 1);
             }
             if constexpr (R16) {
-                const bf16x8 P = softmax16<D>(kl, Q, st, p.c_log2, rel, masked, lane);
+                const bf16x8 P = softmax16<D>(kl, Q, st, p.c_log2, rel, masked, rounded, lane);
                 pv16<D>(vl, P, st, lane);
             } else {
-                block32<D>(kl, vl, Q, st, p.c_log2, rel, masked, lane);
+                block32<D>(kl, vl, Q, st, p.c_log2, rel, masked, rounded, lane);
             }
         });
     }
@@ -1487,11 +1502,11 @@ __device__ __forceinline__ void run_item(const AttnParams& p, int idx, uint32_t 
     const ItemCtx ic = item_ctx<KVT>(p, p.items[idx]);
     if (kind == KIND_WIDE)
         wide_body<D, KVT>(p, ic, smem, tid);
-    else if (kind == KIND_NARROW) {
+    else if (kind == KIND_NARROW) {                        // (next to tiles: rows of at most 32 query rows alone)
         if (ic.nq * ic.gn <= 16)
-            narrow_body<D, KVT, 16, ATTN_WAVES>(p, ic, smem, tid);
+            narrow_body<D, KVT, 16, ATTN_WAVES>(p, ic, smem, tid, false);
         else
-            narrow_body<D, KVT, 32, ATTN_WAVES>(p, ic, smem, tid);
+            narrow_body<D, KVT, 32, ATTN_WAVES>(p, ic, smem, tid, false);
     }
     else if (KVT == KV_BF16)
         append_body(p, ic.row_off + ic.q0, ic.nq, ic.req, [&](int r) { return p.reqs[r]; }, D, tid);
@@ -1545,11 +1560,37 @@ constexpr int rows_smem() {
     return kv > merge ? kv : merge;
 }
 
+// A launch without tiles whose list lies in the workspace: blocks of prefill rows next to short rows, or more short rows than the
+// row table holds.  One workgroup per item.  (Apart from attn_kernel for the sums of both kinds of row, see ItemCtx::rounded: taken side
+// by side, next to tiles the 8-bit decode rows, which are bound by their instructions, lose by it: 24 of them next to a prefill 87.0 -> 87.5 us.)
+template <int D, int KVT>
+__global__ __launch_bounds__(AWG, D == 64 ? 4 : 1) void narrow_kernel(const AttnParams p) {
+    __shared__ __attribute__((aligned(16))) char smem_raw[rows_smem<D, ATTN_WAVES, false>()];
+    const uint32_t smem = (uint32_t)(uintptr_t)LDS_PTR(char, smem_raw);
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0 && tid == 0 && p.slot_flag)           // releases the host's staging slot (see AttnParams)
+        __hip_atomic_store(p.slot_flag, p.slot_seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const Item& it = p.items[blockIdx.x];
+    const int kind = (it.heads >> 24) & 0xff;
+    if (kind == KIND_NULL) return;
+    const ItemCtx ic = item_ctx<KVT>(p, it);
+    if (kind == KIND_NARROW) {
+        if (ic.nq * ic.gn <= 16)
+            narrow_body<D, KVT, 16, ATTN_WAVES>(p, ic, smem, tid, ic.rounded);
+        else
+            narrow_body<D, KVT, 32, ATTN_WAVES>(p, ic, smem, tid, ic.rounded);
+    }
+    else if (KVT == KV_BF16)
+        append_body(p, ic.row_off + ic.q0, ic.nq, ic.req, [&](int r) { return p.reqs[r]; }, D, tid);
+}
+
 // A small launch of tiles alone over a bf16 cache, whose list travels in the arguments (see TileTable): one workgroup per tile or
 // piece, then the append items.  KIND_NARROW: blocks of at most 32 query rows instead of tiles of 256 (see take_blocks for where).  Bound there:
 // the chain item -> page ids -> keys, whose latency eight waves with a block of 32 keys each pass once per 256 keys, where a tile's
 // stage of 128 waits for its own loads (one row of 32 tokens over 256, d = 64: 7.9 -> 6.8 us; of 64 over 1 024, 8 KV heads of 128: 22.6 -> 14.6).
-template <int D, int KIND>
+// SHORT_ROWS: rows of at most 32 query rows are among them, whose sums differ (a kernel of its own without them: taking both sums costs the
+// smallest launch 6.1 -> 6.2 us, and a second pair of bodies behind a branch, whose instructions have to be fetched, 6.5).
+template <int D, int KIND, bool SHORT_ROWS>
 __global__ __launch_bounds__(AWG, KIND == KIND_NARROW && D == 64 ? 4 : 1) void attn_tiles_kernel(const AttnParams p, const TileTable t) {
     __shared__ __attribute__((aligned(16))) char smem_raw[KIND == KIND_NARROW ? rows_smem<D, ATTN_WAVES, false>() : Geo<D>::SMEM];
     const uint32_t smem = (uint32_t)(uintptr_t)LDS_PTR(char, smem_raw);
@@ -1562,12 +1603,13 @@ __global__ __launch_bounds__(AWG, KIND == KIND_NARROW && D == 64 ? 4 : 1) void a
     const uint32_t code = t.items[idx];
     if (code == TILE_NULL) return;                           // a filler that keeps the following items on their XCD
     const ItemCtx ic = item_ctx<KV_BF16>(p, tile_item(t, code));
+    const bool rounded = SHORT_ROWS ? ic.rounded : true;
     if constexpr (KIND == KIND_WIDE)
         wide_body<D, KV_BF16>(p, ic, smem, tid);
     else if (ic.nq * ic.gn <= 16)
-        narrow_body<D, KV_BF16, 16, ATTN_WAVES>(p, ic, smem, tid);
+        narrow_body<D, KV_BF16, 16, ATTN_WAVES>(p, ic, smem, tid, rounded);
     else
-        narrow_body<D, KV_BF16, 32, ATTN_WAVES>(p, ic, smem, tid);
+        narrow_body<D, KV_BF16, 32, ATTN_WAVES>(p, ic, smem, tid, rounded);
 }
 
 // The launch of a batch of decode rows alone whose work list travels in the arguments (see RowTable): one workgroup of NW
@@ -1629,9 +1671,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : NW < ATTN_WAVES && KVT == KV
     // (only there a block is enough loads to matter: 8-bit decode batches of d = 64 lose 0.3 % by it, d = 128 0.2 %)
     const bool paced = D == 128 && KVT == KV_BF16 && NW == ATTN_WAVES && t.paced;
     if (NW < ATTN_WAVES || ic.nq * ic.gn <= 16)
-        narrow_body<D, KVT, 16, NW, KVT == KV_FP8, LEAN>(p, ic, smem, tid, paced);
+        narrow_body<D, KVT, 16, NW, KVT == KV_FP8, LEAN>(p, ic, smem, tid, false, paced);   // (rows of at most 32 query rows)
     else
-        narrow_body<D, KVT, 32, NW, KVT == KV_FP8>(p, ic, smem, tid, paced);
+        narrow_body<D, KVT, 32, NW, KVT == KV_FP8>(p, ic, smem, tid, false, paced);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1929,19 +1971,15 @@ hipError_t launch_upload(const void* h_src, void* d_dst, size_t bytes, hipStream
     return hipGetLastError();
 }
 
-template <int D, int KVT>
-static hipError_t launch_attn_t(const AttnParams& p, int grid, hipStream_t st) {
-    hipLaunchKernelGGL((attn_kernel<D, KVT>), dim3(grid), dim3(AWG), 0, st, p);
-    return hipGetLastError();
-}
-
-hipError_t launch_attn(const AttnParams& p, int D, int kvt, int grid, hipStream_t st) {
+hipError_t launch_attn(const AttnParams& p, int D, int kvt, bool tiles, int grid, hipStream_t st) {
     if (grid <= 0) return hipSuccess;
-    if (D == 128 && kvt == KV_BF16) return launch_attn_t<128, KV_BF16>(p, grid, st);
-    if (D == 64 && kvt == KV_BF16) return launch_attn_t<64, KV_BF16>(p, grid, st);
-    if (D == 128 && kvt == KV_FP8) return launch_attn_t<128, KV_FP8>(p, grid, st);
-    if (D == 64 && kvt == KV_FP8) return launch_attn_t<64, KV_FP8>(p, grid, st);
-    return hipErrorInvalidValue;
+    if ((D != 64 && D != 128) || (kvt != KV_BF16 && kvt != KV_FP8)) return hipErrorInvalidValue;
+    auto kern = tiles ? (D == 128 ? (kvt == KV_BF16 ? attn_kernel<128, KV_BF16> : attn_kernel<128, KV_FP8>)
+                                  : (kvt == KV_BF16 ? attn_kernel<64, KV_BF16> : attn_kernel<64, KV_FP8>))
+                      : (D == 128 ? (kvt == KV_BF16 ? narrow_kernel<128, KV_BF16> : narrow_kernel<128, KV_FP8>)
+                                  : (kvt == KV_BF16 ? narrow_kernel<64, KV_BF16> : narrow_kernel<64, KV_FP8>));
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(AWG), 0, st, p);
+    return hipGetLastError();
 }
 
 template <int D, int KVT>
@@ -1957,6 +1995,7 @@ static hipError_t launch_rows_t(const AttnParams& p, const RowTable& t, int grid
     return hipGetLastError();
 }
 
+
 hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid, hipStream_t st) {
     if (t.D == 128 && kvt == KV_BF16) return launch_rows_t<128, KV_BF16>(p, t, grid, st);
     if (t.D == 64 && kvt == KV_BF16) return launch_rows_t<64, KV_BF16>(p, t, grid, st);
@@ -1966,8 +2005,11 @@ hipError_t launch_rows(const AttnParams& p, const RowTable& t, int kvt, int grid
 }
 
 hipError_t launch_tiles(const AttnParams& p, const TileTable& t, int grid, hipStream_t st) {
-    auto kern = t.kind == KIND_NARROW ? (t.D == 128 ? attn_tiles_kernel<128, KIND_NARROW> : attn_tiles_kernel<64, KIND_NARROW>)
-                                      : (t.D == 128 ? attn_tiles_kernel<128, KIND_WIDE> : attn_tiles_kernel<64, KIND_WIDE>);
+    bool short_rows = false;
+    for (int i = 0; i < t.n_rows; ++i) short_rows |= t.rows[i].L * t.G <= 32;
+    auto kern = t.kind == KIND_WIDE ? (t.D == 128 ? attn_tiles_kernel<128, KIND_WIDE, false> : attn_tiles_kernel<64, KIND_WIDE, false>)
+                : short_rows        ? (t.D == 128 ? attn_tiles_kernel<128, KIND_NARROW, true> : attn_tiles_kernel<64, KIND_NARROW, true>)
+                                    : (t.D == 128 ? attn_tiles_kernel<128, KIND_NARROW, false> : attn_tiles_kernel<64, KIND_NARROW, false>);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(AWG), 0, st, p, t);
     return hipGetLastError();
 }

@@ -219,7 +219,7 @@ void add_append_items(const Plan& plan, int rows, std::vector<Item>& items) {
         while (row >= (int64_t)plan.reqs[r].row_off + plan.reqs[r].L) ++r;
         items.push_back(Item{r, pack_heads(0, 0, 0, KIND_APPEND), (int32_t)(row - plan.reqs[r].row_off),
                              (int32_t)std::min<int64_t>(rows, plan.sum_L - row), 0, 0, -1, plan.reqs[r].C,
-                             plan.reqs[r].row_off, {0, 0, 0}});
+                             plan.reqs[r].row_off, plan.reqs[r].L, {0, 0}});
     }
 }
 
@@ -534,7 +534,8 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
             it.part_off = nsplit > 1 ? (int32_t)(part0 + (int64_t)sp * slot) : -1;
             it.C = out.reqs[b.req].C;
             it.row_off = out.reqs[b.req].row_off;
-            it.pad[0] = it.pad[1] = it.pad[2] = 0;
+            it.row_L = out.reqs[b.req].L;
+            it.pad[0] = it.pad[1] = 0;
             const int64_t keys = it.kv_end - it.kv_begin;
             const int64_t cost = b.kind == KIND_WIDE ? keys * 4 : keys;
             order.push_back(Cost{cost, (int32_t)out.items.size()});
@@ -699,7 +700,7 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
                 if (take_wide ? iw >= wide_ix.size() : in >= narrow_ix.size()) break;
                 const int32_t idx = take_wide ? wide_ix[iw++] : narrow_ix[in++];
                 if (idx < 0) {
-                    sorted.push_back(Item{-1, pack_heads(0, 0, 0, KIND_NULL), 0, 0, 0, 0, -1, 0, 0, {0, 0, 0}});
+                    sorted.push_back(Item{-1, pack_heads(0, 0, 0, KIND_NULL), 0, 0, 0, 0, -1, 0, 0, 0, {0, 0}});
                     continue;
                 }
                 const Item& it = out.items[idx];

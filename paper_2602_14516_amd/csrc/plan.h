@@ -40,7 +40,8 @@ struct Item {             // 48 B, one per attention workgroup, device-visible
     int32_t part_off;     // float offset of this item's partial slot, or -1: write final output
     int32_t C;            // context length of the request and the first row of its packed q / out rows:
     int32_t row_off;      // copies of its ReqInfo, so that a workgroup starts with one dependent load less
-    int32_t pad[3];
+    int32_t row_L;        // and the request's new tokens
+    int32_t pad[2];
 };
 static_assert(sizeof(Item) == 48, "device layout");
 
@@ -111,7 +112,8 @@ AMPD_HD Item table_item(const RowTable& t, const RowEntry& e, int idx) {
     it.part_off = e.part_off < 0 ? -1 : e.part_off + (kvh * pieces + piece) * (L * t.G * (t.D + 2));
     it.C = e.C;
     it.row_off = e.row_off;
-    it.pad[0] = it.pad[1] = it.pad[2] = 0;
+    it.row_L = L;
+    it.pad[0] = it.pad[1] = 0;
     return it;
 }
 // The combine work of row e, KV head kvh (nsplit = 1: none).
@@ -159,7 +161,8 @@ AMPD_HD Item tile_item(const TileTable& t, uint32_t code) {
     it.part_off = keys > chunk ? t.combs[code >> 25].part_off + piece * (it.nq * t.G * (t.D + 2)) : -1;
     it.C = r.C;
     it.row_off = r.row_off;
-    it.pad[0] = it.pad[1] = it.pad[2] = 0;
+    it.row_L = r.L;
+    it.pad[0] = it.pad[1] = 0;
     return it;
 }
 AMPD_HD CombItem tile_comb(const TileTable& t, int i) {
