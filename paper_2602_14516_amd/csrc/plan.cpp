@@ -2,7 +2,6 @@
 #include "plan.h"
 
 #include <algorithm>
-#include <array>
 #include <utility>
 
 namespace ampd {
@@ -23,9 +22,30 @@ constexpr int NUM_XCD = NUM_QUEUES;   // accelerator dies; workgroup i is dispat
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-struct QBlock {            // a query block before splitting
-    int32_t req, heads, q0, nq, nkeys, rows, kind;
-};
+struct Cost { int64_t cost; int32_t idx, piece; };      // of an item: its index (or its block's, and which piece of it)
+
+// Longest first, equal ones in the order they have (a library sort with a comparison took a third of planning a launch of 500 items).
+void longest_first(std::vector<Cost>& v) {
+    if (v.size() <= 32) {
+        for (size_t i = 1; i < v.size(); ++i) {
+            const Cost c = v[i];
+            size_t j = i;
+            for (; j > 0 && v[j - 1].cost < c.cost; --j) v[j] = v[j - 1];
+            v[j] = c;
+        }
+        return;
+    }
+    int64_t most = 0;
+    for (const Cost& c : v) most = std::max(most, c.cost);
+    std::vector<Cost> to(v.size());
+    for (int shift = 0; most >> shift; shift += 8) {               // by the digits of what a cost lacks to the largest one
+        int32_t at[257] = {0};
+        for (const Cost& c : v) ++at[((most - c.cost) >> shift & 255) + 1];
+        for (int i = 1; i < 256; ++i) at[i] += at[i - 1];
+        for (const Cost& c : v) to[at[(most - c.cost) >> shift & 255]++] = c;
+        v.swap(to);
+    }
+}
 
 }  // namespace
 
@@ -44,118 +64,288 @@ bool take_blocks(const Shape& s, const std::vector<ReqInfo>& reqs, const PlanOpt
     const int tq = 32 / (s.Hq / s.Hkv), tile = ATTN_WAVES * tq;
     const bool d64 = s.D == 64, fp8 = opt.kv_bytes == 1;
     const int64_t slots = opt.wg_slots;
-    struct Run { int32_t keys; int64_t n; };                   // n blocks or tiles of about that many keys
-    std::vector<Run> runs, few, full, half;                    // few: rows that are one block either way, cut by the rule for decode
-    int64_t n_blocks = 0, longest_full = 0, longest_half = 0;  // rows; half: tiles of at most 128 query rows, half the work a stage
+    int64_t n_blocks = 0;
+    bool any = false;
     for (const ReqInfo& r : reqs) {
         if (r.L <= 0) continue;
-        const int64_t nb = ceil_div(r.L, tq) * s.Hkv, nt = ceil_div(r.L, tile);
-        n_blocks += nb;
+        n_blocks += r.L <= tq ? s.Hkv : ceil_div(r.L, tq) * s.Hkv;
         if (n_blocks > (fp8 ? 2 : 1) * slots) return false;
-        (r.L <= tq ? few : runs).push_back(Run{r.C + r.L, nb});
+        any |= r.L > tq;
+    }
+    if (!any) return false;
+    struct Run { int32_t keys; uint32_t units; int32_t n; };   // n blocks or tiles of about that many keys: units of 256 or 128 keys
+    std::vector<Run> list;                                     // rows of more than one block, as blocks; the others (few); tiles
+    list.reserve(3 * reqs.size());
+    auto add = [&](int32_t keys, int32_t unit, int64_t n) { list.push_back(Run{keys, (uint32_t)ceil_div(keys, unit), (int32_t)n}); };
+    for (const ReqInfo& r : reqs)
+        if (r.L > tq) add(r.C + r.L, 256, ceil_div(r.L, tq) * s.Hkv);
+    const size_t n_runs = list.size();
+    for (const ReqInfo& r : reqs)                              // cut by the rule for decode
+        if (r.L > 0 && r.L <= tq) add(r.C + r.L, 256, s.Hkv);
+    const size_t n_few = list.size();
+    int64_t n_tiles[2] = {0, 0}, tile_units = 0;               // full tiles; tiles of at most 128 query rows, half the work a stage
+    uint32_t longest[2] = {0, 0};                              // in stages
+    for (const ReqInfo& r : reqs) {
         if (r.L <= tq) continue;
-        const bool last_half = 2 * (r.L - (nt - 1) * tile) <= tile;
-        if (nt > last_half) {
-            full.push_back(Run{r.C + r.L, (nt - last_half) * s.Hkv});
-            longest_full = std::max<int64_t>(longest_full, r.C + r.L);
-        }
-        if (last_half) {
-            half.push_back(Run{nt > 1 ? r.C + r.L % tile : r.C + r.L, s.Hkv});
-            longest_half = std::max<int64_t>(longest_half, half.back().keys);
+        const int32_t nt = (int32_t)ceil_div(r.L, tile), rest = r.L - (nt - 1) * tile, half = 2 * rest <= tile;
+        for (int h = 0; h < 2; ++h) {
+            const int32_t n = (h ? half : nt - half) * s.Hkv;
+            if (n == 0) continue;
+            add(h && nt > 1 ? r.C + r.L % tile : r.C + r.L, WIDE_STAGE_KEYS, h ? -n : n);
+            n_tiles[h] += n;
+            tile_units += (int64_t)list.back().units * n;
+            longest[h] = std::max(longest[h], list.back().units);
         }
     }
-    if (full.empty() && half.empty()) return false;
-    auto pieces = [](const std::vector<Run>& v, int64_t chunk) {
+    const Run *runs = list.data(), *few = runs + n_runs, *tiles = runs + n_few, *end = runs + list.size();
+    auto pieces = [](const Run* i, const Run* e, uint32_t units) {      // of `units` units each
         int64_t n = 0;
-        for (const Run& r : v) n += ceil_div(r.keys, chunk) * r.n;
+        for (; i != e; ++i) n += (int64_t)((i->units + units - 1) / units) * i->n;
         return n;
     };
+    // Both searches start from the uncut launch and end where the longest piece alone is no better than the best so far.
     // blocks: rounds of 256 keys, whole or in pieces that fit one round (and the table); the pieces of a row's blocks read its
     // keys from the memory-side cache, at 8 TB/s
-    const int64_t round_ns = d64 ? 1030 : 1750;
-    auto price = [&](const std::vector<Run>& v, int64_t* chunk) {
-        int64_t blocks = 0, longest = 0, bytes = 0, best = -1;
-        for (const Run& r : v) {
-            blocks += r.n;
-            longest = std::max<int64_t>(longest, r.keys);
-            bytes += r.keys * r.n * 2 * s.D * opt.kv_bytes;
+    const int64_t round_ns = d64 ? 1030 : 1750, start_ns = d64 ? 4700 : 6500;
+    auto price = [&](const Run* v, const Run* e, int64_t* chunk) {
+        int64_t blocks = 0, bytes = 0, units = 0;
+        uint32_t longest = 0;
+        for (const Run* i = v; i != e; ++i) {
+            longest = std::max(longest, i->units);
+            blocks += i->n;
+            units += (int64_t)i->units * i->n;
+            bytes += (int64_t)i->keys * i->n * 2 * s.D * opt.kv_bytes;
         }
-        for (int64_t rounds = 1;; rounds += 1 + rounds / 8) {
-            const bool whole = 256 * rounds >= longest;
-            const int64_t n = whole ? blocks : pieces(v, 256 * rounds);
-            if (whole || (n <= slots && blocks <= TILE_TABLE_COMBS)) {
-                const int64_t one = std::min(rounds, ceil_div(longest, 256)) * round_ns;
-                const int64_t all = n > slots ? pieces(v, 256) * round_ns * 11 / (10 * slots) + 1000 : 0;     // (several rounds end unevenly)
-                const int64_t cost = (d64 ? 4700 : 6500) + n * 5 + (whole ? std::max(one, all) : std::max(one, bytes / 8000) + 4000 + n * 8);
-                if (best < 0 || cost < best) {
-                    best = cost;
-                    *chunk = whole ? 1 << 30 : 256 * rounds;
-                }
+        const int64_t all = blocks > slots ? units * round_ns * 11 / (10 * slots) + 1000 : 0;      // (several rounds end unevenly)
+        int64_t best = start_ns + 5 * blocks + std::max<int64_t>(longest * round_ns, all);
+        *chunk = 1 << 30;
+        if (blocks > TILE_TABLE_COMBS) return best;
+        for (uint32_t rounds = 1; rounds < longest; rounds += 1 + rounds / 8) {
+            if (start_ns + rounds * round_ns + 4000 + 13 * blocks > best) break;
+            if (units > slots * rounds) continue;
+            const int64_t n = pieces(v, e, rounds);
+            if (n > slots) continue;
+            const int64_t cost = start_ns + std::max(rounds * round_ns, bytes / 8000) + 4000 + 13 * n;
+            if (cost < best || (cost == best && *chunk == 1 << 30)) {
+                best = cost;
+                *chunk = 256 * (int64_t)rounds;
             }
-            if (whole) return best;
         }
+        return best;
     };
-    int64_t best = price(runs, chunk_out);
+    int64_t best = price(runs, few, chunk_out);
     // tiles: stages of 128 keys, whole or in pieces of four stages or more that fit one round
-    int64_t best_tiles = -1;
-    for (int64_t stages = 4;; stages += 1 + stages / 8) {
-        const int64_t chunk = WIDE_STAGE_KEYS * stages;
-        const bool whole = chunk >= std::max(longest_full, longest_half);
-        const int64_t nf = pieces(full, chunk), nh = pieces(half, chunk);
-        if (whole || nf + nh <= slots) {
-            const int64_t full_ns = (d64 ? 1950 : 3000) + (2 * nf + nh) * (d64 ? 50 : 200) / slots, half_ns = d64 ? 1050 : 1650;
-            const int64_t work = std::max(std::min(stages, ceil_div(longest_full, WIDE_STAGE_KEYS)) * full_ns,
-                                          std::min(stages, ceil_div(longest_half, WIDE_STAGE_KEYS)) * half_ns);
-            const int64_t cost = (d64 ? 5200 : 6600) + work * (fp8 ? 23 : 20) / 20 + (fp8 ? 1200 : 0) + (whole ? 0 : 4000 + (2 * nf + nh) * (d64 ? 12 : 22));
-            if (best_tiles < 0 || cost < best_tiles) best_tiles = cost;
+    const int64_t full_ns = d64 ? 1950 : 3000, half_ns = d64 ? 1050 : 1650, extra_ns = d64 ? 50 : 200, piece_ns = d64 ? 12 : 22;
+    auto tile_cost = [&](uint32_t stages, int64_t nf, int64_t nh) {
+        const int64_t work = std::max(std::min(stages, longest[0]) * (full_ns + (2 * nf + nh) * extra_ns / slots), std::min(stages, longest[1]) * half_ns);
+        return (d64 ? 5200 : 6600) + work * (fp8 ? 23 : 20) / 20 + (fp8 ? 1200 : 0);
+    };
+    const uint32_t longest_tile = std::max(longest[0], longest[1]);
+    int64_t best_tiles = tile_cost(longest_tile, n_tiles[0], n_tiles[1]);
+    for (uint32_t stages = 4; stages < longest_tile; stages += 1 + stages / 8) {
+        if (tile_cost(stages, n_tiles[0], n_tiles[1]) >= best_tiles) break;
+        if (tile_units > slots * stages) continue;
+        int64_t nf = 0, nh = 0;
+        for (const Run* i = tiles; i != end; ++i) {
+            const int64_t n = (int64_t)((i->units + stages - 1) / stages) * i->n;
+            (n > 0 ? nf : nh) += n > 0 ? n : -n;
         }
-        if (whole) break;
+        if (nf + nh <= slots) best_tiles = std::min(best_tiles, tile_cost(stages, nf, nh) + 4000 + (2 * nf + nh) * piece_ns);
     }
-    if (!few.empty()) {
+    if (few != tiles) {
         // Next to decode rows: only where the tiles last longer than those would alone (otherwise the launch is a matter of cutting
         // the decode rows well: 76 rows of 2.5-6 k tokens next to two of up to 30 34.5 -> 43.6); tiles would need a list in the
         // workspace there (bf16: an upload launch).
         int64_t chunk;
-        const int64_t others = price(few, &chunk);
+        const int64_t others = price(few, tiles, &chunk);
         if (others > best_tiles) return false;
-        best = std::max(std::max(best, others), (d64 ? 4700 : 6500) + (pieces(runs, 256) + pieces(few, 256)) * round_ns * 11 / (10 * slots) + 1000);
+        best = std::max(std::max(best, others), start_ns + pieces(runs, tiles, 1) * round_ns * 11 / (10 * slots) + 1000);
         best_tiles += fp8 ? 0 : 4000;
     }
     return 100 * best <= 97 * best_tiles;
 }
 
-// The launch order of blocks that fit one round: the eight that would make one tile read the same keys at the same rate, so they go
-// next to each other on one die, as tiles of one stream do; -1 pads the shorter dies' queues.  False when a die would get more of them
-// than it has slots.
-bool order_blocks(const std::vector<Item>& items, int G, int64_t slots, std::vector<int32_t>& ix) {
-    const int tile = ATTN_WAVES * (32 / G);
-    if ((int64_t)items.size() > slots) return false;
-    std::vector<std::pair<std::array<int32_t, 4>, int32_t>> by_key;    // (row, KV head, piece, tile): items of one group
-    for (size_t i = 0; i < items.size(); ++i) {
-        const Item& it = items[i];
-        by_key.push_back({{it.req, it.heads & 0xff, it.kv_begin, it.q0 / tile}, (int32_t)i});
+// Append items: consecutive runs of packed rows, whatever request they belong to (a decode batch of 96 rows is two items,
+// not 96); each names the request and token its first row belongs to.
+void add_append_items(const Plan& plan, int rows, std::vector<Item>& items) {
+    int r = 0;
+    for (int64_t row = 0; row < plan.sum_L; row += rows) {
+        while (row >= (int64_t)plan.reqs[r].row_off + plan.reqs[r].L) ++r;
+        items.push_back(Item{r, pack_heads(0, 0, 0, KIND_APPEND), (int32_t)(row - plan.reqs[r].row_off),
+                             (int32_t)std::min<int64_t>(rows, plan.sum_L - row), 0, 0, -1, plan.reqs[r].C,
+                             plan.reqs[r].row_off, plan.reqs[r].L, {0, 0}});
     }
-    std::stable_sort(by_key.begin(), by_key.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
-    std::vector<std::vector<int32_t>> groups;
-    for (size_t i = 0; i < by_key.size(); ++i) {
-        if (i == 0 || by_key[i].first != by_key[i - 1].first) groups.emplace_back();
-        groups.back().push_back(by_key[i].second);
+}
+
+Item null_item() { return Item{-1, pack_heads(0, 0, 0, KIND_NULL), 0, 0, 0, 0, -1, 0, 0, 0, {0, 0}}; }
+
+// What a tile table says of the launch as a whole, and its rows; false when it has no room for them.  row_of (one entry per request):
+// the table's row.
+bool begin_tiles(const Shape& s, int32_t chunk, int32_t few_chunk, bool blocks, const Plan& out, TileTable& t, std::vector<int32_t>& row_of) {
+    const int G = s.Hq / s.Hkv;
+    if (G > 32 || s.Hkv > 64 || out.combs.size() > (size_t)TILE_TABLE_COMBS) return false;
+    t.n_rows = 0;
+    t.n_combs = (int32_t)out.combs.size();
+    t.chunk = chunk;
+    t.few_chunk = few_chunk;
+    t.tq = (blocks ? 1 : ATTN_WAVES) * (32 / G);
+    t.kind = blocks ? KIND_NARROW : KIND_WIDE;
+    t.G = G;
+    t.D = s.D;
+    t.sum_L = (int32_t)out.sum_L;
+    // These launches end with their append items, so an item is small: two 16-byte chunks of K and of V per thread, one trip to
+    // memory (one prefill of 509 tokens over 8 heads of 128, 64 rows an item -> 16 -> 8: 59.6 -> 53.8 -> 53.2 us on the GPU).
+    t.append_rows = std::max(4, std::min(APPEND_ITEM_ROWS, 8192 / (s.Hkv * s.D)));
+    row_of.assign(out.reqs.size(), -1);
+    for (const ReqInfo& r : out.reqs) {
+        if (r.L <= 0) continue;
+        if (t.n_rows == TILE_TABLE_ROWS) return false;
+        row_of[r.req] = t.n_rows;
+        t.rows[t.n_rows++] = r;
     }
-    std::stable_sort(groups.begin(), groups.end(), [](const auto& a, const auto& b) { return a.size() > b.size(); });
-    std::vector<int32_t> queue[NUM_XCD];
-    size_t longest = 0;
-    for (const auto& g : groups) {
-        int best = 0;
-        for (int x = 1; x < NUM_XCD; ++x)
-            if (queue[x].size() < queue[best].size()) best = x;
-        queue[best].insert(queue[best].end(), g.begin(), g.end());
-        longest = std::max(longest, queue[best].size());
-    }
-    if ((int64_t)longest > slots / NUM_XCD) return false;
-    for (size_t j = 0; j < longest; ++j)
-        for (int x = 0; x < NUM_XCD; ++x) ix.push_back(j < queue[x].size() ? queue[x][j] : -1);
-    while (!ix.empty() && ix.back() < 0) ix.pop_back();
     return true;
+}
+
+// A launch of blocks (out.reqs holds the rows): items, combine tiles, launch order.  In a launch that fits one round the blocks that
+// would make one tile read the same keys at the same rate, so they go next to each other on one die, as tiles of one stream do, larger
+// groups first, each to the shortest queue; null items pad the shorter dies' queues.  Where that is more than a round, or more on
+// a die than it has slots: longest first.  All KV heads of a row are alike and its groups are known when the blocks are made, so no
+// more than one head's items is ever sorted, and a list that travels in the arguments is written as its codes straight away: planning
+// 256 tokens over 2 048 (8 KV heads) takes 1.7 us; the launch as tiles took 13, blocks by sorted items and a vector per group 34.
+void build_blocks(const Shape& s, int32_t chunk, int32_t few_chunk, const PlanOptions& opt, Plan& out) {
+    const int G = s.Hq / s.Hkv, tq = 32 / G, tile = ATTN_WAVES * tq, slots = opt.wg_slots;
+    struct Block { int32_t req, q0, nq, pieces; };             // of one KV head
+    struct Row { int32_t block0, block1, group0, group1, chunk; };
+    std::vector<Block> blocks;
+    std::vector<Row> rows;
+    blocks.reserve(slots);
+    rows.reserve(out.reqs.size());
+    int64_t items = 0;
+    for (const ReqInfo& r : out.reqs) {
+        if (r.L <= 0) continue;
+        Row row{(int32_t)blocks.size(), 0, 0, 0, r.L <= tq ? few_chunk : chunk};
+        const int32_t rest = r.L % tq;
+        for (int q0 = 0, nq = rest ? rest : tq; q0 < r.L; q0 += nq, nq = tq) {
+            blocks.push_back(Block{r.req, q0, nq, (int32_t)ceil_div(r.C + q0 + nq, row.chunk)});
+            items += (int64_t)blocks.back().pieces * s.Hkv;
+        }
+        row.block1 = (int32_t)blocks.size();
+        rows.push_back(row);
+    }
+
+    struct Place { int32_t block, kvh, piece; };
+    std::vector<Place> launch;
+    auto by_die = [&]() {
+        struct Group { int32_t block, n, piece; };             // piece `piece` of blocks [block, block + n)
+        std::vector<Group> groups;
+        groups.reserve(slots);
+        uint32_t sizes = 0;                                    // of groups, one bit each (at most 9: the first block may be a remainder)
+        for (Row& row : rows) {
+            row.group0 = (int32_t)groups.size();
+            for (int piece = 0; piece < blocks[row.block1 - 1].pieces; ++piece)
+                for (int i = row.block0, j = i; i < row.block1; i = j) {
+                    const int tile_end = (blocks[i].q0 / tile + 1) * tile;
+                    while (j < row.block1 && blocks[j].q0 < tile_end) ++j;
+                    while (i < j && blocks[i].pieces <= piece) ++i;     // (later blocks see more keys)
+                    if (i == j) continue;
+                    groups.push_back(Group{i, j - i, piece});
+                    sizes |= 1u << (j - i);
+                }
+            row.group1 = (int32_t)groups.size();
+        }
+        launch.assign(slots, Place{-1, 0, 0});
+        int queue[NUM_XCD] = {0}, n = 0;
+        for (int size = 31; size > 0; --size) {
+            if (!(sizes >> size & 1)) continue;
+            for (const Row& row : rows)
+                for (int kvh = 0; kvh < s.Hkv; ++kvh)
+                    for (int g = row.group0; g < row.group1; ++g) {
+                        if (groups[g].n != size) continue;
+                        int x = 0;
+                        for (int y = 1; y < NUM_XCD; ++y)
+                            if (queue[y] < queue[x]) x = y;
+                        if (queue[x] + size > slots / NUM_XCD) return false;
+                        for (int k = 0; k < size; ++k) launch[queue[x]++ * NUM_XCD + x] = Place{groups[g].block + k, kvh, groups[g].piece};
+                        n = std::max(n, (queue[x] - 1) * NUM_XCD + x + 1);
+                    }
+        }
+        launch.resize(n);
+        return true;
+    };
+    if (items > slots || !by_die()) {
+        std::vector<Cost> order;                               // KV head 0
+        order.reserve(items / s.Hkv);
+        for (const Row& row : rows)
+            for (int i = row.block0; i < row.block1; ++i) {
+                int32_t keys = out.reqs[blocks[i].req].C + blocks[i].q0 + blocks[i].nq;
+                for (int piece = 0; piece < blocks[i].pieces; ++piece, keys -= row.chunk) order.push_back(Cost{std::min(keys, row.chunk), i, piece});
+            }
+        longest_first(order);
+        launch.resize(items);
+        Place* to = launch.data();
+        for (size_t i = 0, j = 0; i < order.size(); i = j) {   // equal ones of a row, head by head
+            const int32_t req = blocks[order[i].idx].req;
+            while (j < order.size() && order[j].cost == order[i].cost && blocks[order[j].idx].req == req) ++j;
+            for (int kvh = 0; kvh < s.Hkv; ++kvh)
+                for (size_t k = i; k < j; ++k) *to++ = Place{order[k].idx, kvh, order[k].piece};
+        }
+    }
+    const int n = (int)launch.size();
+
+    std::vector<int32_t> comb_of(blocks.size() * s.Hkv, -1);   // [KV head][block]
+    int32_t max_pieces = 0, max_blocks = 0;
+    for (const Row& row : rows) {
+        max_blocks = std::max(max_blocks, row.block1 - row.block0);
+        for (int kvh = 0; kvh < s.Hkv; ++kvh)
+            for (int i = row.block0; i < row.block1; ++i) {
+                const Block& b = blocks[i];
+                if (b.pieces == 1) continue;
+                max_pieces = std::max(max_pieces, b.pieces);
+                const int32_t slot = b.nq * G * (s.D + 2);
+                comb_of[kvh * blocks.size() + i] = (int32_t)out.combs.size();
+                out.combs.push_back(CombItem{b.req, pack_heads(kvh, 0, G, KIND_NARROW), b.q0, b.nq, (int32_t)out.partial_floats, b.pieces, slot, 0});
+                out.partial_floats += (int64_t)slot * b.pieces;
+            }
+    }
+    out.num_narrow = items;
+
+    std::vector<int32_t> row_of;
+    TileTable& t = out.tiles;
+    if (opt.kv_bytes == 2 && n <= TILE_TABLE_ITEMS && max_pieces <= 128 && max_blocks <= 256 && begin_tiles(s, chunk, few_chunk, true, out, t, row_of)) {
+        auto code_of = [&](int32_t i, int32_t kvh, int32_t piece, int32_t comb) {
+            const int32_t row = row_of[blocks[i].req];
+            return (uint32_t)row | (uint32_t)kvh << 4 | (uint32_t)(i - rows[row].block0) << 10 | (uint32_t)piece << 18 | (uint32_t)comb << 25;
+        };
+        t.n_items = n;
+        for (int i = 0; i < n; ++i) {
+            const Place& e = launch[i];
+            t.items[i] = e.block < 0 ? TILE_NULL : code_of(e.block, e.kvh, e.piece, std::max(0, comb_of[e.kvh * blocks.size() + e.block]));
+        }
+        for (const Row& row : rows)
+            for (int kvh = 0; kvh < s.Hkv && t.n_combs > 0; ++kvh)
+                for (int i = row.block0; i < row.block1; ++i) {
+                    const int32_t comb = comb_of[kvh * blocks.size() + i];
+                    if (comb >= 0) t.combs[comb] = TileComb{code_of(i, kvh, 0, 0), out.combs[comb].part_off};
+                }
+        out.by_tiles = true;
+        return;
+    }
+    out.items.reserve(n + (opt.append_items ? ceil_div(out.sum_L, APPEND_ITEM_ROWS) : 0));
+    for (const Place& e : launch) {
+        if (e.block < 0) {
+            out.items.push_back(null_item());
+            continue;
+        }
+        const Block& b = blocks[e.block];
+        const ReqInfo& r = out.reqs[b.req];
+        const int32_t comb = comb_of[e.kvh * blocks.size() + e.block], ch = r.L <= tq ? few_chunk : chunk, keys = r.C + b.q0 + b.nq;
+        Item it{b.req, pack_heads(e.kvh, 0, G, KIND_NARROW), b.q0, b.nq, e.piece * ch, keys, -1, r.C, r.row_off, r.L, {0, 0}};
+        if (comb >= 0) {
+            it.kv_end = std::min(keys - it.kv_begin, ch) + it.kv_begin;
+            it.part_off = out.combs[comb].part_off + e.piece * out.combs[comb].part_stride;
+        }
+        out.items.push_back(it);
+    }
 }
 
 // The row table of a batch of decode rows alone (out.reqs holds the rows).
@@ -211,51 +401,19 @@ void build_table(const Shape& s, int32_t chunk, const PlanOptions& opt, Plan& ou
     out.total_bytes = std::max<int64_t>(256, round_up(out.partial_floats * 4, 256));
 }
 
-// Append items: consecutive runs of packed rows, whatever request they belong to (a decode batch of 96 rows is two items,
-// not 96); each names the request and token its first row belongs to.
-void add_append_items(const Plan& plan, int rows, std::vector<Item>& items) {
-    int r = 0;
-    for (int64_t row = 0; row < plan.sum_L; row += rows) {
-        while (row >= (int64_t)plan.reqs[r].row_off + plan.reqs[r].L) ++r;
-        items.push_back(Item{r, pack_heads(0, 0, 0, KIND_APPEND), (int32_t)(row - plan.reqs[r].row_off),
-                             (int32_t)std::min<int64_t>(rows, plan.sum_L - row), 0, 0, -1, plan.reqs[r].C,
-                             plan.reqs[r].row_off, plan.reqs[r].L, {0, 0}});
-    }
-}
-
-// The tile table of a plan of uncut or evenly cut tiles (out.items without append items, out.combs in the order of their
+// The tile table of a launch of uncut or evenly cut tiles (out.items without append items, out.combs in the order of their
 // partial results); false when it does not fit.
-bool build_tiles(const Shape& s, int32_t chunk, int32_t few_chunk, bool blocks, Plan& out) {
+bool build_tiles(const Shape& s, int32_t chunk, Plan& out) {
     TileTable& t = out.tiles;
-    const int G = s.Hq / s.Hkv;
-    if ((blocks ? out.num_wide : out.num_narrow) > 0 || G > 32 || s.Hkv > 64 || out.items.size() > (size_t)TILE_TABLE_ITEMS ||
-        out.combs.size() > (size_t)TILE_TABLE_COMBS)
+    std::vector<int32_t> row_of;
+    if (out.num_narrow > 0 || out.items.size() > (size_t)TILE_TABLE_ITEMS || !begin_tiles(s, chunk, 1 << 30, false, out, t, row_of))
         return false;
-    t.n_rows = 0;
-    t.chunk = chunk;
-    t.few_chunk = few_chunk;
-    t.tq = (blocks ? 1 : ATTN_WAVES) * (32 / G);
-    t.kind = blocks ? KIND_NARROW : KIND_WIDE;
-    t.G = G;
-    t.D = s.D;
-    t.sum_L = (int32_t)out.sum_L;
-    // These launches end with their append items, so an item is small: two 16-byte chunks of K and of V per thread, one trip to
-    // memory (one prefill of 509 tokens over 8 heads of 128, 64 rows an item -> 16 -> 8: 59.6 -> 53.8 -> 53.2 us on the GPU).
-    t.append_rows = std::max(4, std::min(APPEND_ITEM_ROWS, 8192 / (s.Hkv * s.D)));
-    std::vector<int32_t> row_of(out.reqs.size(), -1);
-    for (const ReqInfo& r : out.reqs) {
-        if (r.L <= 0) continue;
-        if (t.n_rows == TILE_TABLE_ROWS) return false;
-        row_of[r.req] = t.n_rows;
-        t.rows[t.n_rows++] = r;
-    }
     bool fits = true;                      // (a row of more than 256 tiles, a tile of more than 128 pieces: no)
     auto code_of = [&](int32_t req, int32_t heads, int32_t q0, int32_t nq, int32_t kv_begin) {
         const uint32_t tile = q0 == 0 ? 0 : (uint32_t)((q0 + nq + t.tq - 1) / t.tq - 1);   // (the first tile holds the remainder)
         if (tile > 255) fits = false;
-        return (uint32_t)row_of[req] | (uint32_t)(heads & 0xff) << 4 | tile << 10 | (uint32_t)(kv_begin / tile_chunk(t, out.reqs[req].L)) << 18;
+        return (uint32_t)row_of[req] | (uint32_t)(heads & 0xff) << 4 | tile << 10 | (uint32_t)(kv_begin / chunk) << 18;
     };
-    t.n_combs = (int32_t)out.combs.size();
     for (int i = 0; i < t.n_combs; ++i) {
         const CombItem& c = out.combs[i];
         if (c.nsplit > 128) return false;
@@ -277,14 +435,46 @@ bool build_tiles(const Shape& s, int32_t chunk, int32_t few_chunk, bool blocks, 
     return fits;
 }
 
+// Append items, launch size and byte layout of a plan whose attention items (or tile table) and combine tiles are there.
+void finish_plan(const PlanOptions& opt, Plan& out) {
+    out.num_combs = (int64_t)out.combs.size();
+    if (opt.append_items) out.num_append = ceil_div(out.sum_L, out.by_tiles ? out.tiles.append_rows : APPEND_ITEM_ROWS);
+    if (out.by_tiles) {
+        out.items.clear();
+        out.num_items = out.tiles.n_items + out.num_append;
+        out.grid = (int32_t)out.num_items;
+        out.total_bytes = std::max<int64_t>(256, round_up(out.partial_floats * 4, 256));
+        return;
+    }
+    if (opt.append_items) add_append_items(out, APPEND_ITEM_ROWS, out.items);
+    out.num_items = (int64_t)out.items.size();
+    out.off_reqs = 0;
+    out.off_items = round_up((int64_t)out.reqs.size() * sizeof(ReqInfo), 256);
+    out.off_combs = out.off_items + round_up((int64_t)out.items.size() * sizeof(Item), 256);
+    out.off_queues = out.off_combs + round_up((int64_t)out.combs.size() * sizeof(CombItem), 256);
+    out.plan_bytes = out.off_queues + 256;
+    // persistent workgroups pay off where tiles are in the launch (the dies finish together: -1.2 % on configuration 2, -3.5 % on
+    // the fused mixed launch of configuration 3); a launch of decode rows alone gains nothing from them (+-1 %)
+    out.grid = (int32_t)(out.num_wide > 0 ? std::min<int64_t>((int64_t)out.items.size(), opt.wg_slots) : (int64_t)out.items.size());
+    for (int q = 0; q < NUM_QUEUES; ++q) out.queue_heads[q] = out.grid > q ? (out.grid - q + NUM_QUEUES - 1) / NUM_QUEUES : 0;
+    out.off_partial = out.plan_bytes;
+    out.total_bytes = out.off_partial + round_up(out.partial_floats * 4, 256);
+    if (out.total_bytes == 0) out.total_bytes = 256;
+}
+
 }  // namespace
 
 void plan_items(const Plan& plan, std::vector<Item>& out) {
-    if (!plan.by_table) {
+    if (!plan.by_table && !plan.by_tiles) {
         out = plan.items;
         return;
     }
     out.clear();
+    if (plan.by_tiles) {
+        for (int i = 0; i < plan.tiles.n_items; ++i) out.push_back(plan.tiles.items[i] == TILE_NULL ? null_item() : tile_item(plan.tiles, plan.tiles.items[i]));
+        if (plan.num_append > 0) add_append_items(plan, plan.tiles.append_rows, out);
+        return;
+    }
     const RowTable& t = plan.table;
     int row = 0;
     for (int i = 0; i < t.n_items; ++i) {
@@ -322,7 +512,6 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     // 1. query blocks
     int64_t block_chunk = 1 << 30;
     const bool blocks = !by_table && opt.force_kv_splits <= 0 && nhb == 1 && take_blocks(s, out.reqs, opt, &block_chunk);
-    std::vector<QBlock> qb;
     int64_t narrow_keys = 0;
     int64_t n_wide = 0;
     // (keys, number of blocks with that many): what the split policy needs to know of the blocks; noted for KV head 0
@@ -334,37 +523,25 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
         else
             runs.emplace_back(keys, 1);
     };
+    // f(first token, tokens) of every tile of tq tokens of a row of L.  A tile that is not full costs its workgroup nearly
+    // as much per key as a full one, so the remainder of the row goes into the FIRST tile, which sees the fewest keys.
+    auto each_tile = [](int32_t L, int tq, auto&& f) {
+        const int first = L % tq ? L % tq : tq;
+        for (int q0 = 0; q0 < L; q0 += q0 ? tq : first) f(q0, q0 ? tq : first);
+    };
+    narrow_runs.reserve(num_reqs);
     for (int r = 0; r < num_reqs; ++r) {
         const int C = ctx_len[r], L = incr_len[r];
-        if (L <= 0) continue;
-        if (by_table) {
-            narrow_keys += (int64_t)s.Hkv * (C + L);
-            note(narrow_runs, C + L);
-            continue;
-        }
-        for (int kvh = 0; kvh < s.Hkv; ++kvh) {
-            for (int hb = 0; hb < nhb; ++hb) {
-                const int g0 = hb * 32;
-                const int gn = std::min(32, G - g0);
-                const int tq_wave = 32 / gn;                   // tokens per wave (>= 1)
-                if ((int64_t)L * gn <= 32) {
-                    qb.push_back(QBlock{r, pack_heads(kvh, g0, gn, KIND_NARROW), 0, L, C + L, L * gn, KIND_NARROW});
-                    narrow_keys += C + L;
-                    if (kvh == 0) note(narrow_runs, C + L);
-                } else {
-                    // A tile that is not full costs its workgroup nearly as much per key as a full one, so the
-                    // remainder of the row goes into the FIRST tile, which sees the fewest keys.
-                    const int kind = blocks ? KIND_NARROW : KIND_WIDE;
-                    const int tq = blocks ? tq_wave : ATTN_WAVES * tq_wave;
-                    const int first = L % tq ? L % tq : tq;
-                    for (int q0 = 0; q0 < L; q0 += q0 ? tq : first) {
-                        const int nq = q0 ? tq : first;
-                        qb.push_back(QBlock{r, pack_heads(kvh, g0, gn, kind), q0, nq, C + q0 + nq, nq * gn, kind});
-                        if (blocks) continue;
-                        ++n_wide;
-                        if (kvh == 0) note(wide_runs, C + q0 + nq);
-                    }
-                }
+        for (int g0 = 0; g0 < G && L > 0; g0 += 32) {
+            const int gn = std::min(32, G - g0);
+            if ((int64_t)L * gn <= 32) {
+                narrow_keys += (int64_t)s.Hkv * (C + L);
+                note(narrow_runs, C + L);
+            } else if (!blocks) {
+                each_tile(L, ATTN_WAVES * (32 / gn), [&](int q0, int nq) {
+                    n_wide += s.Hkv;
+                    note(wide_runs, C + q0 + nq);
+                });
             }
         }
     }
@@ -506,41 +683,68 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
         return;
     }
 
+    if (blocks) {
+        build_blocks(s, (int32_t)block_chunk, (int32_t)std::min<int64_t>(narrow_chunk, 1 << 30), opt, out);
+        finish_plan(opt, out);
+        return;
+    }
+
     // 3. items
-    struct Cost { int64_t cost; int32_t idx; };
-    std::vector<Cost> order;
-    for (const QBlock& b : qb) {
+    struct Stream { int64_t cost = 0; int64_t max_keys = 0; std::vector<Cost> items; };
+    std::vector<Cost> nar;                                  // narrow items
+    std::vector<Stream> streams;                            // wide items by (request, KV head)
+    out.items.reserve(2 * opt.wg_slots);
+    nar.reserve(2 * opt.wg_slots);
+    double wide_cost = 0, narrow_cost = 0;
+    auto add_items = [&](int r, int kvh, int g0, int gn, int q0, int nq, int kind) {
+        const int64_t nkeys = ctx_len[r] + q0 + nq;
         int64_t chunk;
         if (opt.force_kv_splits > 0)
-            chunk = std::max<int64_t>(KV_TILE, round_up(ceil_div(b.nkeys, opt.force_kv_splits), KV_TILE));
+            chunk = std::max<int64_t>(KV_TILE, round_up(ceil_div(nkeys, opt.force_kv_splits), KV_TILE));
         else
-            chunk = b.kind == KIND_WIDE ? wide_chunk : blocks && out.reqs[b.req].L > 32 / G ? block_chunk : narrow_chunk;
-        const int nsplit = (int)ceil_div(b.nkeys, chunk);
-        const int32_t slot = b.rows * (s.D + 2);                // floats per partial slot
+            chunk = kind == KIND_WIDE ? wide_chunk : narrow_chunk;
+        const int nsplit = (int)ceil_div(nkeys, chunk);
+        const int32_t slot = nq * gn * (s.D + 2);               // floats per partial slot
+        const int32_t heads = pack_heads(kvh, g0, gn, kind);
         int64_t part0 = -1;
         if (nsplit > 1) {
             part0 = out.partial_floats;
             out.partial_floats += (int64_t)slot * nsplit;
-            out.combs.push_back(CombItem{b.req, b.heads, b.q0, b.nq, (int32_t)part0, nsplit, slot, 0});
+            out.combs.push_back(CombItem{r, heads, q0, nq, (int32_t)part0, nsplit, slot, 0});
         }
         for (int sp = 0; sp < nsplit; ++sp) {
-            Item it;
-            it.req = b.req;
-            it.heads = b.heads;
-            it.q0 = b.q0;
-            it.nq = b.nq;
-            it.kv_begin = (int32_t)(sp * chunk);
-            it.kv_end = (int32_t)std::min<int64_t>(b.nkeys, (sp + 1) * chunk);
-            it.part_off = nsplit > 1 ? (int32_t)(part0 + (int64_t)sp * slot) : -1;
-            it.C = out.reqs[b.req].C;
-            it.row_off = out.reqs[b.req].row_off;
-            it.row_L = out.reqs[b.req].L;
-            it.pad[0] = it.pad[1] = 0;
-            const int64_t keys = it.kv_end - it.kv_begin;
-            const int64_t cost = b.kind == KIND_WIDE ? keys * 4 : keys;
-            order.push_back(Cost{cost, (int32_t)out.items.size()});
-            out.items.push_back(it);
-            if (b.kind == KIND_WIDE) ++out.num_wide; else ++out.num_narrow;
+            const int32_t begin = (int32_t)(sp * chunk), end = (int32_t)std::min<int64_t>(nkeys, (sp + 1) * chunk);
+            const Cost c{(end - begin) * (int64_t)(kind == KIND_WIDE ? 4 : 1), (int32_t)out.items.size(), 0};
+            out.items.push_back(Item{r, heads, q0, nq, begin, end, nsplit > 1 ? (int32_t)(part0 + (int64_t)sp * slot) : -1, ctx_len[r],
+                                     out.reqs[r].row_off, incr_len[r], {0, 0}});
+            if (kind == KIND_WIDE) {
+                ++out.num_wide;
+                wide_cost += (double)c.cost;
+                Stream& st = streams.back();
+                st.cost += c.cost;
+                st.max_keys = std::max<int64_t>(st.max_keys, end);
+                st.items.push_back(c);
+            } else {
+                ++out.num_narrow;
+                narrow_cost += (double)c.cost;
+                nar.push_back(c);
+            }
+        }
+    };
+    for (int r = 0; r < num_reqs; ++r) {
+        const int L = incr_len[r];
+        for (int kvh = 0; kvh < s.Hkv && L > 0; ++kvh) {
+            bool stream = false;
+            for (int g0 = 0; g0 < G; g0 += 32) {
+                const int gn = std::min(32, G - g0);
+                if ((int64_t)L * gn <= 32) {
+                    add_items(r, kvh, g0, gn, 0, L, KIND_NARROW);
+                    continue;
+                }
+                if (!stream) streams.emplace_back();
+                stream = true;
+                each_tile(L, ATTN_WAVES * (32 / gn), [&](int q0, int nq) { add_items(r, kvh, g0, gn, q0, nq, KIND_WIDE); });
+            }
         }
     }
 
@@ -561,47 +765,26 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
     //    any time some CUs run compute-bound tiles while others stream decode rows (or, see wide_first, the tiles
     //    go first because they leave slots for that).
     //    Everything is stable and depends on the lengths only.
-    std::vector<int32_t> wide_ix, narrow_ix;
-    double wide_cost = 0, narrow_cost = 0;
-    if (blocks && order_blocks(out.items, G, opt.wg_slots, wide_ix)) {
-        // (blocks that would make one tile, next to each other on one die)
-    } else {
-        std::vector<Cost> nar;
-        struct Stream { int64_t cost = 0; int64_t max_keys = 0; std::vector<Cost> items; };
-        std::vector<Stream> streams;
-        std::vector<int32_t> stream_of((size_t)num_reqs * s.Hkv, -1);
-        for (const Cost& c : order) {
-            const Item& it = out.items[c.idx];
-            if (((it.heads >> 24) & 0xff) != KIND_WIDE) {
-                nar.push_back(c);
-                narrow_cost += (double)c.cost;
-                continue;
-            }
-            wide_cost += (double)c.cost;
-            int32_t& sid = stream_of[(size_t)it.req * s.Hkv + (it.heads & 0xff)];
-            if (sid < 0) {
-                sid = (int32_t)streams.size();
-                streams.emplace_back();
-            }
-            Stream& st = streams[sid];
-            st.cost += c.cost;
-            st.max_keys = std::max<int64_t>(st.max_keys, it.kv_end);
-            st.items.push_back(c);
-        }
-        std::stable_sort(nar.begin(), nar.end(), [](const Cost& a, const Cost& b) { return a.cost > b.cost; });
-        for (const Cost& c : nar) narrow_ix.push_back(c.idx);
+    longest_first(nar);
+    std::vector<int32_t> wide_ix;
+    if (!streams.empty()) {
 
         // a. pieces well below one XCD's share, dealt to the least loaded XCD, heaviest first
         const int64_t share = std::max<int64_t>(1, ceil_div((int64_t)wide_cost, NUM_XCD));
         std::vector<Stream> pieces;
+        pieces.reserve(streams.size());
         for (Stream& st : streams) {
-            std::stable_sort(st.items.begin(), st.items.end(), [](const Cost& a, const Cost& b) { return a.cost > b.cost; });
+            longest_first(st.items);
             // pieces of a quarter share let the dies mix long and short streams, but a piece keeps at least 8
             // tiles so that a die still reuses what it fetched; a power of two, so that equal streams deal evenly
             const int64_t want = std::max<int64_t>(1, std::min<int64_t>(ceil_div(4 * st.cost, share), (int64_t)st.items.size() / 8));
             int np = 1;
             while (2 * np <= want && np < NUM_XCD) np *= 2;
             const size_t base = pieces.size();
+            if (np == 1) {
+                pieces.push_back(std::move(st));
+                continue;
+            }
             pieces.resize(base + np);
             for (size_t i = 0; i < st.items.size(); ++i) {         // deal the tiles round-robin: equal pieces
                 Stream& pc = pieces[base + i % np];
@@ -652,30 +835,31 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
             for (int x = 0; x < NUM_XCD; ++x) t = std::max(t, finish_time(q[x]));
             return t;
         };
-        {
+        // the next move: from the heaviest queue to the lightest, if it lowers the maximum
+        auto move_of = [](const std::vector<Cost>* q, const int64_t* sum, int* hi, int* lo) {
+            *hi = *lo = 0;
+            for (int x = 1; x < NUM_XCD; ++x) {
+                if (sum[x] > sum[*hi]) *hi = x;
+                if (sum[x] < sum[*lo]) *lo = x;
+            }
+            return !q[*hi].empty() && sum[*lo] + q[*hi].back().cost < sum[*hi];
+        };
+        int hi, lo;
+        if (move_of(queue, bin_cost, &hi, &lo)) {
             std::vector<Cost> trial[NUM_XCD];
             int64_t sum[NUM_XCD];
             for (int x = 0; x < NUM_XCD; ++x) {
                 trial[x] = queue[x];
                 sum[x] = bin_cost[x];
             }
-            bool moved = false;
-            for (size_t moves = 0; moves < out.items.size(); ++moves) {
-                int hi = 0, lo = 0;
-                for (int x = 1; x < NUM_XCD; ++x) {
-                    if (sum[x] > sum[hi]) hi = x;
-                    if (sum[x] < sum[lo]) lo = x;
-                }
-                if (trial[hi].empty()) break;
+            for (size_t moves = 0; moves < out.items.size() && move_of(trial, sum, &hi, &lo); ++moves) {
                 const Cost c = trial[hi].back();
-                if (sum[lo] + c.cost >= sum[hi]) break;
                 trial[hi].pop_back();
                 trial[lo].push_back(c);
                 sum[hi] -= c.cost;
                 sum[lo] += c.cost;
-                moved = true;
             }
-            if (moved && launch_time(trial) < launch_time(queue))
+            if (launch_time(trial) < launch_time(queue))
                 for (int x = 0; x < NUM_XCD; ++x) queue[x].swap(trial[x]);
         }
         // c. interleave; -1 stands for a null item that pads a shorter queue
@@ -686,21 +870,21 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
         while (!wide_ix.empty() && wide_ix.back() < 0) wide_ix.pop_back();
     }
     std::vector<Item> sorted;
-    sorted.reserve(out.items.size());
+    sorted.reserve(wide_ix.size() + nar.size() + (opt.append_items ? ceil_div(out.sum_L, APPEND_ITEM_ROWS) : 0));
     {
         size_t iw = 0, in = 0;
         double dw = 0, dn = 0;                     // cost already emitted per kind
-        while (iw < wide_ix.size() || in < narrow_ix.size()) {
+        while (iw < wide_ix.size() || in < nar.size()) {
             bool take_wide;
             if (iw >= wide_ix.size()) take_wide = false;
-            else if (in >= narrow_ix.size()) take_wide = true;
+            else if (in >= nar.size()) take_wide = true;
             else if (wide_first) take_wide = true;
             else take_wide = dw * narrow_cost <= dn * wide_cost;      // the kind that lags behind its share
             for (int k = 0; k < NUM_XCD; ++k) {
-                if (take_wide ? iw >= wide_ix.size() : in >= narrow_ix.size()) break;
-                const int32_t idx = take_wide ? wide_ix[iw++] : narrow_ix[in++];
+                if (take_wide ? iw >= wide_ix.size() : in >= nar.size()) break;
+                const int32_t idx = take_wide ? wide_ix[iw++] : nar[in++].idx;
                 if (idx < 0) {
-                    sorted.push_back(Item{-1, pack_heads(0, 0, 0, KIND_NULL), 0, 0, 0, 0, -1, 0, 0, 0, {0, 0}});
+                    sorted.push_back(null_item());
                     continue;
                 }
                 const Item& it = out.items[idx];
@@ -711,40 +895,14 @@ void build_plan(const Shape& s, int num_reqs, const int32_t* ctx_len, const int3
         }
     }
     out.items.swap(sorted);
-    out.num_combs = (int64_t)out.combs.size();
 
     // Over a bf16 cache nothing runs in front of the attention launch that could carry the list along: a small one of tiles alone
     // travels in the arguments instead of an upload launch (5 us: one prefill of 32 tokens 10.4 -> 7.6 us a call, one
     // of 509 tokens over 4 099 55.8 -> 49.5 with the small append items).
-    out.by_tiles = opt.force_kv_splits <= 0 && opt.kv_bytes == 2 && build_tiles(s, (int32_t)std::min<int64_t>(blocks ? block_chunk : wide_chunk, 1 << 30),
-                                                                                   (int32_t)std::min<int64_t>(narrow_chunk, 1 << 30), blocks, out);
+    out.by_tiles = opt.force_kv_splits <= 0 && opt.kv_bytes == 2 && build_tiles(s, (int32_t)std::min<int64_t>(wide_chunk, 1 << 30), out);
 
-    // 4b. append items
-    if (opt.append_items) {
-        const int rows = out.by_tiles ? out.tiles.append_rows : APPEND_ITEM_ROWS;
-        add_append_items(out, rows, out.items);
-        out.num_append = ceil_div(out.sum_L, rows);
-    }
-    out.num_items = (int64_t)out.items.size();
-
-    // 5. byte layout
-    if (out.by_tiles) {
-        out.grid = (int32_t)out.num_items;
-        out.total_bytes = std::max<int64_t>(256, round_up(out.partial_floats * 4, 256));
-        return;
-    }
-    out.off_reqs = 0;
-    out.off_items = round_up((int64_t)out.reqs.size() * sizeof(ReqInfo), 256);
-    out.off_combs = out.off_items + round_up((int64_t)out.items.size() * sizeof(Item), 256);
-    out.off_queues = out.off_combs + round_up((int64_t)out.combs.size() * sizeof(CombItem), 256);
-    out.plan_bytes = out.off_queues + 256;
-    // persistent workgroups pay off where tiles are in the launch (the dies finish together: -1.2 % on configuration 2, -3.5 % on
-    // the fused mixed launch of configuration 3); a launch of decode rows alone gains nothing from them (+-1 %)
-    out.grid = (int32_t)(out.num_wide > 0 ? std::min<int64_t>((int64_t)out.items.size(), opt.wg_slots) : (int64_t)out.items.size());
-    for (int q = 0; q < NUM_QUEUES; ++q) out.queue_heads[q] = out.grid > q ? (out.grid - q + NUM_QUEUES - 1) / NUM_QUEUES : 0;
-    out.off_partial = out.plan_bytes;
-    out.total_bytes = out.off_partial + round_up(out.partial_floats * 4, 256);
-    if (out.total_bytes == 0) out.total_bytes = 256;
+    // 5. append items and byte layout
+    finish_plan(opt, out);
 }
 
 }  // namespace ampd

@@ -195,7 +195,7 @@ struct Plan {
     // (plan_items() writes the items out for a caller that wants to see them).
     bool by_table = false;
     RowTable table;
-    // A small launch of tiles alone over a bf16 cache: `tiles` says the same as items and combs.
+    // A small launch of tiles or blocks alone over a bf16 cache: `tiles` stands for items, which stay empty, and says the same as combs.
     bool by_tiles = false;
     TileTable tiles;
     int64_t num_items = 0, num_combs = 0;
