@@ -154,8 +154,10 @@ bool take_blocks(const Shape& s, const std::vector<ReqInfo>& reqs, const PlanOpt
     }
     if (few != tiles) {
         // Next to decode rows: only where the tiles last longer than those would alone (otherwise the launch is a matter of cutting
-        // the decode rows well: 76 rows of 2.5-6 k tokens next to two of up to 30 34.5 -> 43.6); tiles would need a list in the
-        // workspace there (bf16: an upload launch).
+        // the decode rows well: 76 rows of 2.5-6 k tokens next to two of up to 30 34.5 -> 43.6).  Over a bf16 cache tiles cost 4 us more there:
+        // their list needs an upload launch, which most blocks do without (see build_blocks), and where the blocks' list does not fit the
+        // arguments either, tiles are still dearer than priced above: 70 such drawn batches, which go as blocks for those
+        // 4 us alone, take 1.17 times as long sent as tiles (37 short rows next to two prefills 23.1 -> 37.9, the most; the least 0.84).
         int64_t chunk;
         const int64_t others = price(few, tiles, &chunk);
         if (others > best_tiles) return false;

@@ -17,6 +17,7 @@ CASES = {
     "cut": ([4000], [40], 8, 1, 128, 32, True, True),                                # pieces and a combine pass
     "new-tokens-alone": ([0, 0], [200, 16], 8, 1, 128, 64, True, True),              # every key is a new token
     "with-decode-rows": ([200, 900, 90], [1, 60, 1], 16, 4, 64, 16, True, True),
+    "no-room-in-the-table": ([250 + 7 * i for i in range(20)] + [700], [1] * 20 + [60], 8, 2, 64, 16, True, True),  # with a list in the workspace too
     "long-decode-rows": ([7000, 90, 15000], [1, 60, 1], 16, 4, 64, 16, False, False), # they last longer than the tiles would
     "rows-17": ([20 * i for i in range(17)], [9 + i for i in range(17)], 8, 2, 64, 16, True, True),   # more rows than the table holds
     "blocks-256": ([900], [256], 32, 8, 128, 16, True, True),
