@@ -1,12 +1,16 @@
 // The binding's calls with every argument of its usual kind (torch tensors, int32 numpy arrays, a KVCache of plain numbers): the
 // ampd_kv_cache and ampd_batch structures are filled and the entry point is called without an interpreted step per field.  call()
 // returns the status, or None, before anything is called, when an argument is of another kind: the binding then takes its general path.
+// A C++ exception out of an entry point (host memory gone in the planner, say) becomes a Python one, with the interpreter's lock held
+// again: work may be enqueued by then, so the call is never made a second time.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
 #include <cfloat>
 #include <climits>
 #include <cmath>
+#include <exception>
+#include <new>
 
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -92,14 +96,32 @@ typedef ampd_status (*AttnFn)(const ampd_kv_cache*, const ampd_batch*, const voi
 typedef ampd_status (*AppendFn)(const ampd_kv_cache*, const ampd_batch*, const void*, const void*, void*);
 typedef ampd_status (*MoveFn)(const ampd_kv_cache*, const ampd_batch*, int32_t, int32_t, const void*, const void*, void*);
 
-// call(entry point's address, cache, ctx_len, incr_len, block_table, rest...); rest: q, k_new, v_new, out, workspace (attention);
+struct Unlocked {                                        // the interpreter's lock is given up while this lives
+    PyThreadState* state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+struct Call {                                            // the arguments of an entry point
+    void* fn;
+    Py_ssize_t n;
+    ampd_kv_cache c = {};
+    ampd_batch b = {};
+    Lengths ctx, incr;                                   // (b points into them)
+    int32_t heads[2] = {0, 0};
+    void* p[5];
+    size_t ws_bytes = 0;
+    void* stream;
+};
+
+// args: the entry point's address, cache, ctx_len, incr_len, block_table, rest...; rest: q, k_new, v_new, out, workspace (attention);
 // k, v (append); head_begin, head_count, k, v (pack, unpack).  Runs on torch's current stream.  False: not of the usual kind.
-bool run(PyObject* const* a, Py_ssize_t n, ampd_status* status) {
+bool marshal(PyObject* const* a, Py_ssize_t n, Call& x) {
     if (n != 7 && n != 9 && n != 10) return false;
     if (!g_device || !PyLong_CheckExact(a[0])) return false;
-    void* fn = PyLong_AsVoidPtr(a[0]);
-    if (!fn) return false;
-    ampd_kv_cache c = {};
+    x.n = n;
+    x.fn = PyLong_AsVoidPtr(a[0]);
+    if (!x.fn) return false;
+    ampd_kv_cache& c = x.c;
     PyObject* cache = a[1];
     if (!int_attr(cache, s_num_q_heads, &c.num_q_heads) || !int_attr(cache, s_num_kv_heads, &c.num_kv_heads) ||
         !int_attr(cache, s_head_dim, &c.head_dim) || !int_attr(cache, s_page_size, &c.page_size) || !int_attr(cache, s_kv_dtype, &c.kv_dtype))
@@ -115,54 +137,59 @@ bool run(PyObject* const* a, Py_ssize_t n, ampd_status* status) {
     {
         Ref f(PyObject_GetAttr(cache, s_softmax_scale));
         if (!f.o || !PyFloat_CheckExact(f.o)) return false;
-        const double x = PyFloat_AS_DOUBLE(f.o);
-        if (!(std::fabs(x) <= FLT_MAX)) return false;
-        c.softmax_scale = (float)x;
+        const double scale = PyFloat_AS_DOUBLE(f.o);
+        if (!(std::fabs(scale) <= FLT_MAX)) return false;
+        c.softmax_scale = (float)scale;
     }
-    Lengths ctx, incr;
-    if (!ctx.take(a[2]) || !incr.take(a[3]) || ctx.b.shape[0] != incr.b.shape[0]) return false;
+    if (!x.ctx.take(a[2]) || !x.incr.take(a[3]) || x.ctx.b.shape[0] != x.incr.b.shape[0]) return false;
     const at::Tensor* bt;
     if (!tensor(a[4], &bt) || bt->dim() != 2 || !bt->is_cuda() || bt->size(1) > INT_MAX) return false;
-    ampd_batch b = {};
-    b.num_reqs = (int32_t)ctx.b.shape[0];
-    b.max_pages_per_req = (int32_t)bt->size(1);
-    b.h_ctx_len = static_cast<const int32_t*>(ctx.b.buf);
-    b.h_incr_len = static_cast<const int32_t*>(incr.b.buf);
-    b.d_block_table = static_cast<const int32_t*>(bt->data_ptr());
-    int32_t heads[2] = {0, 0};
+    x.b.num_reqs = (int32_t)x.ctx.b.shape[0];
+    x.b.max_pages_per_req = (int32_t)bt->size(1);
+    x.b.h_ctx_len = static_cast<const int32_t*>(x.ctx.b.buf);
+    x.b.h_incr_len = static_cast<const int32_t*>(x.incr.b.buf);
+    x.b.d_block_table = static_cast<const int32_t*>(bt->data_ptr());
     for (int i = 0; n == 9 && i < 2; ++i) {
         if (!PyLong_CheckExact(a[5 + i])) return false;
         int over = 0;
-        const long x = PyLong_AsLongAndOverflow(a[5 + i], &over);
-        if (over || x < INT_MIN || x > INT_MAX) return false;
-        heads[i] = (int32_t)x;
+        const long h = PyLong_AsLongAndOverflow(a[5 + i], &over);
+        if (over || h < INT_MIN || h > INT_MAX) return false;
+        x.heads[i] = (int32_t)h;
     }
-    void* p[5];
     const int first = n == 9 ? 7 : 5;
     for (int i = first; i < n; ++i)
-        if (!address(a[i], &p[i - first])) return false;
-    const size_t ws_bytes = n == 10 ? THPVariable_Unpack(a[9]).nbytes() : 0;
-    void* stream;
-    if (!current_stream(&stream)) return false;
-    Py_BEGIN_ALLOW_THREADS
-    if (n == 10) *status = reinterpret_cast<AttnFn>(fn)(&c, &b, p[0], p[1], p[2], p[3], p[4], ws_bytes, stream, nullptr);
-    else if (n == 9) *status = reinterpret_cast<MoveFn>(fn)(&c, &b, heads[0], heads[1], p[0], p[1], stream);
-    else *status = reinterpret_cast<AppendFn>(fn)(&c, &b, p[0], p[1], stream);
-    Py_END_ALLOW_THREADS
-    return true;
+        if (!address(a[i], &x.p[i - first])) return false;
+    if (n == 10) x.ws_bytes = THPVariable_Unpack(a[9]).nbytes();
+    return current_stream(&x.stream);
+}
+
+ampd_status enter(const Call& x) {
+    Unlocked u;
+    if (x.n == 10)
+        return reinterpret_cast<AttnFn>(x.fn)(&x.c, &x.b, x.p[0], x.p[1], x.p[2], x.p[3], x.p[4], x.ws_bytes, x.stream, nullptr);
+    if (x.n == 9) return reinterpret_cast<MoveFn>(x.fn)(&x.c, &x.b, x.heads[0], x.heads[1], x.p[0], x.p[1], x.stream);
+    return reinterpret_cast<AppendFn>(x.fn)(&x.c, &x.b, x.p[0], x.p[1], x.stream);
 }
 
 PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    ampd_status st = AMPD_OK;
-    bool done = false;
+    Call x;
+    bool usual = false;
     try {
-        done = run(args, n, &st);
+        usual = marshal(args, n, x);
     } catch (...) {                                      // a tensor without storage, say: the general path reports it
-        done = false;
     }
-    if (done) return PyLong_FromLong(st);
-    PyErr_Clear();
-    Py_RETURN_NONE;
+    if (!usual) {
+        PyErr_Clear();
+        Py_RETURN_NONE;
+    }
+    try {
+        return PyLong_FromLong(enter(x));
+    } catch (const std::bad_alloc&) {
+        return PyErr_NoMemory();
+    } catch (const std::exception& e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
 }
 
 // streams(current device, raw stream of a device): torch's functions

@@ -21,8 +21,6 @@ def recorder():
     b._fastcall = None                                       # the next real call hands torch's functions in again
 
 
-
-
 def _call(args, status=0):
     """(status or None, cache bytes, lengths, rest) of a call whose entry point is the recorder."""
     seen = []
@@ -101,3 +99,20 @@ def test_the_structures_equal_the_binding_s(recorder, n, fp8):
     assert st == 0 and list(seen[0][6]) == [1, 2, args[4].data_ptr(), args[5].data_ptr(), 0x1230]
     st, seen = _call(args[:6])
     assert st == 0 and list(seen[0][6]) == [args[4].data_ptr(), args[5].data_ptr(), 0x1230]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [10, 9, 7])
+@pytest.mark.parametrize("symbol,error", [("_ZSt17__throw_bad_allocv", MemoryError), ("_ZSt20__throw_length_errorPKc", RuntimeError)])
+def test_a_cpp_exception_of_the_entry_point_is_raised_once(recorder, symbol, error, n):
+    """The entry point throws (a function of the C++ runtime stands in): a Python exception, not None, which would have the binding make
+    the call a second time; and the interpreter's lock is held again."""
+    print("case: fastcall", symbol, n, flush=True)
+    args = _usual()
+    args[3] = args[3].cuda()
+    rest = {10: args[4:], 9: [0, 1] + args[4:6], 7: args[4:6]}[n]
+    entry = ctypes.cast(getattr(ctypes.CDLL("libstdc++.so.6"), symbol), VP).value
+    for _ in range(3):
+        with pytest.raises(error):
+            _fastcall.call(entry, *args[:4], *rest)
+    assert _call(args, status=-2)[0] == -2
