@@ -233,10 +233,10 @@ def _fast(name, *args):
             return None
         import torch
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is None or not hasattr(torch._C, "_cuda_getDevice"):
+        if raw is None or not hasattr(torch._C, "_cuda_getDevice") or not hasattr(torch._C, "_cuda_isInBadFork"):
             return None
         from . import _fastcall as module                                 # (built next to the library: no fallback for a missing one)
-        module.streams(torch._C._cuda_getDevice, raw)
+        module.streams(torch._C._cuda_getDevice, raw, torch._C._cuda_isInBadFork)
         _fastcall = module.call, {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in EXPORTED_SYMBOLS}
     call, address = _fastcall
     return call(address[name], *args)

@@ -19,7 +19,8 @@
 namespace {
 
 PyObject *s_num_q_heads, *s_num_kv_heads, *s_head_dim, *s_page_size, *s_kv_dtype, *s_k_pool, *s_v_pool, *s_k_scale, *s_v_scale, *s_softmax_scale;
-PyObject *g_device = nullptr, *g_raw_stream = nullptr;   // torch's functions: current device; raw stream of a device
+// torch's functions: current device; raw stream of a device; whether this process was forked from one that used the GPU (or null)
+PyObject *g_device = nullptr, *g_raw_stream = nullptr, *g_bad_fork = nullptr;
 
 struct Ref {                                             // an owned reference
     PyObject* o;
@@ -83,6 +84,10 @@ bool address_attr(PyObject* o, PyObject* name, void** p, bool may_be_none, int64
 }
 
 bool current_stream(void** stream) {
+    if (g_bad_fork) {                                    // torch refuses to look for the stream there: so does the general path
+        Ref bad(PyObject_CallNoArgs(g_bad_fork));
+        if (!bad.o || bad.o != Py_False) return false;
+    }
     Ref dev(PyObject_CallNoArgs(g_device));
     if (!dev.o) return false;
     Ref raw(PyObject_CallOneArg(g_raw_stream, dev.o));
@@ -192,16 +197,18 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
     }
 }
 
-// streams(current device, raw stream of a device): torch's functions
+// streams(current device, raw stream of a device[, forked from a process that used the GPU]): torch's functions
 PyObject* streams(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    if (n != 2 || !PyCallable_Check(args[0]) || !PyCallable_Check(args[1])) {
-        PyErr_SetString(PyExc_TypeError, "two functions");
+    bool ok = n == 2 || n == 3;
+    for (Py_ssize_t i = 0; ok && i < n; ++i) ok = PyCallable_Check(args[i]);
+    if (!ok) {
+        PyErr_SetString(PyExc_TypeError, "two or three functions");
         return nullptr;
     }
-    Py_INCREF(args[0]);
-    Py_INCREF(args[1]);
+    for (Py_ssize_t i = 0; i < n; ++i) Py_INCREF(args[i]);
     g_device = args[0];
     g_raw_stream = args[1];
+    g_bad_fork = n == 3 ? args[2] : nullptr;
     Py_RETURN_NONE;
 }
 

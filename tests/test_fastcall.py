@@ -116,3 +116,15 @@ def test_a_cpp_exception_of_the_entry_point_is_raised_once(recorder, symbol, err
         with pytest.raises(error):
             _fastcall.call(entry, *args[:4], *rest)
     assert _call(args, status=-2)[0] == -2
+
+
+@pytest.mark.gpu
+def test_a_process_forked_from_one_that_used_the_gpu_takes_the_general_path(recorder):
+    """There torch refuses to look for the current stream, and the general path with it; the extension asks before it enters the library."""
+    print("case: fastcall, forked", flush=True)
+    args = _usual()
+    args[3] = args[3].cuda()
+    for bad, entered in ((lambda: True, 0), (lambda: False, 1)):
+        _fastcall.streams(lambda: 0, lambda dev: 0x1230, bad)
+        assert len(_call(args)[1]) == entered
+    assert hasattr(torch._C, "_cuda_isInBadFork") and torch._C._cuda_isInBadFork() is False
