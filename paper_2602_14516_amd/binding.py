@@ -9,6 +9,7 @@ import ctypes
 import os
 import struct
 import types
+import warnings
 from dataclasses import dataclass
 
 import numpy as np
@@ -222,22 +223,36 @@ def _batch_arg(ctx_len, incr_len, block_table_dev, block_table_host=None):
 # Calls with arguments of the usual kind go through an extension module (csrc/fastcall.cpp), which fills the two structures itself and
 # answers None, before anything is called, for the others; those take the functions below.  Once the smallest launches take 6.5 us on the
 # GPU, 3 us of interpreted marshalling in front of 4 us of library and launch kept them 7.9 us apart.
-_fastcall = None
+_fastcall = None                 # (call, addresses of the entry points) after the first use; False: there is no such module
+
+
+def _load_fastcall():
+    if os.environ.get("AMPD_HOST_ONLY") == "1":
+        return False
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not hasattr(torch._C, "_cuda_getDevice") or not hasattr(torch._C, "_cuda_isInBadFork"):
+        return False
+    try:
+        from . import _fastcall as module
+        built_for = getattr(module, "torch_version", "an older one")
+        if built_for != torch.__version__:
+            raise ImportError(f"built for torch {built_for}, not {torch.__version__}")
+    except ImportError as e:                                              # not built, or for another Python or torch
+        warnings.warn(f"paper_2602_14516_amd: calls are marshalled without the extension module, 3 us slower each ({e}); "
+                      "python paper_2602_14516_amd/build.py builds it", RuntimeWarning)
+        return False
+    module.streams(torch._C._cuda_getDevice, raw, torch._C._cuda_isInBadFork)
+    return module.call, {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in EXPORTED_SYMBOLS}
 
 
 def _fast(name, *args):
     """The status of an entry point called that way, or None."""
     global _fastcall
     if _fastcall is None:
-        if os.environ.get("AMPD_HOST_ONLY") == "1":
-            return None
-        import torch
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is None or not hasattr(torch._C, "_cuda_getDevice") or not hasattr(torch._C, "_cuda_isInBadFork"):
-            return None
-        from . import _fastcall as module                                 # (built next to the library: no fallback for a missing one)
-        module.streams(torch._C._cuda_getDevice, raw, torch._C._cuda_isInBadFork)
-        _fastcall = module.call, {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in EXPORTED_SYMBOLS}
+        _fastcall = _load_fastcall()
+    if not _fastcall:
+        return None
     call, address = _fastcall
     return call(address[name], *args)
 

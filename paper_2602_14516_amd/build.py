@@ -79,7 +79,8 @@ def build_fastcall(force: bool = False) -> str:
         t = os.path.dirname(torch.__file__)
         subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"],
                                "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
-                               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", FAST_SRC, "-o", FAST_LIB,
+                               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                               f'-DAMPD_TORCH_VERSION="{torch.__version__}"', FAST_SRC, "-o", FAST_LIB,
                                "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{os.path.join(t, 'lib')}"])
     return FAST_LIB
 

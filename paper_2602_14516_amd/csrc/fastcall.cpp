@@ -9,6 +9,7 @@
 #include <cfloat>
 #include <climits>
 #include <cmath>
+#include <cstdlib>
 #include <exception>
 #include <new>
 
@@ -219,12 +220,26 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
+// The module is built for one Python and one torch: a file left over from before either changed is no module (its name carries no
+// version), instead of one that reads objects of another layout.  The binding compares torch_version.
 PyMODINIT_FUNC PyInit__fastcall() {
+    const char* v = Py_GetVersion();
+    char* end = nullptr;
+    const long major = std::strtol(v, &end, 10), minor = *end == '.' ? std::strtol(end + 1, nullptr, 10) : -1;
+    if (major != PY_MAJOR_VERSION || minor != PY_MINOR_VERSION) {
+        PyErr_Format(PyExc_ImportError, "built for Python %d.%d", PY_MAJOR_VERSION, PY_MINOR_VERSION);
+        return nullptr;
+    }
     struct { PyObject** at; const char* name; } names[] = {
         {&s_num_q_heads, "num_q_heads"}, {&s_num_kv_heads, "num_kv_heads"}, {&s_head_dim, "head_dim"}, {&s_page_size, "page_size"},
         {&s_kv_dtype, "kv_dtype"}, {&s_k_pool, "k_pool"}, {&s_v_pool, "v_pool"}, {&s_k_scale, "k_scale"}, {&s_v_scale, "v_scale"},
         {&s_softmax_scale, "softmax_scale"}};
     for (auto& n : names)
         if (!(*n.at = PyUnicode_InternFromString(n.name))) return nullptr;
-    return PyModule_Create(&module);
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", AMPD_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

@@ -128,3 +128,37 @@ def test_a_process_forked_from_one_that_used_the_gpu_takes_the_general_path(reco
         _fastcall.streams(lambda: 0, lambda dev: 0x1230, bad)
         assert len(_call(args)[1]) == entered
     assert hasattr(torch._C, "_cuda_isInBadFork") and torch._C._cuda_isInBadFork() is False
+
+
+@pytest.mark.parametrize("module", ["none", "another torch's", "this torch's"])
+def test_without_a_module_for_this_torch_calls_take_the_general_path(monkeypatch, module):
+    """The general path needs nothing of the module: one that was not built, or was built for another torch, costs time, not the call."""
+    import sys
+    import types
+    import warnings
+    import paper_2602_14516_amd as A
+    calls = []
+    stand_in = types.ModuleType("paper_2602_14516_amd._fastcall")
+    stand_in.torch_version = torch.__version__ if module == "this torch's" else "0.0"
+    stand_in.streams = lambda *functions: None
+    stand_in.call = lambda *args: calls.append(args)
+    monkeypatch.setitem(sys.modules, "paper_2602_14516_amd._fastcall", None if module == "none" else stand_in)
+    monkeypatch.setattr(A, "_fastcall", stand_in, raising=False)
+    if module == "none":
+        monkeypatch.delattr(A, "_fastcall")
+    monkeypatch.setattr(b, "_fastcall", None)
+    monkeypatch.setattr(b, "_stream_ptr", lambda stream: 0)
+    if module == "this torch's":
+        assert b._fast("ampd_kv_append", 1) is None and len(calls) == 1
+        return
+    cache, ctx, inc, bt, k, v = _usual()[:6]
+    inc[:] = 0                                                            # no new tokens: the library returns before it touches the GPU
+    with pytest.warns(RuntimeWarning, match="extension"):
+        b.kv_append(cache, ctx, inc, bt, k, v)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")                                    # said once
+        b.kv_append(cache, ctx, inc, bt, k, v)
+    assert not calls and b._fastcall is False
+    inc[:] = -1
+    with pytest.raises(b.AmpdError):
+        b.kv_append(cache, ctx, inc, bt, k, v)
