@@ -1144,8 +1144,8 @@ struct BlockLoader {
     }
     // Every block issues the same number of loads (so that waiting for the older of two operands never waits for the younger one as
     // well): a slot past the key range is the last key's once more, and zeroed by commit_v.
-    template <bool DO_K, bool DO_V>
-    __device__ __forceinline__ void fetch_kv(const AttnParams& p, const ItemCtx& ic, int kbase, bool paced, int lane) {
+    template <bool DO_K, bool DO_V, bool SPACED>
+    __device__ __forceinline__ void fetch_kv(const AttnParams& p, const ItemCtx& ic, int kbase, int lane) {
         uint32_t lo = T::lane_off(lane);
         const bool plain = kbase + 32 <= min(ic.kv_end, ic.c_rows);     // uniform: all keys in pages (8-bit: or anything there)
         if (plain) {
@@ -1157,7 +1157,7 @@ struct BlockLoader {
                 for (int i = 0; i < LPH; ++i) {
                     if (DO_K) k[h * LPH + i].v = __builtin_nontemporal_load((GlobalChunk)(ka + i * 1024 + lo));
                     if (DO_V) v[h * LPH + i].v = __builtin_nontemporal_load((GlobalChunk)(va + i * 1024 + lo));
-                    if (paced) __builtin_amdgcn_s_sleep(4);           // (see build_table)
+                    if (SPACED) __builtin_amdgcn_s_sleep(0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -1199,9 +1199,9 @@ constexpr int LEAN_ROWS = 8;
 // ROWS: query rows a wave carries (32, or 16 for items of at most 16 rows: half the matrix and softmax work per key)
 // NW: waves of the workgroup.  QUANT: the item appends its own new tokens (8-bit cache) before it reads its pages.
 // LEAN: K and V of a block take turns in one LDS region per wave, and the merge holds the item's rows only (at most 8).
-// rounded: see ItemCtx.  paced: see build_table.
-template <int D, int KVT, int ROWS, int NW, bool QUANT = false, bool LEAN = false>
-__device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& ic, uint32_t smem, int tid, bool rounded, bool paced = false) {
+// rounded: see ItemCtx.  SPACED: see decode_rows_kernel.
+template <int D, int KVT, int ROWS, int NW, bool QUANT = false, bool LEAN = false, bool SPACED = false>
+__device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& ic, uint32_t smem, int tid, bool rounded) {
     using G_ = Geo<D>;
     constexpr bool R16 = ROWS == 16;
     constexpr int NACC = ATTN_WAVES / NW;
@@ -1253,13 +1253,13 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
         ld.locate(p, ic, key0 + j * STEP);
         if ((j + 1) % ld.IDS == 0) ld.fetch_ids(p, ic, key0, STEP, j + 1, lane);
         ld.fetch_scales(p, ic);
-        ld.template fetch_kv<true, !LEAN>(p, ic, key0 + j * STEP, paced, lane);
+        ld.template fetch_kv<true, !LEAN, SPACED>(p, ic, key0 + j * STEP, lane);
     };
     auto first_block = [&]() {
         ld.take_pages(0);
         fetch(0);
         if constexpr (LEAN) {
-            ld.template fetch_kv<false, true>(p, ic, key0, paced, lane);
+            ld.template fetch_kv<false, true, SPACED>(p, ic, key0, lane);
             ld.take_pages(1);
         }
     };
@@ -1297,7 +1297,7 @@ __device__ __forceinline__ void narrow_body(const AttnParams& p, const ItemCtx& 
                 ld.commit_v(ic, kbase, vl, lane);
                 if (more) {
                     ld.take_pages(j + 2);
-                    ld.template fetch_kv<false, true>(p, ic, kbase + STEP, paced, lane);
+                    ld.template fetch_kv<false, true, SPACED>(p, ic, kbase + STEP, lane);
                 }
                 pv16<D>(vl, P, st, lane);
                 return;
@@ -1652,6 +1652,11 @@ __device__ __forceinline__ void append_table_rows(const AttnParams& p, const Row
 template <int D, int KVT, int NW>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : NW < ATTN_WAVES && KVT == KV_FP8 ? 3 : 2) void decode_rows_kernel(const AttnParams p, const RowTable t) {
     constexpr bool LEAN = NW < ATTN_WAVES && KVT == KV_FP8;
+    // An empty sleep between the pairs of loads of a block: where several items per CU saturate HBM it serves the loads better so than in one
+    // burst (96 rows of 2-16 k tokens over 8 KV heads 544 us without it, 541.6 with it; rows of 4-16 k 0.995), and it costs the others little
+    // (0.995 to 1.01 from 512 to 2 k tokens, 1.00 below; s_nop 7 and s_sleep 1 measure alike, s_sleep 4 costs rows of 64 tokens 3 %).
+    // Only there a block is enough loads to matter: 8-bit decode batches of d = 64 lose 0.3 % by it, d = 128 0.2 %.
+    constexpr bool SPACED = D == 128 && KVT == KV_BF16 && NW == ATTN_WAVES;
     __shared__ __attribute__((aligned(16))) char smem_raw[rows_smem<D, NW, LEAN>()];
     const uint32_t smem = (uint32_t)(uintptr_t)LDS_PTR(char, smem_raw);
     const int idx = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
@@ -1668,12 +1673,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : NW < ATTN_WAVES && KVT == KV
         row = (idx - t.n_whole) / t.Hkv;
     }
     const ItemCtx ic = item_ctx<KVT>(p, table_item(t, t.e[__builtin_amdgcn_readfirstlane(row)], idx));
-    // (only there a block is enough loads to matter: 8-bit decode batches of d = 64 lose 0.3 % by it, d = 128 0.2 %)
-    const bool paced = D == 128 && KVT == KV_BF16 && NW == ATTN_WAVES && t.paced;
     if (NW < ATTN_WAVES || ic.nq * ic.gn <= 16)
-        narrow_body<D, KVT, 16, NW, KVT == KV_FP8, LEAN>(p, ic, smem, tid, false, paced);   // (rows of at most 32 query rows)
+        narrow_body<D, KVT, 16, NW, KVT == KV_FP8, LEAN, SPACED>(p, ic, smem, tid, false);   // (rows of at most 32 query rows)
     else
-        narrow_body<D, KVT, 32, NW, KVT == KV_FP8>(p, ic, smem, tid, false, paced);
+        narrow_body<D, KVT, 32, NW, KVT == KV_FP8, false, SPACED>(p, ic, smem, tid, false);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -392,9 +392,6 @@ void build_table(const Shape& s, int32_t chunk, const PlanOptions& opt, Plan& ou
     // groups of 1 to 16 and pages of 16 to 64, 200 drawn decode batches run at 0.86 of their time before this table, the worst at 1.04.
     const int64_t slots = opt.wg_slots;
     t.small = t.n_items >= 2 * slots && 2 * n * s.Hkv < 3 * slots && keys_sum <= 8192 * slots;
-    // Several items per CU keep HBM saturated from end to end, and then it serves a wave's loads better in a trickle than in one burst
-    // (bf16, d = 128: 96 rows of 2-16 k tokens over 8 KV heads 556.5 -> 552.5 us); one item per CU is latency (four rows of 36-70 k 26.0 -> 26.7).
-    t.paced = t.n_items > slots;
     out.by_table = true;
     out.num_narrow = t.n_items;
     out.num_append = opt.append_items ? ceil_div(out.sum_L, APPEND_ITEM_ROWS) : 0;

@@ -86,7 +86,6 @@ struct RowTable {
     int32_t sum_L, Hkv, G, D;
     int32_t max_rows;     // query rows of the tallest item
     int32_t small;        // workgroups of 4 waves, several to a CU, where the kernel has them (see build_table)
-    int32_t paced;        // workgroups of 8 waves over a bf16 cache of d = 128 space their loads out (see build_table)
     RowEntry e[ROW_TABLE_MAX];
 };
 
