@@ -45,7 +45,8 @@ def test_head_group_shapes(name, C, L, Hq, Hkv, d, P):
     ([1325, 1308, 459, 27], [549, 501, 544, 20], 8, 1),
 ])
 def test_launch_order_with_null_items(C, L, Hq, Hkv):
-    """Few K/V streams: the per-die queues differ in length and are padded with null items, which must do nothing."""
+    """Few K/V streams: the per-die queues differ in length and are padded with null items, which must do nothing (blocks of 32 query
+    rows in the first two cases, tiles in the third)."""
     print(f"case: null items C={C} L={L}", flush=True)
     b = W.make_batch(C, L, Hq, Hkv, 128, 16, seed=sum(C) + Hq, poison=True)
     db = DevBatch(b)
@@ -58,8 +59,8 @@ def test_launch_order_with_null_items(C, L, Hq, Hkv):
 @pytest.mark.parametrize("k_mult", [6.0, 16.0])
 def test_sharp_logits_exercise_the_reference_maximum(k_mult):
     """Logits with a standard deviation of 6 and 16 (scale 1/sqrt(d) on keys 6x / 16x too large): the row maximum
-    keeps rising by more than the slack of the lazily raised reference, in wide tiles, narrow items and across
-    key splits, and the softmax is nearly one-hot."""
+    keeps rising by more than the slack of the lazily raised reference, in blocks of 32 query rows and decode rows (unforced), wide
+    tiles and across key splits (forced), and the softmax is nearly one-hot."""
     print(f"case: sharp logits x{k_mult}", flush=True)
     b = W.make_batch([900, 3000, 0, 517], [300, 1, 130, 9], 16, 4, 128, 16, seed=int(k_mult) + 40, k_mult=k_mult, poison=True)
     db = DevBatch(b)
@@ -73,7 +74,7 @@ def test_sharp_logits_exercise_the_reference_maximum(k_mult):
 def test_logits_rising_along_the_keys_keep_raising_the_reference(per_key, jump_every, jump):
     """Logits that grow with the key position (about +3 per key; steps of ~+2000 every 100 keys, far past the range of
     exp2 in fp32; both): every block needs a new reference, in the step cases the exponentials taken against the old
-    one overflow first.  Wide tiles, narrow items and key splits."""
+    one overflow first.  Blocks of 32 query rows and decode rows (unforced), wide tiles and key splits (forced)."""
     print(f"case: rising logits {per_key} {jump_every} {jump}", flush=True)
     b = W.make_batch([900, 3000, 0, 517], [300, 1, 130, 9], 16, 4, 128, 16, seed=71, poison=True)
     W.impose_key_ramp(b, per_key, jump_every, jump)
@@ -85,8 +86,8 @@ def test_logits_rising_along_the_keys_keep_raising_the_reference(per_key, jump_e
 
 @pytest.mark.parametrize("Hq,Hkv,d,P", [(8, 2, 64, 32), (6, 2, 64, 16), (32, 1, 128, 32)])
 def test_rising_logits_other_geometries(Hq, Hkv, d, P):
-    """The same ramp + steps with head dimension 64 (four steps per pipeline iteration instead of eight), G = 3 (idle
-    rows in every wave) and G = 32 (one token per wave)."""
+    """The same ramp + steps with head dimension 64, G = 3 (idle rows in every wave) and G = 32 (one token per wave): blocks of 32 query
+    rows in the first two, tiles in the third (tests/test_gpu_tiles.py runs all of them as tiles)."""
     print(f"case: rising logits Hq={Hq} Hkv={Hkv} d={d} P={P}", flush=True)
     b = W.make_batch([700, 1500, 0, 333], [260, 1, 150, 40], Hq, Hkv, d, P, seed=72, poison=True)
     W.impose_key_ramp(b, 1.0, 37, 400.0)
@@ -107,13 +108,15 @@ def test_more_requests_than_one_append_launch_carries():
     compare(b, out, label="303 rows")
 
 
-def test_chunked_prefill_composes_on_the_gpu():
+@pytest.mark.parametrize("C,L1,L2,tiles", [(700, 190, 333, False), (700, 1190, 1333, True)])
+def test_chunked_prefill_composes_on_the_gpu(C, L1, L2, tiles):
     """One call with L new tokens == a call with L1 followed by a call with L2 over C + L1 (the paper's
     future-work chunked local prefill needs no new kernel)."""
-    print("case: chunked prefill", flush=True)
-    C, L1, L2 = 700, 190, 333
+    print("case: chunked prefill", L1, L2, flush=True)
     b = W.make_batch([C], [L1 + L2], 8, 2, 128, 16, seed=9, poison=True)
     db = DevBatch(b)
+    for c, l in ((C, L1 + L2), (C, L1), (C + L1, L2)):
+        assert (A.plan_describe(db.cache, [c], [l], b.block_table.shape[1])["num_wide_items"] > 0) == tiles
     whole = run(db, fn=A.incr_prefill_attn)
     db2 = DevBatch(b)                                            # fresh pools
     o1 = A.incr_prefill_attn(db2.cache, [C], [L1], db2.bt, db2.q[:L1].contiguous(), db2.k_new[:L1].contiguous(),
@@ -124,7 +127,7 @@ def test_chunked_prefill_composes_on_the_gpu():
     parts = np.concatenate([from_dev_bits(o1), from_dev_bits(o2)])
     assert np.array_equal(from_dev_bits(db.k_pool), from_dev_bits(db2.k_pool))      # same final cache image
     assert np.array_equal(from_dev_bits(db.v_pool), from_dev_bits(db2.v_pool))
-    compare(b, parts, label="chunked")
+    compare(b, parts, rows=sample_rows(b, 24) if tiles else None, label="chunked")
     assert np.abs(W.bf16_bits_to_f64(parts) - W.bf16_bits_to_f64(whole)).max() <= 1e-2
 
 
@@ -169,10 +172,13 @@ def test_error_paths_enqueue_nothing():
     torch.cuda.synchronize()
 
 
-def test_runs_on_a_non_default_stream():
-    print("case: side stream", flush=True)
-    b = W.make_batch([300, 10], [90, 1], 8, 2, 128, 16, seed=15, poison=True)
+@pytest.mark.parametrize("C,L,upload", [([300, 10], [90, 1], False), ([900, 9000, 2000], [130, 1, 860], True)])
+def test_runs_on_a_non_default_stream(C, L, upload):
+    """With the work list in the arguments, and with one that is staged and uploaded on that stream."""
+    print("case: side stream", upload, flush=True)
+    b = W.make_batch(C, L, 8, 2, 128, 16, seed=15, poison=True)
     db = DevBatch(b)
+    assert (A.plan_describe(db.cache, b.ctx_len, b.incr_len, b.block_table.shape[1])["plan_bytes"] > 0) == upload
     ref = run(db)
     db2 = DevBatch(b)
     s = torch.cuda.Stream()
@@ -225,14 +231,18 @@ def test_many_calls_in_flight_never_wait_for_the_gpu():
         assert torch.equal(outs[i], outs[0])
 
 
-def test_two_host_threads_on_two_streams_share_the_library():
+@pytest.mark.parametrize("first", [([900, 40, 2000], [130, 1, 260]), ([900, 9000, 2000], [130, 1, 860])], ids=["args", "list"])
+def test_two_host_threads_on_two_streams_share_the_library(first):
     """Two host threads, each with its own stream, workspace and batch, call the library at the same time (ctypes releases
     the interpreter lock during a call): the staging ring and its sequence numbers are shared under a mutex, the last
-    plan is kept per thread.  Every output must equal the single-threaded result of its batch bit for bit."""
+    plan is kept per thread.  Every output must equal the single-threaded result of its batch bit for bit.  list: both batches
+    take staging buffers; args: one does, the other's list travels in the kernel's arguments."""
     import threading
     print("case: two host threads", flush=True)
-    batches = [W.make_batch([900, 40, 2000], [130, 1, 260], 16, 4, 128, 16, seed=91, poison=True),
+    batches = [W.make_batch(*first, 16, 4, 128, 16, seed=91, poison=True),
                W.make_batch([3000, 3100, 2900, 5], [1, 1, 1, 70], 16, 4, 128, 16, seed=92, poison=True)]
+    lists = [A.plan_describe(DevBatch(b).cache, b.ctx_len, b.incr_len, b.block_table.shape[1])["plan_bytes"] > 0 for b in batches]
+    assert lists == [max(first[0]) > 2000, True]
     refs = [run(DevBatch(b)) for b in batches]
     dbs = [DevBatch(b) for b in batches]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]

@@ -62,9 +62,12 @@ def errs(got_bits, ref_list, off):
 @pytest.mark.parametrize("name,C0,L0,L1,Hq,Hkv,d,P", [
     ("fp8-ragged", [0, 0, 0, 0], [137, 5, 264, 330], [1, 70, 9, 33], 8, 2, 128, 16),
     ("fp8-d64-p32", [0, 0], [150, 3], [20, 140], 8, 2, 64, 32),
+    ("fp8-ragged-tiles", [0, 0, 0, 0], [137, 5, 264, 330], [1, 70, 9, 33], 8, 2, 128, 16),
+    ("fp8-d64-p32-tiles", [0, 0], [150, 3], [20, 140], 8, 2, 64, 32),
 ])
 def test_fp8_append_bit_exact_and_attention_within_tolerance(name, C0, L0, L1, Hq, Hkv, d, P):
     print(f"case: {name}", flush=True)
+    splits = 1 if "tiles" in name else 0                                   # (unforced, these go as blocks of 32 query rows)
     rng = np.random.default_rng(7)
     B = len(C0)
     tot = np.array(L0) + np.array(L1)
@@ -90,7 +93,9 @@ def test_fp8_append_bit_exact_and_attention_within_tolerance(name, C0, L0, L1, H
         q = W.f32_to_bf16_bits(rng.standard_normal((n, Hq, d), dtype=np.float32))
         k = W.f32_to_bf16_bits(rng.standard_normal((n, Hkv, d), dtype=np.float32) * mag * (1.0 + 3 * step))
         v = W.f32_to_bf16_bits(rng.standard_normal((n, Hkv, d), dtype=np.float32) * mag)
-        out = A.mixed_batch_attn(pool.cache, C, L, d_bt, to_dev_bits(q), to_dev_bits(k), to_dev_bits(v), block_table_host=bt)
+        assert (A.plan_describe(pool.cache, C, L, bt.shape[1], splits)["num_wide_items"] > 0) == (splits == 1)
+        out = A.mixed_batch_attn(pool.cache, C, L, d_bt, to_dev_bits(q), to_dev_bits(k), to_dev_bits(v), block_table_host=bt,
+                                 force_kv_splits=splits)
         torch.cuda.synchronize()
         pool.reference_append(bt, C, L, k, v)
         pool.assert_equal()
@@ -128,7 +133,8 @@ def test_fp8_append_bit_exact_and_attention_within_tolerance(name, C0, L0, L1, H
         assert mx <= TOL_BF16[0] and mean <= TOL_BF16[1], f"vs dequantised cache: {mx:.2e} {mean:.2e}"
         print(f"  step {step}: vs dequantised {mx:.2e}/{mean:.2e}; V-rounding bound used to {vonly:.2f}; " + unq.finish(f"step {step}"), flush=True)
         # re-issuing the same call changes nothing (idempotent append incl. re-encoded old slots)
-        out2 = A.mixed_batch_attn(pool.cache, C, L, d_bt, to_dev_bits(q), to_dev_bits(k), to_dev_bits(v), block_table_host=bt)
+        out2 = A.mixed_batch_attn(pool.cache, C, L, d_bt, to_dev_bits(q), to_dev_bits(k), to_dev_bits(v), block_table_host=bt,
+                                  force_kv_splits=splits)
         torch.cuda.synchronize()
         pool.assert_equal()
         assert np.array_equal(from_dev_bits(out2), ob)

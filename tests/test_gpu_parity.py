@@ -210,13 +210,15 @@ def test_mixed_equals_separate_sub_batches():
         assert np.array_equal(o, mixed[off[r]:off[r + 1]]), f"row {r} differs between mixed and single-row launch"
 
 
-def test_page_permutation_is_bitwise_invariant_and_relaunch_idempotent():
-    print("case: permutation", flush=True)
+@pytest.mark.parametrize("splits", [0, 1], ids=["blocks", "tiles"])
+def test_page_permutation_is_bitwise_invariant_and_relaunch_idempotent(splits):
+    print("case: permutation", splits, flush=True)
     C, L = [333, 40, 1200], [70, 1, 5]
     b1 = W.make_batch(C, L, 8, 2, 128, 16, seed=41, poison=True)
     db1 = DevBatch(b1)
-    o1 = run_attn(db1)
-    o1b = run_attn(db1)                       # same call again: append and attention are idempotent
+    assert (A.plan_describe(db1.cache, C, L, b1.block_table.shape[1], splits)["num_wide_items"] > 0) == (splits == 1)
+    o1 = run_attn(db1, force_kv_splits=splits)
+    o1b = run_attn(db1, force_kv_splits=splits)                       # same call again: append and attention are idempotent
     assert np.array_equal(o1, o1b)
     # same logical content, other physical pages, bigger pool
     n2 = b1.num_pages + 37
@@ -232,7 +234,7 @@ def test_page_permutation_is_bitwise_invariant_and_relaunch_idempotent():
                 k2[bt2[r, c]] = b1.k_pool[b1.block_table[r, c]]
                 v2[bt2[r, c]] = b1.v_pool[b1.block_table[r, c]]
     b2 = W.Batch(b1.Hq, b1.Hkv, b1.d, b1.P, b1.scale, b1.ctx_len, b1.incr_len, bt2, n2, k2, v2, b1.q, b1.k_new, b1.v_new)
-    o2 = run_attn(DevBatch(b2))
+    o2 = run_attn(DevBatch(b2), force_kv_splits=splits)
     assert np.array_equal(o1, o2)
 
 

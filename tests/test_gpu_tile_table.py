@@ -1,5 +1,6 @@
-"""Small launches of tiles alone over a bf16 cache, whose work list travels in the kernel's arguments, and their neighbours that
-do not fit the table: every row of the batch against the oracle, the cache image bit for bit."""
+"""Small launches of prefill rows alone over a bf16 cache, whose work list travels in the kernel's arguments, and their neighbours that
+do not fit the table: every row of the batch against the oracle, the cache image bit for bit.  Most of these go as blocks of 32 query
+rows (TILES: as tiles; tests/test_gpu_tiles.py runs larger batches of the other shapes as tiles)."""
 import numpy as np
 import pytest
 import torch
@@ -27,12 +28,18 @@ CASES = [
     ("tiles-264", [0], [2049], 32, 8, 128, 16),
 ]
 
+TILES = {"cut", "many-pieces", "tiles-256", "tiles-264"}
+WORKSPACE = {"rows-17", "heads-65", "tiles-264"}                                # the list does not fit the arguments
+
 
 @pytest.mark.parametrize("name,C,L,Hq,Hkv,d,P", CASES, ids=[c[0] for c in CASES])
 def test_tile_launches(name, C, L, Hq, Hkv, d, P):
     print("case: tiles,", name, flush=True)
     b = W.make_batch(C, L, Hq, Hkv, d, P, seed=92, poison=True)
     db = DevBatch(b)
+    info = A.plan_describe(db.cache, b.ctx_len, b.incr_len, b.block_table.shape[1])
+    assert (info["num_wide_items"] > 0) == (name in TILES) and (info["num_narrow_items"] == 0) == (name in TILES)
+    assert (info["plan_bytes"] > 0) == (name in WORKSPACE)
     rows = sample_rows(b, 12) if sum(L) > 200 else None
     out = A.mixed_batch_attn(db.cache, b.ctx_len, b.incr_len, db.bt, db.q, db.k_new, db.v_new, block_table_host=b.block_table)
     torch.cuda.synchronize()

@@ -24,17 +24,20 @@ def _both(b, **kw):
     return ref_db, st_db, ref, out
 
 
-def test_static_workspace_entry_point_matches_the_workspace_one_on_two_calls_in_a_row():
-    print("case: static workspace, two calls", flush=True)
+@pytest.mark.parametrize("second,in_args", [(([1200, 64, 5], [1, 130, 3]), True), (([1200, 64, 5, 40], [1, 530, 3, 370]), False)], ids=["args", "list"])
+def test_static_workspace_entry_point_matches_the_workspace_one_on_two_calls_in_a_row(second, in_args):
+    print("case: static workspace, two calls", in_args, flush=True)
     A.init()
     assert A.static_workspace_limit() == 32 << 20
     # call 1: decode rows over long contexts (many key splits: partial results and a combine pass), a prefill row whose
-    # key range is split too (few wide tiles), and a short row; call 2: a smaller batch of the same kinds
+    # key range is split too (few wide tiles), and a short row; call 2: a smaller batch, as blocks of 32 query rows whose list travels
+    # in the arguments, or of the same kinds
     big = W.make_batch([9000, 4100, 300, 2500, 0], [1, 1, 700, 40, 9], 16, 2, 128, 16, seed=71, poison=True)
-    small = W.make_batch([1200, 64, 5], [1, 130, 3], 16, 2, 128, 16, seed=72, poison=True)
-    for b in (big, small):
+    small = W.make_batch(*second, 16, 2, 128, 16, seed=72, poison=True)
+    for b, args in ((big, False), (small, in_args)):
         info = A.plan_describe(DevBatch(b).cache, b.ctx_len, b.incr_len, b.block_table.shape[1])
         assert info["num_combine_items"] > 0 and info["partial_bytes"] > 0, "the case is meant to use the partial results"
+        assert (info["plan_bytes"] == 0) == args and (info["num_wide_items"] == 0) == args
     pending = [_both(big), _both(small)]              # both calls enqueued back to back before anything is read
     torch.cuda.synchronize()
     for b, (ref_db, st_db, ref, out) in zip((big, small), pending):
