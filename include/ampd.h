@@ -158,16 +158,16 @@ ampd_status ampd_kv_unpack(const ampd_kv_cache *cache, const ampd_batch *batch, 
  * keys (paper Section 3, performance model T_pre(l_hist, l_incr): a prefill with history
  * l_hist = C_r and incremental length l_incr = L_r; initial prefill is l_hist = 0).
  * This and ampd_mixed_batch_attn are one implementation under two names: the planner turns
- * rows with few query rows into split-KV items and the others into prefill tiles, whatever
- * the entry point.
+ * rows with few query rows into split-KV items and the others into prefill tiles (in small
+ * launches into blocks of 32 query rows), whatever the entry point.
  * bf16 cache: the page writes ride in the attention launch as work items of their own and the
  * attention items read the new tokens from k_new / v_new (which, like every DEVICE argument,
  * must stay valid until the call's stream work is done).  8-bit cache: a quantising append
  * launch runs first and attention reads the quantised pages; in a batch of decode rows alone
  * (every row has at most 32 query rows per KV head; up to 128 rows with new tokens) the items
  * that read a row's last pages quantise its new tokens themselves, and the work list travels
- * in the kernel's arguments (as it does for up to 256 prefill tiles or pieces of at most 16
- * rows alone over a bf16 cache).
+ * in the kernel's arguments (as it does for up to 256 prefill tiles, or blocks, or pieces of
+ * at most 16 rows over a bf16 cache).
  * q: DEVICE bf16 [sum L][Hq][d];  out: DEVICE bf16 [sum L][Hq][d].
  * workspace: DEVICE, 256-byte aligned, >= ampd_workspace_bytes(). */
 ampd_status ampd_incr_prefill_attn(const ampd_kv_cache *cache, const ampd_batch *batch,
@@ -232,14 +232,14 @@ ampd_status ampd_paged_attn(const ampd_kv_cache *cache, const ampd_batch *batch,
 typedef struct {
     int64_t num_items;          /* attention work items (= workgroups of the attention launch), null items included */
     int64_t num_wide_items;     /* prefill tiles: up to 256 query rows, 8 waves share K/V tiles */
-    int64_t num_narrow_items;   /* decode-style items: <= 32 query rows, 8 waves split the keys */
+    int64_t num_narrow_items;   /* items of <= 32 query rows, 8 waves split the keys: decode rows, blocks of a small launch */
     int64_t num_combine_items;  /* query tiles whose key range was split */
     int64_t num_append_launches; /* append launches that precede the attention launch (8-bit cache; 0 for bf16, and for
                                  * decode rows alone, whose items append) */
     int64_t partial_bytes;      /* split-KV partial results inside the workspace */
     int64_t plan_bytes;         /* work list inside the workspace (0: it travels in the kernel's arguments) */
-    int64_t num_append_items;   /* bf16 cache: page-write items (64 packed rows each, 4 to 64 in a small launch of tiles
-                                 * alone) that close the attention launch */
+    int64_t num_append_items;   /* bf16 cache: page-write items (64 packed rows each, 4 to 64 in a small launch whose
+                                 * list of tiles or blocks travels in the kernel's arguments) that close the attention launch */
     int64_t num_workgroups;     /* workgroups of the attention launch: num_items, or 256 persistent workgroups that work
                                  * through the items when the launch holds tiles and more items than that */
 } ampd_plan_info;

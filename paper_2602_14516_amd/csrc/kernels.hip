@@ -111,7 +111,7 @@ struct RawChunk<KV_BF16> {
     static constexpr int ES = 2;                      // bytes per stored element
     __device__ __forceinline__ void zero() { v = u32x4{0, 0, 0, 0}; }
     __device__ __forceinline__ void load(const char* base, uint32_t lane_off) {
-        v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + lane_off));   // streamed once: do not displace L2 lines
+        v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + lane_off));   // streamed: see BlockLoader
     }
     __device__ __forceinline__ u32x4 widen(float) const { return v; }
 };
@@ -1095,12 +1095,15 @@ struct NewToken {
 
 // K/V loader of one wave of a narrow item: 32-key blocks (from a multiple of 32), global -> registers -> the wave's LDS region.
 // A wave alone issues an instruction every four cycles or more, and the block loop used to be bound by that: page ids, branches and
-// 64-bit addresses for every 1 KB load were half of its instructions.  A block touches at most two pages (page size >= 16), so it
+// 64-bit addresses for every 1 KB load were a quarter of its instructions.  A block touches at most two pages (page size >= 16), so it
 // takes one address per half block, the loads of a half differ in their immediate offset only, and one vector load fetches
 // the page ids of the wave's next 8 blocks (scalar loads share their counter with LDS reads and return out of order: the first
 // fragment read of every block waited for the next block's page ids).  bf16 d = 128: 240 instructions a block instead of 330.
-// Four rows over 36-70 k keys in 8 bits 26.6 -> 25.9 us, 64 decode rows next to 8 prefill rows 89.3 -> 87.3 us; 90 drawn batches:
-// decode at d = 128 0.98 of its time before, at d = 64 (a block always was two or four loads a side) 1.00, mixed 0.99, small prefill 0.98.
+// Four rows over 36-70 k keys 26.6 -> 25.9 us; 90 drawn batches: decode at d = 128 0.98 of its time before, at d = 64 (a block always
+// was two or four loads a side) 1.00, mixed 0.99, small prefill 0.98.
+// Loads are non-temporal: a decode row's keys are read once and should not displace L2 lines (plain loads: more than 128 rows of up to
+// 2 k tokens 1.06 in 8 bits, 1.2 in bf16).  The eight blocks of a prefill row that share keys on a die find most of them in its L2 all the same
+// (256 tokens over 2 048: 85 % hits; 102 such launches with plain loads 1.00, the worst 1.05, the best 0.98).
 template <int D, int KVT>
 struct BlockLoader {
     using G_ = Geo<D>;
@@ -1615,10 +1618,10 @@ __global__ __launch_bounds__(AWG, KIND == KIND_NARROW && D == 64 ? 4 : 1) void a
 // The launch of a batch of decode rows alone whose work list travels in the arguments (see RowTable): one workgroup of NW
 // waves per item, then (bf16 cache) the append items.  Bound: HBM, and around an item's stream its latencies (item, page
 // ids, first block before the first key; merge behind the last), which only other items can hide.
-//   8 waves: one workgroup fills a CU (133 KB of LDS; 57 GB/s when it streams alone, over an 8-bit cache 41).  Few items,
+//   8 waves: one workgroup fills a CU (137 KB of LDS; 57 GB/s when it streams alone, over an 8-bit cache 41).  Few items,
 //     or whole rows that keep HBM busy by themselves.
-//   4 waves: two (bf16 cache: 223 -> 203 registers, 67 KB) or three workgroups per CU (8-bit cache: K and V of a block take
-//     turns in one LDS region and the merge holds 8 rows, 33 KB and 166 registers), so that an item's latencies pass under
+//   4 waves: two (bf16 cache: 232 -> 212 registers, 69 KB) or three workgroups per CU (8-bit cache: K and V of a block take
+//     turns in one LDS region and the merge holds 8 rows, 34 KB and 166 registers), so that an item's latencies pass under
 //     its neighbours' streams.
 // No list in memory means no upload launch in front; over an 8-bit cache the item that reads the pages of a row's new tokens
 // quantises them itself, so the append launch is gone too (25 rows of 0.7-7 k tokens over 8 KV heads: append 5.1 us + gap

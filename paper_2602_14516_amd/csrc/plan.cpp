@@ -104,7 +104,8 @@ bool take_blocks(const Shape& s, const std::vector<ReqInfo>& reqs, const PlanOpt
         return n;
     };
     // Both searches start from the uncut launch and end where the longest piece alone is no better than the best so far.
-    // blocks: rounds of 256 keys, whole or in pieces that fit one round (and the table); the pieces of a row's blocks read its
+    // blocks: rounds of 256 keys, whole or in pieces that fit one round, cut only while a table in the arguments holds the cut blocks (the
+    // rule the prices were fitted with, over lists in the workspace too); the pieces of a row's blocks read its
     // keys from the memory-side cache, at 8 TB/s
     const int64_t round_ns = d64 ? 1030 : 1750, start_ns = d64 ? 4700 : 6500;
     auto price = [&](const Run* v, const Run* e, int64_t* chunk) {
@@ -116,7 +117,11 @@ bool take_blocks(const Shape& s, const std::vector<ReqInfo>& reqs, const PlanOpt
             units += (int64_t)i->units * i->n;
             bytes += (int64_t)i->keys * i->n * 2 * s.D * opt.kv_bytes;
         }
-        const int64_t all = blocks > slots ? units * round_ns * 11 / (10 * slots) + 1000 : 0;      // (several rounds end unevenly)
+        // Between one block a CU and two: the second ones start late, and the fewer they are the less evenly the launch ends.  (80 launches of
+        // 257 to 512 blocks, 8-bit: with a fixed tenth on top, 10 were slower than as tiles, 7 rows of 40 tokens over 3 000 41.4 -> 46.4 the most.)
+        const int64_t all = blocks > slots ? units * round_ns * (10 * slots + 3 * std::max<int64_t>(0, 2 * slots - blocks)) / (10 * slots * slots) +
+                                                 (d64 ? 800 : 3500)
+                                           : 0;
         int64_t best = start_ns + 5 * blocks + std::max<int64_t>(longest * round_ns, all);
         *chunk = 1 << 30;
         if (blocks > TILE_TABLE_COMBS) return best;
@@ -164,6 +169,11 @@ bool take_blocks(const Shape& s, const std::vector<ReqInfo>& reqs, const PlanOpt
         best = std::max(std::max(best, others), start_ns + pieces(runs, tiles, 1) * round_ns * 11 / (10 * slots) + 1000);
         best_tiles += fp8 ? 0 : 4000;
     }
+    // The prices were fitted where this matters most, on launches of up to 40 us.  Longer ones are many rows of few tokens over long contexts,
+    // whose tiles run up to a fifth faster than that (their loads overlap across rows) and whose blocks read every key up to eight times: of 700
+    // such launches 51 were slower as blocks than as tiles (five rows of 20 to 130 tokens over 600 to 8 000, 8-bit 65.9 -> 84.3), with this 15.
+    constexpr int64_t LONG_NS = 38000;
+    if (best_tiles > LONG_NS) best_tiles = LONG_NS + (best_tiles - LONG_NS) * 6 / 10;
     return 100 * best <= 97 * best_tiles;
 }
 

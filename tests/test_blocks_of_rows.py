@@ -23,6 +23,8 @@ CASES = {
     "blocks-256": ([900], [256], 32, 8, 128, 16, True, True),
     "blocks-264": ([900], [257], 32, 8, 128, 16, False, True),                       # bf16: more than one round
     "blocks-520": ([900], [513], 32, 8, 128, 16, False, False),
+    "a-round-and-a-bit": ([0, 0], [222, 239], 32, 8, 128, 16, False, False),         # 464 blocks, each one trip: the second round costs a start
+    "many-long-rows": ([6850, 7994, 4209, 621, 6742], [71, 18, 39, 120, 134], 32, 8, 128, 16, False, False),   # 8-bit: 66 us as tiles, 84 as blocks
     "long-tiles": ([16384], [256], 32, 8, 128, 16, False, False),                    # the keys would be read eight times as often
 }
 
